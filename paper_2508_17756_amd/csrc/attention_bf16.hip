@@ -41,16 +41,6 @@ constexpr int kTileBytes = kBC * kRowBytes;          // one K (or V) stage: 16 K
 constexpr int kVRegion = kStages * kTileBytes;       // V stages start at 64 KiB
 constexpr int kLdsBytes = 2 * kStages * kTileBytes;  // 128 KiB
 
-// 16 bytes per lane from global memory straight into LDS: lane i fills bytes [16 i, 16 i + 16) of the
-// 1 KiB block at LDS byte address `lds_dst` (wave-uniform).  Address = sbase + voff (32-bit byte offset).
-// Inline assembly keeps the compiler from ordering later LDS reads behind the transfer; completion is
-// awaited explicitly with wait_vmcnt.  The statement overwrites m0 and says so.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"   // m0 is a reserved register; naming it as clobbered is the point
-__device__ __forceinline__ void dma16(const void* sbase, uint32_t voff, uint32_t lds_dst) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_dst), "v"(voff), "s"(sbase) : "memory", "m0");
-}
-#pragma clang diagnostic pop
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   static_assert(N == 0 || N == 4 || N == 8, "");

@@ -13,7 +13,24 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 #define SG_LDS __attribute__((address_space(3)))
+
+// 16 bytes per lane from global memory straight into LDS: lane i fills bytes [16 i, 16 i + 16) of the
+// 1 KiB block at LDS byte address `lds_dst` (wave-uniform).  Address = sbase + voff (32-bit byte offset), or
+// a 64-bit address per lane.
+// Inline assembly keeps the compiler from ordering later LDS reads behind the transfer; completion is
+// awaited explicitly on vmcnt.  The statements overwrite m0 and say so.
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"   // m0 is a reserved register; naming it as clobbered is the point
+__device__ __forceinline__ void dma16(const void* sbase, uint32_t voff, uint32_t lds_dst) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(lds_dst), "v"(voff), "s"(sbase) : "memory", "m0");
+}
+__device__ __forceinline__ void dma16_addr(const void* addr, uint32_t lds_dst) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(lds_dst), "v"(addr) : "memory", "m0");
+}
+#pragma clang diagnostic pop
 
 // ---------------------------------------------------------------------------------------------------
 // One launch attends up to kAttnTilesPerLaunch tiles of the same shape (Algorithm 1: for all tiles of the

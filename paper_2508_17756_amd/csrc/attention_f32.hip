@@ -1,160 +1,296 @@
-// Tile attention, fp32 throughout (paper Section 2.1 "full attention" restricted to one tile).
-// Plain vector-ALU kernel for SG_F32 problems, where fp32 accuracy matters more than speed:
-// a workgroup owns 64 query rows; its 4 wavefronts split the keys (each wavefront takes every
-// fourth 32-key chunk), one thread per query row and wavefront with q and o in registers, keys
-// and values staged through LDS and read back as wave-wide broadcasts, softmax in the online
-// (running max / running sum) form, which is algebraically the two-pass softmax.  The four
-// partial states (m, l, o) of a query are merged through LDS at the end.
+// Tile attention, fp32 throughout (paper Section 2.1 "full attention" restricted to one tile), for SG_F32
+// problems, on the fp32 matrix instruction (32x32x2: fp32 operands, fp32 accumulation, 64 FLOP per cycle and
+// SIMD; a large fp32 matrix product reaches 154 TFLOP/s on the same device).
+//
+// A workgroup owns QB x 32 query rows of one head and its 8 wavefronts split the keys (wavefront w takes the
+// 32-key blocks w, w + 8, ...), so that even one tile of a few hundred tokens gives every SIMD of its compute
+// units work, and no workgroup barrier stands in the key loop: every wavefront moves its own K blocks into
+// its own part of LDS (direct global->LDS transfers; K of the next block is requested when QK is done and has the
+// length of PV to arrive), reads its V rows straight into registers a few key pairs ahead, and keeps its own softmax
+// state; the 8 states of a query are merged through LDS at the end.  Two wavefronts per SIMD cover each other's softmax
+// and waits.  (One wavefront per SIMD with 64 queries and V in LDS as well, which halves what is read per FLOP, spills
+// its 512 registers around the rescaling of the accumulators: 2.14 ms where this takes 1.30.)
+//
+// Transposed products, S^T = K Q^T and O^T = V^T P^T, keep the probabilities in their lanes: accumulator register r
+// of S^T holds, for the lane's query, key 8 (r >> 2) + (r & 3) in the lower and that key + 4 in the upper half of the
+// wavefront, which is what the second product takes as its B operand for the key pair (k, k + 4).  The order of the
+// channels inside either product is free, so they are numbered such that a lane's operands of four (head_dim 64: two)
+// products are adjacent in LDS, and the results of a query adjacent in memory.
+//
+// Bound: matrix pipe (per 32 x 32 block and head_dim 128: 128 instructions of 64 cycles against 32 fragment reads
+// and 16 exponentials a lane).  Measured, before (vector ALU, keys and values broadcast from LDS) -> now, whole steps:
+// 4 tiles of 2,880 tokens, 8 heads x 128: 7.35 -> 1.30 ms (106 TFLOP/s in the kernel); 4 tiles of 300 tokens,
+// 2 heads x 64: 75.6 -> 17.6 us.
 #include <atomic>
 #include "attention_common.h"
 
 namespace sg {
 namespace {
 
-constexpr int kQ = 64;       // queries per workgroup
-constexpr int kSplit = 4;    // wavefronts per workgroup, each on its own share of the keys
-constexpr int kKC = 32;      // keys per wavefront and LDS chunk
+#define SG_INLINE __attribute__((always_inline))
 
-// element offset of tile token n from the tile's pointers (head 0); a wrapped window (shifted partition)
-// starts at canvas position (y0, x0) and wraps around both canvas edges
-__device__ __forceinline__ int64_t token_offset(const TileView& tv, int n, int y0, int x0) {
-  const int plane = tv.th * tv.tw;
-  const int t = n / plane, r = n - t * plane;
-  int i = r / tv.tw, j = r - i * tv.tw;
-  if (tv.wrapped) {
-    i += y0; j += x0;
-    i -= (i >= tv.H) ? tv.H : 0;
-    j -= (j >= tv.W) ? tv.W : 0;
-  }
-  return (((int64_t)t * tv.H + i) * tv.W + j) * tv.stride_token;
-}
+constexpr int kKeys = 32;    // keys per block
+constexpr int kXcd = 8;
+constexpr float kLog2e = 1.4426950408889634f;
+// The softmax reference moves only when a score exceeds it by this much (log2 domain): exponentials up to 2^8 lose
+// nothing in fp32, and the output accumulators are not rescaled for every new maximum.
+constexpr float kSlack = 8.0f;
 
-// grid: (query blocks, heads, tiles of the launch); a tile whose run flag is 0 is skipped
-template <int D>
-__global__ __launch_bounds__(kQ * kSplit) void attention_f32_kernel(const TileView tv, const float scale, const AttnTable tab,
-                                                                    const uint8_t* __restrict__ run_flags) {
-  const int tile = blockIdx.z;
-  if (run_flags && !run_flags[tile]) return;
-  const float* __restrict__ q = (const float*)tab.q[tile];
-  const float* __restrict__ k = (const float*)tab.k[tile];
-  const float* __restrict__ v = (const float*)tab.v[tile];
-  float* __restrict__ out = (float*)tab.out[tile];
-  const int y0 = tab.y0[tile], x0 = tab.x0[tile];
-  // [wavefront][key][d] chunks of K and V; after the key loop the same memory holds the partial outputs
-  extern __shared__ __attribute__((aligned(16))) float smem[];
-  float (*sK)[kKC][D] = (float (*)[kKC][D])smem;
-  float (*sV)[kKC][D] = (float (*)[kKC][D])(smem + kSplit * kKC * D);
-  const int head = blockIdx.y;
-  const int lane = threadIdx.x & (kQ - 1), wave = threadIdx.x / kQ;
-  const int n = blockIdx.x * kQ + lane;
-  const bool valid = n < tv.N;
-  const int64_t hoff = (int64_t)head * tv.stride_head;
+constexpr int KS = 8;          // wavefronts of a workgroup = shares of the keys: two per SIMD
+constexpr int kThreads = KS * 64;
+constexpr int kWaveBytes = 16384;   // LDS of a wavefront: its K block, after the key loop its partial output
+template <int QB>
+constexpr int kLds = KS * kWaveBytes + 2 * KS * QB * 32 * 4;   // and (reference, sum) per wavefront and query
 
-  float qr[D], o[D];
-  {
-    const float4* src = (const float4*)(q + hoff + token_offset(tv, valid ? n : tv.N - 1, y0, x0));
+enum { kCursor = 0, kLinearRows = 1, kWrappedRows = 2 };   // how a tile token is found
+
+template <int D, int QB, int MODE>
+__global__ __launch_bounds__(kThreads) void attention_f32_kernel(
+    const View16 vw, const float scale, const int heads, const int n_qblocks, const int n_tiles, const AttnTable tab,
+    const uint8_t* __restrict__ run_flags) {
+  static_assert(kKeys * D * 4 <= kWaveBytes && QB * 32 * D * 4 <= kWaveBytes, "K block and partial output");
+  constexpr int kPer = D / 32;   // channels a lane holds of one V row: output blocks
+  extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+  SG_LDS uint8_t* const lds = (SG_LDS uint8_t*)smem;
+
+  // (active tile, head, query block), query block fastest; each XCD walks a contiguous range (one head's K/V per L2)
+  const uint32_t active = attn_active_mask(run_flags, n_tiles);
+  const int per_tile = heads * n_qblocks;
+  const int total = __builtin_popcount(active) * per_tile;
+  const int per_xcd = (total + kXcd - 1) / kXcd;
+  const int slot_x = blockIdx.x / kXcd;
+  const int logical = (blockIdx.x % kXcd) * per_xcd + slot_x;
+  if (slot_x >= per_xcd || logical >= total) return;
+  const int nth = logical / per_tile, in_tile = logical - nth * per_tile;
+  const int tile = __builtin_amdgcn_readfirstlane(attn_nth_tile(active, nth));
+  const int head = in_tile / n_qblocks, qblk = in_tile - head * n_qblocks;
+  const int wy0 = (MODE == kWrappedRows) ? tab.y0[tile] : 0, wx0 = (MODE == kWrappedRows) ? tab.x0[tile] : 0;
+  // offset of tile token n from the tile's pointers, in units of 8 elements (32 bytes)
+  auto token_off8 = [&](int n) SG_INLINE -> uint32_t {
+    if (MODE == kLinearRows) return (uint32_t)n * vw.st16;
+    if (MODE == kWrappedRows) return wrap_offset16(vw, wrap_cursor_at(vw, n), wy0, wx0);
+    return cursor_at(vw, n).off16;
+  };
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const int lq = lane & 31, half = lane >> 5;
+  const int N = vw.N;
+  const size_t head_off = (size_t)head * vw.head16 * 32;
+  const char* const qh = (const char*)tab.q[tile] + head_off;
+  const char* const kh = (const char*)tab.k[tile] + head_off;
+  const char* const vh = (const char*)tab.v[tile] + head_off;
+
+  // ---- Q (B operand of S^T): query lq, step (c, j) contracts channel 8 c + j in the lower, 8 c + 4 + j in the upper half
+  const int q0 = qblk * (QB * 32);
+  float qr[QB][D / 8][4];
 #pragma unroll
-    for (int c = 0; c < D / 4; ++c) {
-      float4 x = src[c];
-      qr[4 * c] = x.x * scale; qr[4 * c + 1] = x.y * scale; qr[4 * c + 2] = x.z * scale; qr[4 * c + 3] = x.w * scale;
+  for (int qb = 0; qb < QB; ++qb) {
+    int n = q0 + 32 * qb + lq;
+    if (n > N - 1) n = N - 1;
+    const float4* src = (const float4*)(qh + (size_t)token_off8(n) * 32);
+#pragma unroll
+    for (int c = 0; c < D / 8; ++c) {
+      const float4 x = src[2 * c + half];
+      qr[qb][c][0] = x.x * scale; qr[qb][c][1] = x.y * scale; qr[qb][c][2] = x.z * scale; qr[qb][c][3] = x.w * scale;
     }
   }
-#pragma unroll
-  for (int c = 0; c < D; ++c) o[c] = 0.f;
-  float m = -__builtin_inff(), l = 0.f;
-  constexpr float kLog2e = 1.4426950408889634f;
 
-  // every wavefront loads and consumes its own chunk: no workgroup barrier inside the loop
-  for (int m0 = wave * kKC; m0 < tv.N; m0 += kSplit * kKC) {
-    const int cnt = (tv.N - m0 < kKC) ? tv.N - m0 : kKC;
-    for (int e = lane; e < kKC * (D / 4); e += kQ) {
-      const int row = e / (D / 4), c4 = e - row * (D / 4);
-      if (row < cnt) {
-        const int64_t off = hoff + token_offset(tv, m0 + row, y0, x0);
-        ((float4*)sK[wave][row])[c4] = ((const float4*)(k + off))[c4];
-        ((float4*)sV[wave][row])[c4] = ((const float4*)(v + off))[c4];
+  // ---- loader: one instruction moves 1 KiB = kRows rows; 16-byte chunk c of K row r sits at chunk c ^ (r & 15), so that
+  // the 32 rows read side by side (below) fall on different banks
+  constexpr int kChunks = D / 4;                 // 16-byte chunks per row
+  constexpr int kRows = 64 / kChunks;
+  constexpr int kInstr = kKeys / kRows;          // transfers per block: 16 (head_dim 64: 8)
+  const int sub = lane / kChunks, slot = lane % kChunks;
+  const uint32_t lds_k = (uint32_t)(uintptr_t)lds + wave * kWaveBytes;
+  auto block_off8 = [&](int b) SG_INLINE -> uint32_t {   // lane l: where key l % 32 of block b lies (keys >= N: the last one)
+    const int n = b * kKeys + lq;
+    return token_off8(n < N ? n : N - 1);
+  };
+  auto issue_k = [&](uint32_t off8) SG_INLINE {
+#pragma unroll
+    for (int i = 0; i < kInstr; ++i) {
+      const int row = kRows * i + sub;
+      const uint32_t o = (uint32_t)__shfl((int)off8, row, 64);
+      dma16_addr(kh + (size_t)o * 32 + ((slot ^ (row & 15)) << 4), lds_k + i * 1024);
+    }
+  };
+  // V straight into registers, one coalesced load per key pair (k, k + 4): the upper half of the wavefront reads row k + 4
+  typedef float vrow __attribute__((ext_vector_type(kPer)));
+  auto load_v = [&](uint32_t off8, int r) SG_INLINE -> vrow {
+    const uint32_t o = (uint32_t)__shfl((int)off8, 8 * (r >> 2) + (r & 3) + 4 * half, 64);
+    return *(const vrow*)(vh + (size_t)o * 32 + lq * (kPer * 4));
+  };
+  constexpr int kAhead = 4;   // key pairs whose V rows are in flight: 1,024 cycles of matrix work
+  auto reads_done = [&]() SG_INLINE {   // this wavefront's fragment reads have returned: the block may be overwritten
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  };
+
+  f32x16 acc[QB][kPer];
+  float ref[QB], l[QB];
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+#pragma unroll
+    for (int db = 0; db < kPer; ++db)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[qb][db][r] = 0.f;
+    ref[qb] = -__builtin_inff();   // log2 domain
+    l[qb] = 0.f;
+  }
+  uint32_t kaddr[8];   // chunk 2 c + half of row lq; bit 4 of the chunk is not swizzled: chunk 16 and on lie 256 bytes behind
+#pragma unroll
+  for (int c = 0; c < 8; ++c) kaddr[c] = lds_k + lq * (D * 4) + (((2 * c + half) ^ (lq & 15)) << 4);
+  auto kfrag = [&](int c) SG_INLINE -> f32x4 {
+    return *(const SG_LDS f32x4*)(uintptr_t)(kaddr[c & 7] + (c >> 3) * 256);
+  };
+
+  const int n_blocks = (N + kKeys - 1) / kKeys;
+  uint32_t off = 0;   // block_off8 of the block in work
+  if (wave < n_blocks) {
+    off = block_off8(wave);
+    issue_k(off);
+  }
+  for (int b = wave; b < n_blocks; b += KS) {
+    const bool more = b + KS < n_blocks;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // K of block b
+    __builtin_amdgcn_sched_barrier(0);
+    // ---- S^T = K Q^T; even and odd channel groups in accumulators of their own: two short chains round less than one
+    f32x16 s[QB][2];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+      for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[qb][e][r] = 0.f;
+    f32x4 a[D / 8];   // fragments are read two steps (512 cycles and more) ahead
+    a[0] = kfrag(0);
+    a[1] = kfrag(1);
+#pragma unroll
+    for (int c = 0; c < D / 8; ++c) {
+      if (c + 2 < D / 8) a[c + 2] = kfrag(c + 2);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
+          s[qb][c & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[c][j], qr[qb][c][j], s[qb][c & 1], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    reads_done();
+    uint32_t next = 0;
+    if (more) {
+      next = block_off8(b + KS);
+      issue_k(next);
+    }
+    vrow v[16];
+#pragma unroll
+    for (int r = 0; r < kAhead; ++r) v[r] = load_v(off, r);
+    __builtin_amdgcn_sched_barrier(0);
+    // ---- softmax
+    float p[QB][16];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) p[qb][r] = s[qb][0][r] + s[qb][1][r];
+      if (b == n_blocks - 1) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if (b * kKeys + 8 * (r >> 2) + 4 * half + (r & 3) >= N) p[qb][r] = -__builtin_inff();
       }
+      float mx = p[qb][0];
+#pragma unroll
+      for (int r = 1; r < 16; ++r) mx = fmaxf(mx, p[qb][r]);
+      const uint32_t mu = __float_as_uint(mx);
+      const auto sw = __builtin_amdgcn_permlane32_swap(mu, mu, false, false);
+      mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * kLog2e;
+      if (__any(!(mx <= ref[qb] + kSlack))) {   // also the first block, where the reference is -inf
+        const float moved = fmaxf(ref[qb], mx);
+        const float alpha = (ref[qb] == moved) ? 1.f : __builtin_amdgcn_exp2f(ref[qb] - moved);
+        ref[qb] = moved;
+        l[qb] *= alpha;
+#pragma unroll
+        for (int db = 0; db < kPer; ++db) acc[qb][db] *= alpha;
+      }
+      float l0 = 0.f, l1 = 0.f;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) p[qb][r] = __builtin_amdgcn_exp2f(fmaf(p[qb][r], kLog2e, -ref[qb]));
+#pragma unroll
+      for (int r = 0; r < 16; r += 2) { l0 += p[qb][r]; l1 += p[qb][r + 1]; }
+      l[qb] += l0 + l1;
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    float s[kKC];
-    float cmax = -__builtin_inff();
+    // ---- O^T += V^T P^T: row m of output block db is channel kPer m + db
 #pragma unroll
-    for (int r = 0; r < kKC; ++r) {
-      float a0 = 0.f, a1 = 0.f, a2 = 0.f, a3 = 0.f;
-      if (r < cnt) {
+    for (int r = 0; r < 16; ++r) {
+      if (r + kAhead < 16) v[r + kAhead] = load_v(off, r + kAhead);
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int c = 0; c < D / 4; ++c) {
-          const float4 kk = ((const float4*)sK[wave][r])[c];
-          a0 = fmaf(qr[4 * c], kk.x, a0); a1 = fmaf(qr[4 * c + 1], kk.y, a1);
-          a2 = fmaf(qr[4 * c + 2], kk.z, a2); a3 = fmaf(qr[4 * c + 3], kk.w, a3);
-        }
-        s[r] = (a0 + a1) + (a2 + a3);
-        cmax = fmaxf(cmax, s[r]);
+      for (int db = 0; db < kPer; ++db)
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) acc[qb][db] = __builtin_amdgcn_mfma_f32_32x32x2f32(v[r][db], p[qb][r], acc[qb][db], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    off = next;
+  }
+
+  // ---- merge the KS partial states of every query: a wavefront that saw no key has reference -inf, sum 0, output 0
+  SG_LDS float* const s_ref = (SG_LDS float*)(lds + KS * kWaveBytes);   // [KS][QB * 32]
+  SG_LDS float* const s_sum = s_ref + KS * QB * 32;
+  // partial output of (wavefront, query): D floats, kPer-float groups at m ^ (query & 31) so that neither side conflicts
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) {
+    const uint32_t lu = __float_as_uint(l[qb]);
+    const auto sw = __builtin_amdgcn_permlane32_swap(lu, lu, false, false);
+    if (half == 0) {
+      s_ref[wave * (QB * 32) + 32 * qb + lq] = ref[qb];
+      s_sum[wave * (QB * 32) + 32 * qb + lq] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int m = 8 * (r >> 2) + 4 * half + (r & 3);
+      const uint32_t at = lds_k + (32 * qb + lq) * (D * 4) + (m ^ lq) * (kPer * 4);
+      if constexpr (kPer == 4) {
+        const f32x4 x = {acc[qb][0][r], acc[qb][1][r], acc[qb][2][r], acc[qb][3][r]};
+        *(SG_LDS f32x4*)(uintptr_t)at = x;
       } else {
-        s[r] = -__builtin_inff();
+        const f32x2 x = {acc[qb][0][r], acc[qb][1][r]};
+        *(SG_LDS f32x2*)(uintptr_t)at = x;
       }
     }
-    const float m_new = fmaxf(m, cmax);
-    const float alpha = exp2f((m - m_new) * kLog2e);  // m = -inf on the first chunk gives 0
-    l *= alpha;
-#pragma unroll
-    for (int c = 0; c < D; ++c) o[c] *= alpha;
-#pragma unroll
-    for (int r = 0; r < kKC; ++r) {
-      if (r < cnt) {
-        const float p = exp2f((s[r] - m_new) * kLog2e);
-        l += p;
-#pragma unroll
-        for (int c = 0; c < D / 4; ++c) {
-          const float4 vv = ((const float4*)sV[wave][r])[c];
-          o[4 * c] = fmaf(p, vv.x, o[4 * c]); o[4 * c + 1] = fmaf(p, vv.y, o[4 * c + 1]);
-          o[4 * c + 2] = fmaf(p, vv.z, o[4 * c + 2]); o[4 * c + 3] = fmaf(p, vv.w, o[4 * c + 3]);
-        }
-      }
-    }
-    m = m_new;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();   // the chunk is consumed before the next one overwrites it
   }
-
-  // ---- merge the kSplit partial states of every query: a wavefront that saw no key has m = -inf, l = 0
   __syncthreads();
-  float* sM = smem;                          // [kSplit][kQ]
-  float* sL = smem + kSplit * kQ;            // [kSplit][kQ]
-  float* sO = smem + 2 * kSplit * kQ;        // [kSplit][D][kQ]  (query fastest: conflict-free)
-  sM[wave * kQ + lane] = m;
-  sL[wave * kQ + lane] = l;
+  if ((int)threadIdx.x < QB * 32) {   // weights of the KS states, normalised, in place of the references
+    const int q = threadIdx.x;
+    float top = s_ref[q];
 #pragma unroll
-  for (int c = 0; c < D; ++c) sO[(wave * D + c) * kQ + lane] = o[c];
+    for (int w = 1; w < KS; ++w) top = fmaxf(top, s_ref[w * (QB * 32) + q]);
+    float wgt[KS], sum = 0.f;
+#pragma unroll
+    for (int w = 0; w < KS; ++w) {
+      const float rw = s_ref[w * (QB * 32) + q];
+      wgt[w] = (rw == -__builtin_inff()) ? 0.f : __builtin_amdgcn_exp2f(rw - top);
+      sum += wgt[w] * s_sum[w * (QB * 32) + q];
+    }
+    const float inv = 1.0f / sum;
+#pragma unroll
+    for (int w = 0; w < KS; ++w) s_ref[w * (QB * 32) + q] = wgt[w] * inv;
+  }
   __syncthreads();
-  if (wave == 0 && valid) {
-    float mt = sM[lane];
+  float* const out = (float*)tab.out[tile] + (size_t)head * N * D;
+  for (int e = threadIdx.x; e < QB * 32 * 32; e += kThreads) {   // (query, group of kPer channels), group fastest
+    const int q = e >> 5, m = e & 31;
+    if (q0 + q >= N) break;   // queries rise with e
+    float o[kPer];
 #pragma unroll
-    for (int w = 1; w < kSplit; ++w) mt = fmaxf(mt, sM[w * kQ + lane]);
-    float lt = 0.f;
-    float wgt[kSplit];
+    for (int x = 0; x < kPer; ++x) o[x] = 0.f;
 #pragma unroll
-    for (int w = 0; w < kSplit; ++w) {
-      const float mw = sM[w * kQ + lane];
-      wgt[w] = (mw == -__builtin_inff()) ? 0.f : exp2f((mw - mt) * kLog2e);
-      lt += wgt[w] * sL[w * kQ + lane];
+    for (int w = 0; w < KS; ++w) {
+      const float wgt = s_ref[w * (QB * 32) + q];
+      const SG_LDS float* src = (const SG_LDS float*)(lds + w * kWaveBytes + q * (D * 4) + (m ^ (q & 31)) * (kPer * 4));
+#pragma unroll
+      for (int x = 0; x < kPer; ++x) o[x] = fmaf(wgt, src[x], o[x]);
     }
-    const float inv = 1.0f / lt;
-    float4* dst = (float4*)(out + ((int64_t)head * tv.N + n) * D);
-#pragma unroll
-    for (int c = 0; c < D / 4; ++c) {
-      float r4[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        float acc = 0.f;
-#pragma unroll
-        for (int w = 0; w < kSplit; ++w) acc += wgt[w] * sO[(w * D + 4 * c + e) * kQ + lane];
-        r4[e] = acc * inv;
-      }
-      dst[c] = make_float4(r4[0], r4[1], r4[2], r4[3]);
-    }
+    float* dst = out + (size_t)(q0 + q) * D + m * kPer;
+    if constexpr (kPer == 4) *(float4*)dst = make_float4(o[0], o[1], o[2], o[3]);
+    else *(float2*)dst = make_float2(o[0], o[1]);
   }
 }
 
@@ -163,20 +299,14 @@ __global__ __launch_bounds__(kQ * kSplit) void attention_f32_kernel(const TileVi
 int launch_attention_f32(const TileView& tv, int heads, int head_dim, float scale, const AttnBatch& b, hipStream_t s) {
   if (head_dim != 64 && head_dim != 128) return SG_ERR_UNSUPPORTED;
   if (b.n_tiles <= 0) return SG_OK;
-  // K and V chunks of the 4 wavefronts (2 * 4 * 32 * D floats); the merge reuses them for the partial
-  // outputs (4 * D * 64 floats, the same amount) and needs 2 * 4 * 64 floats more for the (m, l) pairs
-  const size_t lds = ((size_t)2 * kSplit * kKC * head_dim + 2 * kSplit * kQ) * sizeof(float);
-  static_assert(2 * kKC == kQ, "the merge buffer is sized by the chunk buffers");
+  const View16 vw = make_view16(tv);
+  const int mode = tv.wrapped ? kWrappedRows : ((tv.W == tv.tw && tv.H == tv.th) ? kLinearRows : kCursor);
   constexpr int kMaxDevices = 64;
-  static std::atomic<bool> attr_set[kMaxDevices][2];   // zero-initialised; set twice by racing threads is harmless
-  int dev = 0;
+  static std::atomic<bool> attr_set[kMaxDevices][9];   // zero-initialised; set twice by racing threads is harmless
+  int dev = 0, n_cu = 0;
   SG_HIP_TRY(hipGetDevice(&dev));
-  const int slot = head_dim == 64 ? 0 : 1;
-  const void* kern = head_dim == 64 ? (const void*)attention_f32_kernel<64> : (const void*)attention_f32_kernel<128>;
-  if (dev < 0 || dev >= kMaxDevices || !attr_set[dev][slot].load(std::memory_order_acquire)) {
-    SG_HIP_TRY(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    if (dev >= 0 && dev < kMaxDevices) attr_set[dev][slot].store(true, std::memory_order_release);
-  }
+  SG_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
+  if (n_cu < 1) n_cu = 1;
   for (int t0 = 0; t0 < b.n_tiles; t0 += kAttnTilesPerLaunch) {
     const int n = (b.n_tiles - t0 < kAttnTilesPerLaunch) ? b.n_tiles - t0 : kAttnTilesPerLaunch;
     AttnTable tab;
@@ -190,10 +320,32 @@ int launch_attention_f32(const TileView& tv, int heads, int head_dim, float scal
       tab.x0[i] = (in && b.x0) ? b.x0[t0 + i] : 0;
       tab.refresh[i] = nullptr;   // the cache refresh is not carried by this kernel
     }
-    const dim3 grid((tv.N + kQ - 1) / kQ, heads, n);
     const uint8_t* flags = b.run_flags ? b.run_flags + t0 : nullptr;
-    if (head_dim == 64) attention_f32_kernel<64><<<grid, kQ * kSplit, lds, s>>>(tv, scale, tab, flags);
-    else attention_f32_kernel<128><<<grid, kQ * kSplit, lds, s>>>(tv, scale, tab, flags);
+    // One workgroup runs per compute unit at a time.  64 queries per workgroup (head_dim 64: the registers hold them) read
+    // K and V half as often as 32 but make half as many workgroups: taken where their rounds over the device are not longer.
+    const int64_t wg1 = (int64_t)n * heads * ((tv.N + 31) / 32), wg2 = (int64_t)n * heads * ((tv.N + 63) / 64);
+    const bool wide = head_dim == 64 && 2 * ((wg2 + n_cu - 1) / n_cu) <= (wg1 + n_cu - 1) / n_cu;
+    const int64_t total = wide ? wg2 : wg1;
+    if (total > (1ll << 31) - 2 * kXcd) return SG_ERR_UNSUPPORTED;
+    const dim3 grid((unsigned)(((total + kXcd - 1) / kXcd) * kXcd));
+    const int n_qblocks = (tv.N + (wide ? 63 : 31)) / (wide ? 64 : 32);
+    auto launch = [&](auto kern, int lds, int slot) -> int {
+      if (dev < 0 || dev >= kMaxDevices || !attr_set[dev][slot].load(std::memory_order_acquire)) {
+        SG_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+        if (dev >= 0 && dev < kMaxDevices) attr_set[dev][slot].store(true, std::memory_order_release);
+      }
+      kern<<<grid, kThreads, lds, s>>>(vw, scale, heads, n_qblocks, n, tab, flags);
+      return SG_OK;
+    };
+    int st;
+#define SG_F32_MODES(D, QB, SLOT)                                                            \
+  (mode == kLinearRows    ? launch(attention_f32_kernel<D, QB, kLinearRows>, kLds<QB>, SLOT)      \
+   : mode == kWrappedRows ? launch(attention_f32_kernel<D, QB, kWrappedRows>, kLds<QB>, SLOT + 1) \
+                          : launch(attention_f32_kernel<D, QB, kCursor>, kLds<QB>, SLOT + 2))
+    if (head_dim == 128) st = SG_F32_MODES(128, 1, 0);
+    else st = wide ? SG_F32_MODES(64, 2, 3) : SG_F32_MODES(64, 1, 6);
+#undef SG_F32_MODES
+    if (st != SG_OK) return st;
     SG_HIP_TRY(hipGetLastError());
   }
   return SG_OK;

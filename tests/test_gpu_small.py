@@ -49,6 +49,29 @@ def test_attention_f32_key_split(th, tw):
     assert_close(to_f64(gpu_tile_attention(g, q, k, v, 0, 0)), oracle_tile_attention_full(g, q, k, v, 0, 0), "f32")
 
 
+@pytest.mark.parametrize("d,heads,th,tw", [(64, 9, 25, 40), (64, 9, 23, 43), (128, 3, 16, 17), (128, 1, 5, 51), (128, 1, 8, 32)])
+@pytest.mark.parametrize("view", [False, True], ids=["packed", "wrapped"])
+def test_attention_f32_growing_scores(d, heads, th, tw, view):
+    """Scores that grow along the key axis, so that the softmax reference has to move past its slack in every share of the
+    keys; 9 heads of about 1,000 tokens take 64 queries per workgroup (head_dim 64), the others 32; 255, 256, 272, 989 and
+    1,000 tokens end in partial and whole 32-key blocks.  The logits reach 12: their rounding, a few times 12 * 2^-24,
+    is the relative error of the probabilities (the bound below leaves a factor of three)."""
+    g = _geom("f32g", 1, 2 * th, 2 * tw, th, tw, th, tw, heads, d, "f32", 900 + th) if view else _geom(
+        "f32g", 1, th, tw, th, tw, th, tw, heads, d, "f32", 900 + th)
+    shift = (th // 2, tw // 3) if view else (0, 0)
+    tr, tc = (1, 1) if view else (0, 0)
+    q, k, v = canvas_qkv(g)
+    u = torch.nn.functional.normalize(randn_tensor((d,), "f32", 5).cuda(), dim=0)
+    rise = torch.linspace(0.0, 1.0, g.H * g.W, device="cuda").reshape(1, 1, g.H, g.W, 1)
+    q = 0.3 * q + 8.0 * u
+    k = 0.3 * k + (12.0 * math.sqrt(d) / 8.0) * rise * u
+    out = torch.empty(g.tile_shape, dtype=torch.float32, device="cuda")
+    sg.sg_tile_attention(sg.make_problem(g, shift=shift), q, k, v, tr, tc, out)
+    win = [oracle.slice_tile_shifted(to_f64(t), g, tr, tc, *shift).reshape(heads, -1, d) for t in (q, k, v)]
+    ref = np.stack([oracle.attention(win[0][a], win[1][a], win[2][a], g.scale) for a in range(heads)]).reshape(g.tile_shape)
+    assert errors(to_f64(out), ref)[1] <= 1e-5
+
+
 BF16_CASES = [
     # name, T, H, W, th, tw, sh, sw, heads: packed tiles (linear addressing) and canvas views
     ("packed_n576", 3, 12, 16, 12, 16, 12, 16, 2),      # 576 = 2*256 + 64, 9 full key blocks

@@ -105,12 +105,12 @@ int sg_workspace_bytes(int32_t n_tiles, size_t* out_bytes);
  *   out_tile  device, packed tile [heads][T][tile_h][tile_w][head_dim], 16-byte aligned
  * A packed tile is attended by describing it as a canvas that is one tile (H = tile_h,
  * W = tile_w, 1 x 1 tiles).  Under a shifted partition (shift_h or shift_w non-zero) the tile's
- * window is read at its shifted position, wrapping around the canvas edges where it crosses them
- * (a window that wraps is read row by row and runs somewhat slower than one that does not; gathering
- * it with sg_tile_slice and attending the packed copy is the faster route for large tiles).
+ * window is read at its shifted position, wrapping around the canvas edges where it crosses them, at
+ * the rate of one that does not; a packed copy (sg_tile_slice) is attended 3 % faster.
  * Q is multiplied by scale * log2(e) and rounded to bf16 once more before the products of a bf16
  * problem (the score then leaves the matrix cores as the exponent): one extra bf16 rounding of the
- * scores' left factor on top of "multiply in bf16, accumulate in fp32".
+ * scores' left factor on top of "multiply in bf16, accumulate in fp32".  Tiles of head_dim 64 that are read
+ * in place from a larger canvas are scaled in fp32 behind the product instead.
  */
 int sg_tile_attention(const sg_problem* p, const void* q, const void* k, const void* v,
                       int32_t tile_row, int32_t tile_col, void* out_tile, void* stream);
@@ -246,8 +246,7 @@ typedef struct sg_step_io {
  * One stage-2 step over all tiles (Algorithm 1 loop body; Section 5.1: Tile Dispatcher ->
  * Threshold Comparator -> recompute or reuse -> Tile Fuser).
  *   canvas mode: cache_out[i] = attention(tile i of q, k, v) for every tile; grid_out = Fuse.  All
- *     tiles are read in place and attended by one launch (two under a shifted partition: the windows
- *     that wrap around a canvas edge and those that do not).  If `workspace` (256-byte aligned) holds
+ *     tiles are read in place and attended by one launch.  If `workspace` (256-byte aligned) holds
  *     G >= 1 packed tile inputs (each 3 * heads * T * tile_h * tile_w * head_dim elements, rounded up
  *     to 256 bytes), the tiles are instead gathered into it G at a time (sg_tile_slice) and every group
  *     is attended in packed form by one launch; with room for all tiles this is the fastest form.

@@ -74,15 +74,18 @@ struct Softmax {
 
 // Scores of keys at or beyond n_keys become -inf.  Branch- and compare-free (sign mask + bit select), so the
 // 16 NB decisions do not each occupy a pair of scalar registers.
+// Register (kb, r) holds row R = 8 (r >> 2) + 4 half + (r & 3) of its block: key 32 kb + R of the stage (head_dim 128), or key
+// 2 (32 (kb >> 1) + R) + (kb & 1) (head_dim 64, two keys per slot).
 template <int NB>
 __device__ __forceinline__ void mask_tail(f32x16 (&t)[kMaxSB], const int key0, const int n_keys) {
   const int half = (threadIdx.x & 63) >> 5;
-  const int limit = n_keys - key0 - 4 * half;   // register (kb, r) holds key offset 32 kb + 8 (r >> 2) + (r & 3)
+  const int limit = n_keys - key0 - (NB == 2 ? 4 : 8) * half;
 #pragma unroll
   for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int c = 32 * kb + 8 * (r >> 2) + (r & 3);
+      const int row = 8 * (r >> 2) + (r & 3);
+      const int c = (NB == 2) ? 32 * kb + row : 2 * (32 * (kb >> 1) + row) + (kb & 1);
       const uint32_t beyond = (uint32_t)((limit - 1 - c) >> 31);   // all ones if c >= limit
       t[kb][r] = __uint_as_float((__float_as_uint(t[kb][r]) & ~beyond) | (0xff800000u & beyond));
     }
@@ -130,9 +133,12 @@ __device__ __forceinline__ float block_max(const f32x16 (&t)[kMaxSB]) {
   const auto sw = __builtin_amdgcn_permlane32_swap(mu, mu, false, false);
   return fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
 }
+__device__ __forceinline__ f32x16 zero16() {
+  return f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+}
 constexpr float kOverflowGuard = 65536.0f;   // a stage's exponentials may grow to 2^16 before the reference moves
 
-enum { kPerLane = 0, kLinear = 1, kScalarWalk = 2, kWrapped = 3 };   // how the loader walks the tile (see the DMA loader)
+enum { kLinear = 0, kWindow = 1 };   // packed tile, or window of a canvas (see the DMA loader)
 
 template <int D, int MODE>
 __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 vw, const float c_log2, const int heads,
@@ -140,13 +146,15 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
                                                                   const uint8_t* __restrict__ run_flags, const int first_copy_block,
                                                                   const int64_t copy_vecs, uint8_t* __restrict__ has_cache) {
   static_assert(D == 128 || D == 64, "head_dim 64 or 128");
-  static_assert(D == 128 || MODE == kLinear, "head_dim 64 streams packed tiles only");
   // LDS rows ("slots") are always 256 bytes.  With head_dim 128 a slot is one key and a stage 64 keys; with
-  // head_dim 64 a stage is 128 keys and slot 32 g + r holds key 64 g + r in its first half and key
-  // 64 g + 32 + r in its second, so the fragment reads and the MFMA count per stage are the same and only
-  // the pairing of fragments with accumulators differs (see qk and pv).
+  // head_dim 64 a stage is 128 keys and slot s holds the keys 2 s and 2 s + 1, neighbours in a tile row, so the
+  // transfers, the fragment reads and the MFMA count per stage are the same and only the pairing of
+  // fragments with accumulators differs (see qk and pv).
   constexpr int kSB = (D == 128) ? 2 : 4;   // 32-key score blocks per stage
   constexpr int kKeys = 32 * kSB;           // keys per stage
+  // Windows of head_dim 64 keep Q as stored and multiply the scores by log2(e) * scale in fp32 (one more vector instruction
+  // per score, and no rounding of the scaled Q); the other forms scale Q first.
+  constexpr bool kLate = (D == 64 && MODE == kWindow);
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
   SG_LDS uint8_t* const lds = (SG_LDS uint8_t*)smem;
   const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
@@ -188,16 +196,15 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
   }
   const int nth = logical / per_tile, in_tile = logical - nth * per_tile;
   const int tile = __builtin_amdgcn_readfirstlane(attn_nth_tile(active, nth));
-  const int head = in_tile / n_qblocks, qblk = in_tile - head * n_qblocks;
+  const int head = __builtin_amdgcn_readfirstlane(in_tile / n_qblocks), qblk = in_tile - head * n_qblocks;   // uniform, and kept scalar
   const u32x4* const qg = (const u32x4*)tab.q[tile];
   const u32x4* const kg = (const u32x4*)tab.k[tile];
   const u32x4* const vg = (const u32x4*)tab.v[tile];
   uint16_t* const out = (uint16_t*)tab.out[tile];
-  const int wy0 = (MODE == kWrapped) ? tab.y0[tile] : 0, wx0 = (MODE == kWrapped) ? tab.x0[tile] : 0;
-  // offset of tile token n from the tile's pointers, in 16-byte units
+  const int wy0 = (MODE == kWindow) ? tab.y0[tile] : 0, wx0 = (MODE == kWindow) ? tab.x0[tile] : 0;
+  // offset of tile token n from the head's first element, in 16-byte units
   auto token_off16 = [&](int n) SG_INLINE -> uint32_t {
-    if (MODE == kWrapped) return wrap_offset16(vw, wrap_cursor_at(vw, n), wy0, wx0);
-    return cursor_at(vw, n).off16;
+    return (MODE == kLinear) ? (uint32_t)n * vw.st16 : window_token(vw, n, wy0, wx0).off16;
   };
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -218,6 +225,7 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
 #pragma unroll
     for (int kk = 0; kk < D / 16; ++kk) {
       const u32x4 raw = src[2 * kk + half];
+      if (kLate) { qf[kk] = __builtin_bit_cast(bf16x8, raw); continue; }
       u32x4 scaled;   // q * log2(e) * scale, rounded to bf16 once
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -242,166 +250,131 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
   for (int db = 0; db < 4; ++db)
     vaddr[db] = lds0 + kVRegion + vt_row * kRowBytes + (((4 * db + (vt_dbyte >> 4)) ^ ((vt_row & 3) << 2)) << 4) + (vt_dbyte & 15);
 
-  // ---- DMA loader: wavefront w moves rows 8w..8w+7 of every stage, 4 rows (1 KiB) per instruction; lane l
-  // fills chunk slot (l & 15) of row 8w + 4u + (l >> 4) and therefore fetches the chunk that belongs there.
+  // ---- DMA loader: wavefront w moves slots 8w..8w+7 of every stage, 4 slots (1 KiB) per instruction; lane l
+  // fills chunk (l & 15) of slot 8w + 4u + (l >> 4) and therefore fetches the chunk that belongs there.
   //
-  // kScalarWalk / kLinear: the 8 rows of a wavefront are always consecutive tokens of one tile row (tile
-  // width a multiple of 8, or a packed tile whose rows are adjacent anyway).  The address then splits into
-  // a wave-uniform 64-bit pointer that walks the tile (scalar registers, scalar ALU) and a per-lane byte
-  // offset that never changes, so the steady loop spends no vector instructions on addressing.
-  // kPerLane: every lane walks its own row with a cursor and 32-bit offsets from the head's base.
-  // kWrapped: the same for the wrapped window of a shifted partition; the offset is formed from the token's
-  // coordinates each time, since a tile row may cross the canvas edge.
-  constexpr bool kLaneWalk = (MODE == kPerLane || MODE == kWrapped);
-  const int ld_sub = lane >> 4, ld_slot = lane & 15;
-  uint32_t kchunk[2], vchunk[2];
-#pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    const int row = 8 * wave + 4 * u + ld_sub;
-    kchunk[u] = ld_slot ^ (row & 15);
-    vchunk[u] = ld_slot ^ ((row & 3) << 2);
-  }
-  const uint32_t last16 = token_off16(N - 1);   // the last valid row: stands in for rows >= N
-  const uint32_t dma_dst = lds0 + wave * (8 * kRowBytes);
-  // scalar walk: pointers to row 8w of the stage to issue (K and V), its tile row / column, lane offsets
-  const char* kcur = (const char*)kh;
-  const char* vcur = (const char*)vh;
-  int32_t row_i = 0, col_j = 0;
+  // A wavefront's slots are a run of kTok consecutive tokens.  Where they lie side by side in memory - always in a packed
+  // tile - the address is a wave-uniform 64-bit pointer plus a per-lane byte offset that never changes, and the transfer
+  // spends no vector instructions on addressing.  In a window a run is broken where a tile row ends and where the row crosses
+  // the canvas edge, at most once each if the tile is at least kTok wide; such a run adds the two jumps to the lanes behind them.
+  // Where the runs start and break is worked out for 64 stages at a time, one lane per stage, and read back lane by lane: on
+  // the scalar unit the same arithmetic costs 2 % of the loop before the transfers of a stage and 5 % between its MFMAs.
+  // Measured on 3 x 3 tiles of 11,520 tokens, 40 heads x 128: 18.46 ms a step, 18.50 under a shift that makes windows wrap,
+  // 17.87 packed (19.1 shifted when every lane formed its token's offset from wrapped coordinates each stage); on 2 x 2 shifted
+  // tiles of 17,550 tokens, 48 heads x 64: 16.4 ms (21.8 with register-staged loads).
+  constexpr int kTok = kKeys / kWaves;   // tokens per wavefront and stage: 8 (head_dim 64: 16)
+  auto slot_token = [&](int l, int u, bool is_v, uint32_t& chunk) SG_INLINE -> int {   // what lane l moves: token of the run, chunk of it
+    const int slot_w = 4 * u + (l >> 4), row = 8 * wave + slot_w;
+    const int c = (l & 15) ^ (is_v ? (row & 3) << 2 : row & 15);
+    chunk = (uint32_t)(D == 128 ? c : c & 7);
+    return D == 128 ? slot_w : 2 * slot_w + (c >> 3);
+  };
   uint32_t klane[2], vlane[2];
-  // per-lane walk
-  RowCursor cur[2];
-  WrapCursor wcur[2];
-  uint32_t koff[2], voff[2];              // byte offsets from kh / vh of the next stage to issue
-  // head_dim 64: key (within a stage) whose chunk this lane moves, for K and for V
-  int ktok[2], vtok[2];
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
-    const int slot_u = 8 * wave + 4 * u + ld_sub;
-    ktok[u] = 64 * (slot_u >> 5) + 32 * (int)(kchunk[u] >> 3) + (slot_u & 31);
-    vtok[u] = 64 * (slot_u >> 5) + 32 * (int)(vchunk[u] >> 3) + (slot_u & 31);
+    uint32_t kc, vc;
+    const int kt = slot_token(lane, u, false, kc), vt = slot_token(lane, u, true, vc);
+    klane[u] = ((uint32_t)kt * vw.st16 + kc) << 4;
+    vlane[u] = ((uint32_t)vt * vw.st16 + vc) << 4;
   }
-  if (!kLaneWalk) {
-    const int n0 = (D == 128) ? 8 * wave : 0;
-    const RowCursor c = cursor_at(vw, n0 < N ? n0 : 0);
-    row_i = __builtin_amdgcn_readfirstlane(c.i);
-    col_j = __builtin_amdgcn_readfirstlane(c.j);
-    const uint64_t first = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)c.off16) << 4;
-    kcur += first;
-    vcur += first;
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      if (D == 128) {
-        klane[u] = ((uint32_t)(4 * u + ld_sub) * vw.st16 + kchunk[u]) << 4;
-        vlane[u] = ((uint32_t)(4 * u + ld_sub) * vw.st16 + vchunk[u]) << 4;
-      } else {   // offsets from the stage's first key; the pointers below start at key 0, not at the wavefront's rows
-        klane[u] = ((uint32_t)ktok[u] * vw.st16 + (kchunk[u] & 7)) << 4;
-        vlane[u] = ((uint32_t)vtok[u] * vw.st16 + (vchunk[u] & 7)) << 4;
-      }
-    }
-  } else {
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int row = 8 * wave + 4 * u + ld_sub;
-      uint32_t off16;
-      if (MODE == kWrapped) {
-        wcur[u] = wrap_cursor_at(vw, row < N ? row : N - 1);
-        off16 = wrap_offset16(vw, wcur[u], wy0, wx0);
-      } else {
-        cur[u] = cursor_at(vw, row < N ? row : N - 1);
-        off16 = cur[u].off16;
-      }
-      koff[u] = (off16 + kchunk[u]) << 4;
-      voff[u] = (off16 + vchunk[u]) << 4;
-    }
-  }
-  // per-lane walk: row u of this lane moves one stage on (only while the new row exists)
-  auto lane_advance = [&](int u, int n) SG_INLINE {
-    uint32_t off16;
-    if (MODE == kWrapped) {
-      if (n + kKeys < N) wrap_cursor_advance(vw, wcur[u], kKeys);
-      off16 = wrap_offset16(vw, wcur[u], wy0, wx0);
-    } else {
-      if (n + kKeys < N) cursor_advance(vw, cur[u], kKeys);
-      off16 = cur[u].off16;
-    }
-    koff[u] = (off16 + kchunk[u]) << 4;
-    voff[u] = (off16 + vchunk[u]) << 4;
+  const uint32_t dma_dst = lds0 + wave * (8 * kRowBytes);
+  uint32_t plan_first = 0, plan_jump = 0, plan_info = 0;   // lane l: this wavefront's run of stage 64 m + l
+  const int edge0 = (wx0 + vw.tw > vw.W) ? vw.W - wx0 : 0x3fffffff;   // tokens of a tile row before the canvas edge (none crossed: many)
+  auto plan64 = [&](int blk) SG_INLINE {
+    const int n0 = ((blk & ~63) + lane) * kKeys + kTok * wave;
+    const int t = (int)divide((uint32_t)n0, vw.by_plane);
+    const int in_plane = n0 - t * (vw.th * vw.tw);
+    const int i = (int)divide((uint32_t)in_plane, vw.by_row), j = in_plane - i * vw.tw;
+    int y = wy0 + i, x = wx0 + j;
+    y -= (y >= vw.H) ? vw.H : 0;
+    x -= (x >= vw.W) ? vw.W : 0;
+    plan_first = (uint32_t)((t * vw.H + y) * vw.W + x) * vw.st16;
+    int row_end = vw.tw - j;     // tokens before the tile row ends
+    int edge = edge0 - j;        // tokens before the canvas edge is crossed; at or below 0: this row has crossed already
+    const bool here = edge > 0 && edge < row_end;   // crossed in this row, else in the next
+    const bool frame_end = i + 1 == vw.th;
+    int y1 = frame_end ? wy0 : y + 1;
+    y1 -= (y1 >= vw.H) ? vw.H : 0;
+    const uint32_t next16 = (uint32_t)(((frame_end ? t + 1 : t) * vw.H + y1) * vw.W + wx0) * vw.st16;
+    plan_jump = next16 - (plan_first + (uint32_t)row_end * vw.st16) + (here ? (uint32_t)vw.W * vw.st16 : 0u);   // offset's jump at the row's end
+    if (!here) edge = row_end + edge0;
+    row_end = row_end < kTok ? row_end : kTok;   // breaks behind the run: no lane reaches them
+    edge = edge < kTok ? edge : kTok;
+    const bool whole = (vw.reach & kReachLane) && row_end == kTok && edge == kTok;
+    plan_info = whole ? 0u : (uint32_t)row_end | (uint32_t)edge << 8;
   };
+  uint32_t run_info = 0, run_first16 = 0;   // of the stage that the next steady iteration issues; info 0: side by side
+  auto fetch_plan = [&](int blk) SG_INLINE {
+    run_info = __builtin_amdgcn_readlane(plan_info, blk & 63);
+    run_first16 = __builtin_amdgcn_readlane(plan_first, blk & 63);
+  };
+  auto look_up = [&](int blk, uint32_t dst) SG_INLINE {   // every lane looks its token up; tokens >= N: the last one (masked later)
+    int l = lane;
+    asm volatile("" : "+v"(l));   // worked out here, not kept in registers over the loop
+    const u32x4* kb = kh;
+    const u32x4* vb = vh;
+    asm volatile("" : "+s"(kb), "+s"(vb));
+    const int n0 = blk * kKeys + kTok * wave;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      uint32_t kc, vc;
+      const int nk = n0 + slot_token(l, u, false, kc), nv = n0 + slot_token(l, u, true, vc);
+      const uint32_t ko = token_off16(nk < N ? nk : N - 1);
+      const uint32_t vo = (D == 128) ? ko : token_off16(nv < N ? nv : N - 1);
+      dma16_addr(kb + ((uint64_t)ko + kc), dst + u * (4 * kRowBytes));
+      dma16_addr(vb + ((uint64_t)vo + vc), dst + kVRegion + u * (4 * kRowBytes));
+    }
+  };
+  auto move_run = [&](const char* kp, const char* vp, uint32_t dst) SG_INLINE {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      dma16(kp, klane[u], dst + u * (4 * kRowBytes));
+      dma16(vp, vlane[u], dst + kVRegion + u * (4 * kRowBytes));
+    }
+  };
+  // packed tiles: pointers to the run of the stage to issue
   const uint64_t stage_bytes = (uint64_t)(kKeys * 16) * vw.st16;
-  const uint64_t row_skip_bytes = (uint64_t)vw.row_skip16 << 4, frame_skip_bytes = (uint64_t)vw.frame_skip16 << 4;
-  auto scalar_advance = [&]() SG_INLINE {   // the wavefront's rows move one stage on
-    uint64_t delta = stage_bytes;
-    if (MODE == kScalarWalk) {
-      col_j += kKeys;
-      if (vw.tw >= kKeys) {         // at most one tile-row wrap: branch-free
-        const bool wrap = col_j >= vw.tw;
-        col_j -= wrap ? vw.tw : 0;
-        row_i += wrap ? 1 : 0;
-        const bool fwrap = row_i == vw.th;
-        row_i = fwrap ? 0 : row_i;
-        delta += (wrap ? row_skip_bytes : 0) + (fwrap ? frame_skip_bytes : 0);
-      } else {
-        while (col_j >= vw.tw) {
-          col_j -= vw.tw;
-          delta += row_skip_bytes;
-          if (++row_i == vw.th) { row_i = 0; delta += frame_skip_bytes; }
-        }
-      }
-    }
-    kcur += delta;
-    vcur += delta;
-  };
-  // issue stage `blk` (all of its rows below N) into ring slot `st`; advance to the next stage
+  const char* kcur = (const char*)kh + (uint64_t)(kTok * wave * 16) * vw.st16;
+  const char* vcur = (const char*)vh + (uint64_t)(kTok * wave * 16) * vw.st16;
+  // issue stage `blk`, whose keys are all below N, into ring slot `st` = blk % 4
   auto issue_full = [&](int blk, int st) SG_INLINE {
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      if (!kLaneWalk) {
-        dma16(kcur, klane[u], dma_dst + st * kTileBytes + u * (4 * kRowBytes));
-        dma16(vcur, vlane[u], dma_dst + kVRegion + st * kTileBytes + u * (4 * kRowBytes));
-      } else {
-        dma16(kh, koff[u], dma_dst + st * kTileBytes + u * (4 * kRowBytes));
-        dma16(vh, voff[u], dma_dst + kVRegion + st * kTileBytes + u * (4 * kRowBytes));
-        lane_advance(u, blk * kKeys + 8 * wave + 4 * u + ld_sub);
-      }
+    const uint32_t dst = dma_dst + st * kTileBytes;
+    if (MODE == kLinear) {
+      move_run(kcur, vcur, dst);
+      kcur += stage_bytes;
+      vcur += stage_bytes;
+      return;
     }
-    if (!kLaneWalk) scalar_advance();
+    if (run_info == 0) {
+      const uint64_t first = (uint64_t)run_first16 << 4;
+      move_run((const char*)kh + first, (const char*)vh + first, dst);
+    } else if ((vw.reach & kReachHead) && vw.tw >= kTok) {
+      // token x of the run lies behind a break at token b exactly if its lane offset is at or beyond b tokens
+      const uint32_t first = run_first16 << 4, token = vw.st16 << 4;
+      const uint32_t end_at = (run_info & 255u) * token, edge_at = (run_info >> 8) * token;
+      const uint32_t end_by = __builtin_amdgcn_readlane(plan_jump, blk & 63) << 4, edge_by = 0u - (uint32_t)vw.W * token;
+      auto behind = [&](uint32_t off) SG_INLINE -> uint32_t { return (off >= end_at ? end_by : 0u) + (off >= edge_at ? edge_by : 0u); };
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const uint32_t kj = behind(klane[u]), vj = (D == 128) ? kj : behind(vlane[u]);
+        dma16(kh, klane[u] + kj + first, dst + u * (4 * kRowBytes));
+        dma16(vh, vlane[u] + vj + first, dst + kVRegion + u * (4 * kRowBytes));
+      }
+    } else {   // tiles narrower than a run, heads of 4 GiB and more
+      look_up(blk, dst);
+    }
+    if (st == kStages - 1 && (blk & 63) == 63) plan64(blk + 1);
+    fetch_plan(blk + 1);
   };
-  // same for a stage that may hold rows >= N: those lanes fetch the last valid row (masked later)
+  // the same for a stage that may hold keys >= N
   auto issue_any = [&](int blk, int st) SG_INLINE {
-    const int n0 = blk * kKeys + ((D == 128) ? 8 * wave : 0);   // wave-uniform
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int n = n0 + 4 * u + ld_sub;
-      if (D == 64) {               // the stage's first key is valid; keys >= N take the last row, at or after it
-        const uint32_t back = (uint32_t)(((const char*)kh + ((uint64_t)last16 << 4)) - kcur);
-        const uint32_t ko = (n0 + ktok[u] < N) ? klane[u] : back + ((kchunk[u] & 7) << 4);
-        const uint32_t vo = (n0 + vtok[u] < N) ? vlane[u] : back + ((vchunk[u] & 7) << 4);
-        dma16(kcur, ko, dma_dst + st * kTileBytes + u * (4 * kRowBytes));
-        dma16(vcur, vo, dma_dst + kVRegion + st * kTileBytes + u * (4 * kRowBytes));
-      } else if (!kLaneWalk) {
-        if (n0 + 7 < N) {          // all 8 rows valid
-          dma16(kcur, klane[u], dma_dst + st * kTileBytes + u * (4 * kRowBytes));
-          dma16(vcur, vlane[u], dma_dst + kVRegion + st * kTileBytes + u * (4 * kRowBytes));
-        } else if (n0 < N) {       // partly valid: rows >= N take the last row, which lies at or after row n0
-          const uint32_t back = (uint32_t)(((const char*)kh + ((uint64_t)last16 << 4)) - kcur);
-          const uint32_t ko = (n < N) ? klane[u] : back + (kchunk[u] << 4);
-          const uint32_t vo = (n < N) ? vlane[u] : back + (vchunk[u] << 4);
-          dma16(kcur, ko, dma_dst + st * kTileBytes + u * (4 * kRowBytes));
-          dma16(vcur, vo, dma_dst + kVRegion + st * kTileBytes + u * (4 * kRowBytes));
-        } else {                   // no valid row: every lane takes the last row
-          const uint64_t lastb = (uint64_t)last16 << 4;
-          dma16((const char*)kh + lastb, kchunk[u] << 4, dma_dst + st * kTileBytes + u * (4 * kRowBytes));
-          dma16((const char*)vh + lastb, vchunk[u] << 4, dma_dst + kVRegion + st * kTileBytes + u * (4 * kRowBytes));
-        }
-      } else {
-        const uint32_t ko = (n < N) ? koff[u] : ((last16 + kchunk[u]) << 4);
-        const uint32_t vo = (n < N) ? voff[u] : ((last16 + vchunk[u]) << 4);
-        dma16(kh, ko, dma_dst + st * kTileBytes + u * (4 * kRowBytes));
-        dma16(vh, vo, dma_dst + kVRegion + st * kTileBytes + u * (4 * kRowBytes));
-        lane_advance(u, n);
-      }
+    const uint32_t dst = dma_dst + st * kTileBytes;
+    if (MODE == kLinear && blk * kKeys + kTok * (wave + 1) <= N) move_run(kcur, vcur, dst);
+    else look_up(blk, dst);
+    if (MODE == kLinear) {
+      kcur += stage_bytes;
+      vcur += stage_bytes;
     }
-    if (!kLaneWalk && n0 + kKeys < N) scalar_advance();
   };
 
   f32x16 oacc[D / 32];
@@ -451,8 +424,8 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
       const int b1 = b0 + kSB / 2;
       const int qi = kk % kPerChain;
       if (qi == 0) {
-        s[b0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk][0], qf[qi], cinit, 0, 0, 0);
-        s[b1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk][1], qf[qi], cinit, 0, 0, 0);
+        s[b0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk][0], qf[qi], kLate ? zero16() : cinit, 0, 0, 0);
+        s[b1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk][1], qf[qi], kLate ? zero16() : cinit, 0, 0, 0);
       } else {
         s[b0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk][0], qf[qi], s[b0], 0, 0, 0);
         s[b1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk][1], qf[qi], s[b1], 0, 0, 0);
@@ -491,6 +464,13 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
   // reference moves by delta per query: scores, running sum and output accumulators are brought to the new
   // reference and the exponentials are retaken.  One copy of the code, looped at most twice.
   auto softmax_phase = [&](int key0, bool masked, bool first, bf16x8 (&p)[2 * kMaxSB]) SG_INLINE {
+    if (kLate) {
+#pragma unroll
+      for (int kb = 0; kb < kSB; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[kb][r] = __builtin_fmaf(s[kb][r], c_log2, -sm.M);
+      __builtin_amdgcn_sched_barrier(0);
+    }
     if (masked) mask_tail<kSB>(s, key0, N);
     bool move = first;
     float sum;
@@ -566,7 +546,8 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
   };
   auto softmax_pinned = [&](int j, bool masked, bool first) SG_INLINE {
     softmax_phase(j * kKeys, masked, first, p);
-    asm volatile("" : : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "v"(sm.l), "v"(cinit));
+    asm volatile("" : : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "v"(sm.l));
+    if constexpr (!kLate) asm volatile("" : : "v"(cinit));
     if constexpr (kSB == 4) asm volatile("" : : "v"(p[kSB]), "v"(p[kSB + 1]), "v"(p[kSB + 2]), "v"(p[kSB + 3]));
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -600,6 +581,10 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
     };
     int k = 0;
     for (; k < kStages && k < n_blocks; ++k) general(k);
+    if (MODE == kWindow && k < n_steady) {
+      plan64(k + 3);
+      fetch_plan(k + 3);
+    }
     for (; k < n_steady; k += kStages) {
       steady(k, std::integral_constant<int, 0>{});
       steady(k + 1, std::integral_constant<int, 1>{});
@@ -627,6 +612,10 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
     };
     int k = 0;
     for (; k < kStages && k < n_blocks; ++k) general(k);
+    if (MODE == kWindow && k < n_steady) {
+      plan64(k + 3);
+      fetch_plan(k + 3);
+    }
     for (; k < n_steady; k += kStages) {
       steady(k, std::integral_constant<int, 0>{});
       steady(k + 1, std::integral_constant<int, 1>{});
@@ -663,30 +652,20 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
 int launch_attention_bf16(const TileView& tv, int heads, int head_dim, float scale, const AttnBatch& b, hipStream_t s) {
   if (head_dim != 128 && head_dim != 64) return SG_ERR_UNSUPPORTED;
   if (b.n_tiles <= 0) return SG_OK;
-  const bool linear = (tv.W == tv.tw && tv.H == tv.th) && !tv.wrapped;
-  // head_dim 64 streams packed tiles only (two keys share an LDS slot, 32 keys apart: not one tile row);
-  // tiles read in place from a canvas take the register-staged kernel
-  if (head_dim == 64 && !linear) return launch_attention_bf16_generic(tv, heads, head_dim, scale, b, s);
   const View16 vw = make_view16(tv);
-  // a wavefront moves 8 consecutive tile tokens per stage: contiguous in memory whenever they cannot
-  // straddle a tile row (tile width a multiple of 8) or the tile rows are themselves adjacent (packed tile)
-  const int mode = tv.wrapped ? kWrapped : (linear ? kLinear : (tv.tw % 8 == 0 ? kScalarWalk : kPerLane));
-  // The per-lane cursors address a head's K/V with 32-bit byte offsets from a wave-uniform base; canvases
-  // whose per-head extent does not fit take the kernel with 64-bit addressing.
-  const int64_t head_extent = ((int64_t)tv.T * tv.H * tv.W) * tv.stride_token;
-  if ((mode == kPerLane || mode == kWrapped) && head_extent * 2 >= (1ll << 32))
-    return launch_attention_bf16_generic(tv, heads, head_dim, scale, b, s);
+  // a packed tile whose tokens are so far apart that 16 of them span 4 GiB is read like a window (of itself)
+  const bool window = tv.window || !(vw.reach & kReachLane);
   const int n_qblocks = (tv.N + kBR - 1) / kBR;
   const float c_log2 = scale * 1.4426950408889634f;
   // the kernels need more dynamic LDS than the default limit; the attribute is set once per device and kernel
   constexpr int kMaxDevices = 64;
-  static std::atomic<bool> attr_set[kMaxDevices][5];   // zero-initialised; set twice by racing threads is harmless
+  static std::atomic<bool> attr_set[kMaxDevices][4];   // zero-initialised; set twice by racing threads is harmless
   int dev = 0, n_cu = 0;
   SG_HIP_TRY(hipGetDevice(&dev));
   SG_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
   if (n_cu < 4) n_cu = 4;
   // the cache refresh rides on this launch for packed tiles (their inputs are one contiguous run each)
-  const bool fuse_refresh = b.refresh_dst && b.has_cache && b.refresh_bytes > 0 && (b.refresh_bytes & 15) == 0 && linear;
+  const bool fuse_refresh = b.refresh_dst && b.has_cache && b.refresh_bytes > 0 && (b.refresh_bytes & 15) == 0 && !window;
   bool tab_refresh_ok = false;
   for (int t0 = 0; t0 < b.n_tiles; t0 += kAttnTilesPerLaunch) {
     const int n = (b.n_tiles - t0 < kAttnTilesPerLaunch) ? b.n_tiles - t0 : kAttnTilesPerLaunch;
@@ -725,11 +704,8 @@ int launch_attention_bf16(const TileView& tv, int heads, int head_dim, float sca
       return SG_OK;
     };
     int st = SG_OK;
-    if (head_dim == 64) st = launch(attention_bf16_kernel<64, kLinear>, 4);
-    else if (mode == kLinear) st = launch(attention_bf16_kernel<128, kLinear>, kLinear);
-    else if (mode == kScalarWalk) st = launch(attention_bf16_kernel<128, kScalarWalk>, kScalarWalk);
-    else if (mode == kWrapped) st = launch(attention_bf16_kernel<128, kWrapped>, kWrapped);
-    else st = launch(attention_bf16_kernel<128, kPerLane>, kPerLane);
+    if (head_dim == 64) st = window ? launch(attention_bf16_kernel<64, kWindow>, 0) : launch(attention_bf16_kernel<64, kLinear>, 1);
+    else st = window ? launch(attention_bf16_kernel<128, kWindow>, 2) : launch(attention_bf16_kernel<128, kLinear>, 3);
     if (st != SG_OK) return st;
     SG_HIP_TRY(hipGetLastError());
   }

@@ -34,15 +34,15 @@ __device__ __forceinline__ void dma16_addr(const void* addr, uint32_t lds_dst) {
 
 // ---------------------------------------------------------------------------------------------------
 // One launch attends up to kAttnTilesPerLaunch tiles of the same shape (Algorithm 1: for all tiles of the
-// partition).  Per tile the table holds the tensors its offsets are relative to, the packed output and,
-// for a shifted (wrapping) partition, the canvas position of its first token.
+// partition).  Per tile the table holds the tensors its offsets are relative to (packed tile or canvas), the packed
+// output and, for a window of a canvas, the canvas position of its first token.
 constexpr int kAttnTilesPerLaunch = 32;
 struct AttnTable {
   const void* q[kAttnTilesPerLaunch];
   const void* k[kAttnTilesPerLaunch];
   const void* v[kAttnTilesPerLaunch];
   void* out[kAttnTilesPerLaunch];
-  int32_t y0[kAttnTilesPerLaunch], x0[kAttnTilesPerLaunch];   // wrapped windows only
+  int32_t y0[kAttnTilesPerLaunch], x0[kAttnTilesPerLaunch];   // windows only
   void* refresh[kAttnTilesPerLaunch];   // cache refresh fused into the launch (packed tiles): copy of the tile's input, or unused
 };
 
@@ -62,81 +62,63 @@ __device__ __forceinline__ int attn_nth_tile(uint32_t mask, int a) {
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Tile addressing on the device in units of 16 bytes, so that offsets inside one head fit 32 bits.
-// Offsets are relative to the tile's table pointers: the host folds the tile origin of a fixed partition
-// into them; a wrapped window keeps the canvas pointers and carries its origin in the table.
+// Tile addressing on the device, in units of 8 elements (16 bytes of bf16, 32 of fp32), so that offsets inside one
+// head fit 32 bits.  A packed tile (a canvas that is one unshifted tile) is walked linearly; any other tile is a window of
+// a canvas tensor: token (t, i, j) sits at canvas row (y0 + i) mod H, column (x0 + j) mod W, where (y0, x0) is the
+// canvas position of its first token (Algorithm 1 "SliceTile"; "Shift" lets it wrap around the edges).
+// Divisions by the tile's width and plane are multiplications: n / d = ((n * mul) >> 32 >> shift) + (n & all) for 0 <= n < 2^31.
+struct Divisor {
+  uint32_t mul, shift, all;
+};
 struct View16 {
-  uint32_t st16;          // 16-byte units per canvas token
-  uint32_t row_skip16;    // (W - tw) * st16: jump at the end of a tile row
-  uint32_t frame_skip16;  // (H - th) * W * st16: jump at the end of a tile frame
+  uint32_t st16;     // units per canvas token
+  uint32_t head16;   // units per head
   int32_t th, tw, N;
-  uint32_t head16;        // 16-byte units per head
-  int32_t H, W;           // canvas size: used by wrapped windows only
+  int32_t H, W;      // canvas size
+  Divisor by_plane, by_row;   // th * tw, tw
+  uint32_t reach;    // kReach* bits
 };
+constexpr uint32_t kReachLane = 1;   // 16 tokens span less than 4 GiB (16-byte units)
+constexpr uint32_t kReachHead = 2;   // so does a whole head
 
-struct RowCursor {  // a tile token (i, j of the current frame) and its offset
-  int32_t i, j;
-  uint32_t off16;
+__device__ __forceinline__ uint32_t divide(uint32_t n, const Divisor d) { return (__umulhi(n, d.mul) >> d.shift) + (n & d.all); }
+
+struct WindowToken {
+  uint32_t off16;   // offset from the canvas tensor's head
+  int32_t x0j, j;   // x0 + column before wrapping, column inside the tile
 };
-
-__device__ __forceinline__ RowCursor cursor_at(const View16& vw, int n) {
-  const int plane = vw.th * vw.tw;
-  const int t = n / plane, r = n - t * plane;
-  RowCursor c;
-  c.i = r / vw.tw;
-  c.j = r - c.i * vw.tw;
-  // canvas token index = (t*H + i)*W + j = n + (t*th + i)*(W - tw) + t*(H - th)*W
-  c.off16 = (uint32_t)n * vw.st16 + (uint32_t)(t * vw.th + c.i) * vw.row_skip16 + (uint32_t)t * vw.frame_skip16;
-  return c;
-}
-__device__ __forceinline__ void cursor_advance(const View16& vw, RowCursor& c, int step) {
-  c.j += step;
-  c.off16 += (uint32_t)step * vw.st16;
-  while (c.j >= vw.tw) {
-    c.j -= vw.tw;
-    c.off16 += vw.row_skip16;
-    if (++c.i == vw.th) { c.i = 0; c.off16 += vw.frame_skip16; }
-  }
-}
-
-// Wrapped window of a shifted partition (Algorithm 1 "Shift"): tile token (t, i, j) sits at canvas row
-// (y0 + i) mod H, column (x0 + j) mod W, so a tile row may consist of two runs and the offset is formed
-// from the coordinates each time.
-struct WrapCursor {
-  int32_t t, i, j;
-};
-__device__ __forceinline__ WrapCursor wrap_cursor_at(const View16& vw, int n) {
-  const int plane = vw.th * vw.tw;
-  WrapCursor c;
-  c.t = n / plane;
-  const int r = n - c.t * plane;
-  c.i = r / vw.tw;
-  c.j = r - c.i * vw.tw;
-  return c;
-}
-__device__ __forceinline__ void wrap_cursor_advance(const View16& vw, WrapCursor& c, int step) {
-  c.j += step;
-  while (c.j >= vw.tw) {
-    c.j -= vw.tw;
-    if (++c.i == vw.th) { c.i = 0; ++c.t; }
-  }
-}
-__device__ __forceinline__ uint32_t wrap_offset16(const View16& vw, const WrapCursor& c, int y0, int x0) {
-  int y = y0 + c.i, x = x0 + c.j;
+__device__ __forceinline__ WindowToken window_token(const View16& vw, int n, int y0, int x0) {
+  const int t = (int)divide((uint32_t)n, vw.by_plane);
+  const int r = n - t * (vw.th * vw.tw);
+  const int i = (int)divide((uint32_t)r, vw.by_row);
+  WindowToken k;
+  k.j = r - i * vw.tw;
+  k.x0j = x0 + k.j;
+  int y = y0 + i, x = k.x0j;
   y -= (y >= vw.H) ? vw.H : 0;
   x -= (x >= vw.W) ? vw.W : 0;
-  return (uint32_t)((c.t * vw.H + y) * vw.W + x) * vw.st16;
+  k.off16 = (uint32_t)((t * vw.H + y) * vw.W + x) * vw.st16;
+  return k;
 }
 
-// Host side: the device view of a tile shape.
+// Host side: the divisor of 0 <= n < 2^31 by d >= 1.  With l = ceil(log2 d) the rounded-up reciprocal
+// floor(2^(31+l) / d) + 1 is below 2^32 and exact for 31-bit dividends (Granlund and Montgomery, 1994).
+inline Divisor make_divisor(uint32_t d) {
+  if (d <= 1) return {0u, 0u, 0xffffffffu};
+  uint32_t l = 0;
+  while ((1ull << l) < d) ++l;
+  return {(uint32_t)((1ull << (31 + l)) / d + 1), l - 1, 0u};
+}
 inline View16 make_view16(const TileView& tv) {
   View16 vw;
   vw.st16 = (uint32_t)(tv.stride_token / 8);
-  vw.row_skip16 = (uint32_t)(tv.W - tv.tw) * vw.st16;
-  vw.frame_skip16 = (uint32_t)((int64_t)(tv.H - tv.th) * tv.W) * vw.st16;
-  vw.th = tv.th; vw.tw = tv.tw; vw.N = tv.N;
   vw.head16 = (uint32_t)(tv.stride_head / 8);
+  vw.th = tv.th; vw.tw = tv.tw; vw.N = tv.N;
   vw.H = tv.H; vw.W = tv.W;
+  vw.by_plane = make_divisor((uint32_t)tv.th * (uint32_t)tv.tw);
+  vw.by_row = make_divisor((uint32_t)tv.tw);
+  vw.reach = (tv.stride_token / 8 < (1 << 23) ? kReachLane : 0u) |
+             ((int64_t)tv.T * tv.H * tv.W * (tv.stride_token / 8) < (1ll << 28) ? kReachHead : 0u);
   return vw;
 }
 

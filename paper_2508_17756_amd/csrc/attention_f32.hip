@@ -42,7 +42,7 @@ constexpr int kWaveBytes = 16384;   // LDS of a wavefront: its K block, after th
 template <int QB>
 constexpr int kLds = KS * kWaveBytes + 2 * KS * QB * 32 * 4;   // and (reference, sum) per wavefront and query
 
-enum { kCursor = 0, kLinearRows = 1, kWrappedRows = 2 };   // how a tile token is found
+enum { kLinear = 0, kWindow = 1 };   // how a tile token is found
 
 template <int D, int QB, int MODE>
 __global__ __launch_bounds__(kThreads) void attention_f32_kernel(
@@ -64,12 +64,10 @@ __global__ __launch_bounds__(kThreads) void attention_f32_kernel(
   const int nth = logical / per_tile, in_tile = logical - nth * per_tile;
   const int tile = __builtin_amdgcn_readfirstlane(attn_nth_tile(active, nth));
   const int head = in_tile / n_qblocks, qblk = in_tile - head * n_qblocks;
-  const int wy0 = (MODE == kWrappedRows) ? tab.y0[tile] : 0, wx0 = (MODE == kWrappedRows) ? tab.x0[tile] : 0;
+  const int wy0 = (MODE == kWindow) ? tab.y0[tile] : 0, wx0 = (MODE == kWindow) ? tab.x0[tile] : 0;
   // offset of tile token n from the tile's pointers, in units of 8 elements (32 bytes)
   auto token_off8 = [&](int n) SG_INLINE -> uint32_t {
-    if (MODE == kLinearRows) return (uint32_t)n * vw.st16;
-    if (MODE == kWrappedRows) return wrap_offset16(vw, wrap_cursor_at(vw, n), wy0, wx0);
-    return cursor_at(vw, n).off16;
+    return (MODE == kLinear) ? (uint32_t)n * vw.st16 : window_token(vw, n, wy0, wx0).off16;
   };
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const int lq = lane & 31, half = lane >> 5;
@@ -300,9 +298,8 @@ int launch_attention_f32(const TileView& tv, int heads, int head_dim, float scal
   if (head_dim != 64 && head_dim != 128) return SG_ERR_UNSUPPORTED;
   if (b.n_tiles <= 0) return SG_OK;
   const View16 vw = make_view16(tv);
-  const int mode = tv.wrapped ? kWrappedRows : ((tv.W == tv.tw && tv.H == tv.th) ? kLinearRows : kCursor);
   constexpr int kMaxDevices = 64;
-  static std::atomic<bool> attr_set[kMaxDevices][9];   // zero-initialised; set twice by racing threads is harmless
+  static std::atomic<bool> attr_set[kMaxDevices][6];   // zero-initialised; set twice by racing threads is harmless
   int dev = 0, n_cu = 0;
   SG_HIP_TRY(hipGetDevice(&dev));
   SG_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
@@ -338,12 +335,11 @@ int launch_attention_f32(const TileView& tv, int heads, int head_dim, float scal
       return SG_OK;
     };
     int st;
-#define SG_F32_MODES(D, QB, SLOT)                                                            \
-  (mode == kLinearRows    ? launch(attention_f32_kernel<D, QB, kLinearRows>, kLds<QB>, SLOT)      \
-   : mode == kWrappedRows ? launch(attention_f32_kernel<D, QB, kWrappedRows>, kLds<QB>, SLOT + 1) \
-                          : launch(attention_f32_kernel<D, QB, kCursor>, kLds<QB>, SLOT + 2))
+#define SG_F32_MODES(D, QB, SLOT)                                                   \
+  (tv.window ? launch(attention_f32_kernel<D, QB, kWindow>, kLds<QB>, SLOT)          \
+             : launch(attention_f32_kernel<D, QB, kLinear>, kLds<QB>, SLOT + 1))
     if (head_dim == 128) st = SG_F32_MODES(128, 1, 0);
-    else st = wide ? SG_F32_MODES(64, 2, 3) : SG_F32_MODES(64, 1, 6);
+    else st = wide ? SG_F32_MODES(64, 2, 2) : SG_F32_MODES(64, 1, 4);
 #undef SG_F32_MODES
     if (st != SG_OK) return st;
     SG_HIP_TRY(hipGetLastError());

@@ -40,13 +40,13 @@ static int validate(const sg_problem* p) {
 }
 
 // Shape and strides shared by all tiles of p.
-static TileView make_view(const sg_problem& p, bool wrapped) {
+static TileView make_view(const sg_problem& p, bool window) {
   TileView tv;
   tv.stride_token = p.grid_stride_token;
   tv.stride_head = p.grid_stride_head;
   tv.T = p.T; tv.H = p.H; tv.W = p.W; tv.th = p.tile_h; tv.tw = p.tile_w;
   tv.N = p.T * p.tile_h * p.tile_w;
-  tv.wrapped = wrapped;
+  tv.window = window;
   return tv;
 }
 
@@ -66,35 +66,22 @@ static int attention_launch(const sg_problem& p, const TileView& tv, const AttnB
   return launch_attention_bf16(tv, p.heads, p.head_dim, p.scale, b, s);
 }
 
-// Attention of the listed tiles of canvas tensors q, k, v, read in place, in as few launches as possible
-// (Algorithm 1: for all tiles of the partition).  Under a shifted partition the windows that cross a canvas
-// edge are read through the wrapping loader and the others as ordinary windows at their shifted origin.
+// Attention of the listed tiles of canvas tensors q, k, v, read in place, in one launch per table of tiles
+// (Algorithm 1: for all tiles of the partition), whether their windows wrap around a canvas edge or not.
 // tiles[i] = tile_row * n_tile_cols + tile_col;  out[i] = packed output of tiles[i].
 static int attention_canvas_tiles(const sg_problem& p, const void* q, const void* k, const void* v, const int* tiles,
                                   int n, void* const* out, hipStream_t s) {
-  const size_t esz = p.dtype == SG_BF16 ? 2 : 4;
   const void* qp[SG_MAX_TILES]; const void* kp[SG_MAX_TILES]; const void* vp[SG_MAX_TILES];
-  void* op[SG_MAX_TILES];
   int32_t y0[SG_MAX_TILES], x0[SG_MAX_TILES];
-  for (int pass = 0; pass < 2; ++pass) {   // pass 0: windows inside the canvas; pass 1: windows that wrap
-    int m = 0;
-    for (int i = 0; i < n; ++i) {
-      const int tr = tiles[i] / p.n_tile_cols, tc = tiles[i] - tr * p.n_tile_cols;
-      const int y = (int)(((int64_t)tr * p.stride_h + p.shift_h) % p.H), x = (int)(((int64_t)tc * p.stride_w + p.shift_w) % p.W);
-      const bool wraps = y + p.tile_h > p.H || x + p.tile_w > p.W;
-      if (wraps != (pass == 1)) continue;
-      const size_t origin = wraps ? 0 : (size_t)(((int64_t)y * p.W + x) * p.grid_stride_token) * esz;
-      qp[m] = (const char*)q + origin; kp[m] = (const char*)k + origin; vp[m] = (const char*)v + origin;
-      op[m] = out[i];
-      y0[m] = y; x0[m] = x;
-      ++m;
-    }
-    if (!m) continue;
-    const AttnBatch b = {m, qp, kp, vp, op, pass ? y0 : nullptr, pass ? x0 : nullptr, nullptr, nullptr, nullptr, 0, nullptr};
-    const int st = attention_launch(p, make_view(p, pass == 1), b, s);
-    if (st != SG_OK) return st;
+  for (int i = 0; i < n; ++i) {
+    const int tr = tiles[i] / p.n_tile_cols, tc = tiles[i] - tr * p.n_tile_cols;
+    qp[i] = q; kp[i] = k; vp[i] = v;
+    y0[i] = (int32_t)(((int64_t)tr * p.stride_h + p.shift_h) % p.H);
+    x0[i] = (int32_t)(((int64_t)tc * p.stride_w + p.shift_w) % p.W);
   }
-  return SG_OK;
+  const bool window = p.H != p.tile_h || p.W != p.tile_w || p.shift_h != 0 || p.shift_w != 0;
+  const AttnBatch b = {n, qp, kp, vp, out, y0, x0, nullptr, nullptr, nullptr, 0, nullptr};
+  return attention_launch(p, make_view(p, window), b, s);
 }
 
 // Attention of packed tile inputs x[i] = [3][heads][T][tile_h][tile_w][d] (Q, K, V) in one launch; tiles whose

@@ -21,19 +21,18 @@ struct TileView {
   int32_t T, H, W;       // canvas
   int32_t th, tw;        // tile
   int32_t N;             // T*th*tw tokens
-  bool wrapped;          // shifted partition: windows wrap around the canvas edges
+  bool window;           // tiles are windows of canvas tensors (else packed: the canvas is one unshifted tile)
 };
 
-// The tiles of one attention call.  For a fixed partition q[i], k[i], v[i] point at tile i's first token
-// (the tile origin is folded into the pointer); for wrapped windows they are the canvas tensors and
-// (y0[i], x0[i]) is the canvas position of tile i's first token.
+// The tiles of one attention call.  q[i], k[i], v[i] are tile i's packed tensors or, for windows, the canvas
+// tensors, and (y0[i], x0[i]) is then the canvas position of tile i's first token.
 struct AttnBatch {
   int n_tiles;
   const void* const* q;      // host arrays of n_tiles device pointers
   const void* const* k;
   const void* const* v;
   void* const* out;          // packed tile outputs
-  const int32_t* y0;         // host arrays, wrapped windows only (else nullptr)
+  const int32_t* y0;         // host arrays, windows only (else nullptr)
   const int32_t* x0;
   const uint8_t* run_flags;  // device, n_tiles bytes: tiles with a 0 are skipped; nullptr = all tiles run
   // Cache refresh of the tiled step, carried out by the same launch where the kernel supports it (*refreshed is
@@ -48,8 +47,6 @@ struct AttnBatch {
 // Launchers (each validates nothing: the API layer has already done so).
 int launch_attention_f32(const TileView& tv, int heads, int head_dim, float scale, const AttnBatch& b, hipStream_t s);
 int launch_attention_bf16(const TileView& tv, int heads, int head_dim, float scale, const AttnBatch& b, hipStream_t s);
-int launch_attention_bf16_generic(const TileView& tv, int heads, int head_dim, float scale, const AttnBatch& b,
-                                  hipStream_t s);
 int launch_blend(const sg_problem& p, const void* const* tile_out, void* grid_out, const void* latent, float c_latent,
                  float c_noise, hipStream_t s);
 int launch_slice(const sg_problem& p, const void* const* src, int n_src, int tile_row, int tile_col, void* dst,

@@ -202,6 +202,31 @@ def test_attention_reads_a_wrapped_window_in_place(case):
     assert 0 < wrapped < g.n_tiles or g.n_tiles == 1      # the case exercises both kinds of window
 
 
+@pytest.mark.parametrize("d,T,th,tw,shift,token_major", [
+    (128, 7, 13, 47, (6, 3), False),     # 4,277 tokens = 66 full stages and a tail; breaks everywhere, the edge 3 tokens before a row's end
+    (128, 5, 27, 32, (0, 31), False),    # rows are whole runs; the edge one token after a row's start
+    (128, 60, 9, 8, (8, 5), True),       # rows as wide as a run: two breaks in every run
+    (128, 50, 12, 7, (5, 2), False),     # narrower than a run: every lane looks its token up
+    (64, 9, 21, 45, (20, 44), False),    # 8,505 tokens = 66 full stages and a tail of 57
+    (64, 31, 17, 16, (3, 15), True),     # rows as wide as a run of 16
+    (64, 40, 16, 13, (0, 6), False),     # narrower than a run
+])
+def test_attention_window_runs_and_breaks(d, T, th, tw, shift, token_major):
+    """The streaming kernel's window loader past its first 64 stages (the plan of the runs is renewed there): every tile of a
+    2 x 2 partition, so windows that cross neither, one and both canvas edges; sampled query rows against the oracle."""
+    g = TileGeometry("runs", T, 2 * th, 2 * tw, th, tw, th, tw, 2, 2, 1, d, "bf16", 600 + tw)
+    q, k, v = [randn_tensor(g.grid_shape, "bf16", g.seed + i).cuda() for i in range(3)]
+    laid = [t.permute(1, 2, 3, 0, 4).contiguous() if token_major else t for t in (q, k, v)]
+    p = sg.make_problem(g, token_major=token_major, shift=shift)
+    rows = np.unique(np.concatenate([np.arange(0, g.tile_tokens, 131), [g.tile_tokens - 1]]))
+    for tr in range(2):
+        for tc in range(2):
+            out = torch.full(g.tile_shape, float("nan"), dtype=torch.bfloat16, device="cuda")
+            sg.sg_tile_attention(p, *laid, tr, tc, out)
+            win = [oracle.slice_tile_shifted(to_f64(t), g, tr, tc, *shift).reshape(-1, d) for t in (q, k, v)]
+            assert_close(to_f64(out).reshape(-1, d)[rows], oracle.attention_rows(win[0][rows], win[1], win[2], g.scale), "bf16", (tr, tc))
+
+
 def _random_tilings(count, seed):
     rng = np.random.default_rng(seed)
     out = []

@@ -256,7 +256,7 @@ typedef struct sg_step_io {
  *     step); grid_out = Fuse of all cache_out.
  * The decisions stay on the device and nothing is read back: one attention launch covers all tiles
  * and numbers only the work of the tiles to recompute; for bf16 problems the same launch also carries
- * the cache refresh, on the compute units its last, partial round of workgroups leaves idle.
+ * the cache refresh, stored from the stages of keys and values as they pass through it.
  */
 int sg_denoise_step_tiled(const sg_problem* p, const sg_step_io* io, void* stream);
 

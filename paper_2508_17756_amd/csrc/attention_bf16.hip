@@ -43,10 +43,11 @@ constexpr int kLdsBytes = 2 * kStages * kTileBytes;  // 128 KiB
 
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
-  static_assert(N == 0 || N == 4 || N == 8, "");
+  static_assert(N == 0 || N == 4 || N == 8 || N == 12, "");
   if (N == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   if (N == 4) asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
   if (N == 8) asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+  if (N == 12) asm volatile("s_waitcnt vmcnt(12)" ::: "memory");
 }
 __device__ __forceinline__ void meet() {  // workgroup barrier that nothing is scheduled across
   __builtin_amdgcn_sched_barrier(0);
@@ -140,12 +141,15 @@ constexpr float kOverflowGuard = 65536.0f;   // a stage's exponentials may grow 
 
 enum { kLinear = 0, kWindow = 1 };   // packed tile, or window of a canvas (see the DMA loader)
 
-template <int D, int MODE>
+// REFRESH: the launch also refreshes the cache of the tiles it attends (packed tiles: refresh <- the tile's Q, K, V,
+// has_cache <- 1).
+template <int D, int MODE, bool REFRESH>
 __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 vw, const float c_log2, const int heads,
                                                                   const int n_qblocks, const int n_tiles, const AttnTable tab,
-                                                                  const uint8_t* __restrict__ run_flags, const int first_copy_block,
-                                                                  const int64_t copy_vecs, uint8_t* __restrict__ has_cache) {
+                                                                  const uint8_t* __restrict__ run_flags,
+                                                                  uint8_t* __restrict__ has_cache) {
   static_assert(D == 128 || D == 64, "head_dim 64 or 128");
+  static_assert(!REFRESH || MODE == kLinear, "a packed tile's input is refreshed");
   // LDS rows ("slots") are always 256 bytes.  With head_dim 128 a slot is one key and a stage 64 keys; with
   // head_dim 64 a stage is 128 keys and slot s holds the keys 2 s and 2 s + 1, neighbours in a tile row, so the
   // transfers, the fragment reads and the MFMA count per stage are the same and only the pairing of
@@ -169,31 +173,7 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
   const int per_xcd = (total + kXcd - 1) / kXcd;
   const int xcd = blockIdx.x % kXcd, slot = blockIdx.x / kXcd;
   const int logical = xcd * per_xcd + slot;
-  if (slot >= per_xcd || logical >= total) {
-    // The workgroups behind the attention grid carry the step's cache refresh (cache_x <- x for the tiles that run):
-    // they are dispatched last, onto the compute units the attention's final, partial round leaves idle, and
-    // stream through HBM, which the attention hardly uses.  Chunks of one vector per thread are dealt round-robin,
-    // so the copy walks both buffers as one contiguous window.
-    if ((int)blockIdx.x < first_copy_block) return;
-    const int c = blockIdx.x - first_copy_block, n_copy = gridDim.x - first_copy_block;
-    for (uint32_t m = active; m; m &= m - 1) {
-      const int t = __builtin_ctz(m);
-      const u32x4* __restrict__ src = (const u32x4*)tab.q[t];
-      u32x4* __restrict__ dst = (u32x4*)tab.refresh[t];
-      int64_t i = (int64_t)c * kThreads + threadIdx.x;
-      const int64_t step = (int64_t)n_copy * kThreads;
-      for (; i + 7 * step < copy_vecs; i += 8 * step) {   // eight 16-byte loads in flight per thread
-        u32x4 v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = __builtin_nontemporal_load(src + i + u * step);
-#pragma unroll
-        for (int u = 0; u < 8; ++u) __builtin_nontemporal_store(v[u], dst + i + u * step);
-      }
-      for (; i < copy_vecs; i += step) __builtin_nontemporal_store(__builtin_nontemporal_load(src + i), dst + i);
-      if (c == 0 && threadIdx.x == 0) has_cache[t] = 1;
-    }
-    return;
-  }
+  if (slot >= per_xcd || logical >= total) return;
   const int nth = logical / per_tile, in_tile = logical - nth * per_tile;
   const int tile = __builtin_amdgcn_readfirstlane(attn_nth_tile(active, nth));
   const int head = __builtin_amdgcn_readfirstlane(in_tile / n_qblocks), qblk = in_tile - head * n_qblocks;   // uniform, and kept scalar
@@ -317,15 +297,7 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
   const uint64_t stage_bytes = (uint64_t)(kKeys * 16) * vw.st16;
   const char* kcur = (const char*)kh + (uint64_t)(kTok * wave * 16) * vw.st16;
   const char* vcur = (const char*)vh + (uint64_t)(kTok * wave * 16) * vw.st16;
-  // issue stage `blk`, whose keys are all below N, into ring slot `st` = blk % 4
-  auto issue_full = [&](int blk, int st) SG_INLINE {
-    const uint32_t dst = dma_dst + st * kTileBytes;
-    if (MODE == kLinear) {
-      move_run(kcur, vcur, dst);
-      kcur += stage_bytes;
-      vcur += stage_bytes;
-      return;
-    }
+  auto move_planned = [&](int blk, uint32_t dst) SG_INLINE {
     if (run_info == 0) {
       const uint64_t first = (uint64_t)run_first16 << 4;
       move_run((const char*)kh + first, (const char*)vh + first, dst);
@@ -344,14 +316,55 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
     } else {   // tiles narrower than a run, heads of 4 GiB and more
       look_up(blk, dst);
     }
-    if (st == kStages - 1 && (blk & 63) == 63) plan64(blk + 1);
-    fetch_plan(blk + 1);
   };
+  // issue stage `blk`, whose keys are all below N, into ring slot `st` = blk % 4
+  auto issue_full = [&](int blk, int st) SG_INLINE {
+    const uint32_t dst = dma_dst + st * kTileBytes;
+    if (MODE == kLinear) {
+      move_run(kcur, vcur, dst);
+      kcur += stage_bytes;
+      vcur += stage_bytes;
+    } else {
+      move_planned(blk, dst);
+      if (st == kStages - 1 && (blk & 63) == 63) plan64(blk + 1);
+      fetch_plan(blk + 1);   // for the next steady iteration
+    }
+  };
+  // Cache refresh: a workgroup copies the keys and values of its own query rows out of the LDS ring while their stages are
+  // there (kCopy of its stages, each wavefront what it moved itself, to the place it came from), so that the copy reads
+  // nothing from HBM and its stores are spread over the launch; its rows of Q follow at the end.
+  constexpr int kCopy = kBR / kKeys;
+  const int copy0 = qblk * kCopy, copy_from = copy0 & ~(kStages - 1);
+  const int64_t to_cache = REFRESH ? (char*)tab.refresh[tile] - (const char*)tab.q[tile] : 0;
+  auto copies = [&](int k) SG_INLINE -> int { return (REFRESH && k >= copy0 && k < copy0 + kCopy) ? 1 : 0; };
+  auto copy_stage = [&](int k, bool full) SG_INLINE {
+    int l = lane;
+    asm volatile("" : "+v"(l));   // addresses are formed here, not kept in registers over the loop
+    const uint32_t at = dma_dst + (k % kStages) * kTileBytes + l * 16;
+    const int n0 = k * kKeys + kTok * wave;
+    const uint64_t run = (uint64_t)((uint32_t)n0 * vw.st16) << 4;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {   // K, V of the wavefront's first four slots, of the other four
+      const bool is_v = u & 1;
+      uint32_t c, off = is_v ? vlane[u >> 1] : klane[u >> 1];
+      asm volatile("" : "+v"(off));
+      const u32x4 x = *(const SG_LDS u32x4*)(uintptr_t)(at + (is_v ? kVRegion : 0) + (u >> 1) * (4 * kRowBytes));
+      char* const base = (char*)(is_v ? vh : kh) + to_cache + run;
+      if (full || n0 + slot_token(l, u >> 1, is_v, c) < N) __builtin_nontemporal_store(x, (u32x4*)(base + off));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+
   // the same for a stage that may hold keys >= N
   auto issue_any = [&](int blk, int st) SG_INLINE {
     const uint32_t dst = dma_dst + st * kTileBytes;
-    if (MODE == kLinear && blk * kKeys + kTok * (wave + 1) <= N) move_run(kcur, vcur, dst);
-    else look_up(blk, dst);
+    if (MODE == kWindow) {
+      if ((blk & 63) == 0) plan64(blk);
+      fetch_plan(blk);
+    }
+    if (blk * kKeys + kTok * (wave + 1) > N) look_up(blk, dst);
+    else if (MODE == kLinear) move_run(kcur, vcur, dst);
+    else move_planned(blk, dst);
     if (MODE == kLinear) {
       kcur += stage_bytes;
       vcur += stage_bytes;
@@ -517,10 +530,14 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
   const int grp1 = __builtin_amdgcn_readfirstlane((wave >> 2) ^ (D == 64 ? 1 : 0));
   auto wait_stage = [&](int younger_stages) SG_INLINE {   // own transfers: all but the youngest `younger_stages` stages landed
     __builtin_amdgcn_sched_barrier(0);
-    if (younger_stages >= 2) wait_vmcnt<8>();
+    if (younger_stages >= 3) wait_vmcnt<12>();
+    else if (younger_stages == 2) wait_vmcnt<8>();
     else if (younger_stages == 1) wait_vmcnt<4>();
     else wait_vmcnt<0>();
   };
+  // end of iteration k: the stage issued last but one has landed.  Behind its transfers stand those of the last stage and the
+  // four stores of every stage copied in this iteration and the one before (whole stages: none of them is skipped).
+  auto wait_iteration = [&](int k, bool issued) SG_INLINE { wait_stage(issued ? 1 + copies(k) + copies(k - 1) : 0); };
   bf16x8 p[2 * kMaxSB];   // the first 2 kSB entries
   // keeps the score registers live across the phase boundary (a macro: the statement has to sit in the
   // lambdas that are its call sites)
@@ -562,6 +579,18 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
     if (b < n_blocks) issue_any(b, b);
   wait_stage(n_blocks >= 3 ? 2 : (n_blocks == 2 ? 1 : 0));
   meet();
+  if (q0 >= N) {   // a wavefront without a query (the last query block) moves its share of the stages and leaves the matrix
+                   // pipe and the vector ALU to the other wavefront of its SIMD
+    wait_stage(n_blocks >= 3 ? 1 : 0);
+    meet();
+    for (int k = 0; k < n_blocks; ++k) {
+      if (k + 3 < n_blocks) issue_any(k + 3, (k + 3) % kStages);
+      if (copies(k)) copy_stage(k, (k + 1) * kKeys <= N);
+      wait_iteration(k, k + 3 <= n_blocks - 1);
+      meet();
+    }
+    return;
+  }
   qk(0, s, false);
   SG_PIN_SCORES();
   const int n_steady = (n_blocks >= 2 * kStages) ? kStages + ((n_blocks - 2 * kStages) / kStages) * kStages : 0;
@@ -572,9 +601,10 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
     meet();   // B_0
     auto general = [&](int k) SG_INLINE {
       if (k + 3 < n_blocks) issue_any(k + 3, (k + 3) % kStages);
+      if (copies(k)) copy_stage(k, (k + 1) * kKeys <= N);
       mfma_phase_any(k);
       if (k + 1 < n_blocks) softmax_pinned(k + 1, tail && k + 1 == n_blocks - 1, false);
-      wait_stage(k + 3 <= n_blocks - 1 ? 1 : 0);
+      wait_iteration(k, k + 3 <= n_blocks - 1);
       meet();
     };
     auto steady = [&](int k, auto st_tag) SG_INLINE {
@@ -587,15 +617,17 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
     };
     int k = 0;
     for (; k < kStages && k < n_blocks; ++k) general(k);
-    if (MODE == kWindow && k < n_steady) {
-      plan64(k + 3);
-      fetch_plan(k + 3);
-    }
-    for (; k < n_steady; k += kStages) {
-      steady(k, std::integral_constant<int, 0>{});
-      steady(k + 1, std::integral_constant<int, 1>{});
-      steady(k + 2, std::integral_constant<int, 2>{});
-      steady(k + 3, std::integral_constant<int, 3>{});
+    if (MODE == kWindow && k < n_steady) fetch_plan(k + 3);
+    for (;;) {   // a refresh interrupts the steady loop for the iterations around the stages it copies
+      const int until = (REFRESH && k <= copy0) ? (copy_from < n_steady ? copy_from : n_steady) : n_steady;
+      for (; k < until; k += kStages) {
+        steady(k, std::integral_constant<int, 0>{});
+        steady(k + 1, std::integral_constant<int, 1>{});
+        steady(k + 2, std::integral_constant<int, 2>{});
+        steady(k + 3, std::integral_constant<int, 3>{});
+      }
+      if (!REFRESH || k >= n_steady) break;
+      for (int i = 0; i < kStages; ++i, ++k) general(k);
     }
     for (; k < n_blocks; ++k) general(k);
   } else {
@@ -603,9 +635,10 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
     meet();   // B_0
     auto general = [&](int k) SG_INLINE {
       if (k + 3 < n_blocks) issue_any(k + 3, (k + 3) % kStages);
+      if (copies(k)) copy_stage(k, (k + 1) * kKeys <= N);
       softmax_pinned(k, tail && k == n_blocks - 1, k == 0);
       mfma_phase_any(k);
-      wait_stage(k + 3 <= n_blocks - 1 ? 1 : 0);
+      wait_iteration(k, k + 3 <= n_blocks - 1);
       meet();
     };
     auto steady = [&](int k, auto st_tag) SG_INLINE {
@@ -618,15 +651,17 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
     };
     int k = 0;
     for (; k < kStages && k < n_blocks; ++k) general(k);
-    if (MODE == kWindow && k < n_steady) {
-      plan64(k + 3);
-      fetch_plan(k + 3);
-    }
-    for (; k < n_steady; k += kStages) {
-      steady(k, std::integral_constant<int, 0>{});
-      steady(k + 1, std::integral_constant<int, 1>{});
-      steady(k + 2, std::integral_constant<int, 2>{});
-      steady(k + 3, std::integral_constant<int, 3>{});
+    if (MODE == kWindow && k < n_steady) fetch_plan(k + 3);
+    for (;;) {   // a refresh interrupts the steady loop for the iterations around the stages it copies
+      const int until = (REFRESH && k <= copy0) ? (copy_from < n_steady ? copy_from : n_steady) : n_steady;
+      for (; k < until; k += kStages) {
+        steady(k, std::integral_constant<int, 0>{});
+        steady(k + 1, std::integral_constant<int, 1>{});
+        steady(k + 2, std::integral_constant<int, 2>{});
+        steady(k + 3, std::integral_constant<int, 3>{});
+      }
+      if (!REFRESH || k >= n_steady) break;
+      for (int i = 0; i < kStages; ++i, ++k) general(k);
     }
     for (; k < n_blocks; ++k) general(k);
   }
@@ -634,6 +669,7 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
   // ---- epilogue: O^T accumulators -> packed tile [head][n][d]; register r of block db is
   // d = 32 db + 8 (r>>2) + 4 half + (r&3): 4 consecutive d = 8 bytes
   {
+    const int sub = lane / (D / 8), chunk = lane % (D / 8);
     const uint32_t lu = __float_as_uint(sm.l);
     const auto sw = __builtin_amdgcn_permlane32_swap(lu, lu, false, false);
     const float inv = 1.0f / (__uint_as_float(sw[0]) + __uint_as_float(sw[1]));
@@ -653,13 +689,30 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
         *(SG_LDS u32x2*)(uintptr_t)(buf + lq * (D * 2) + (((4 * db + g) ^ (lq & (kChunks - 1))) << 4) + 8 * half) = w;
       }
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    const int sub = lane / kChunks, c = lane % kChunks;
     u32x4* const dst = (u32x4*)(out + ((size_t)head * N + q0) * D);
 #pragma unroll
     for (int i = 0; i < 32 / kRowsPer; ++i) {
       const int r = kRowsPer * i + sub;
-      const u32x4 x = *(const SG_LDS u32x4*)(uintptr_t)(buf + r * (D * 2) + ((c ^ (r & (kChunks - 1))) << 4));
-      if (q0 + r < N) dst[r * kChunks + c] = x;
+      const u32x4 x = *(const SG_LDS u32x4*)(uintptr_t)(buf + r * (D * 2) + ((chunk ^ (r & (kChunks - 1))) << 4));
+      if (q0 + r < N) dst[r * kChunks + chunk] = x;
+    }
+    if constexpr (REFRESH) {   // this wavefront's rows of Q once more, for the cache
+      __builtin_amdgcn_sched_barrier(0);
+      constexpr int kPieces = 32 / kRowsPer;
+      const u32x4* const qs = qg + head_off16;
+      u32x4* const qd = (u32x4*)((char*)qs + to_cache);
+      u32x4 x[kPieces];
+#pragma unroll
+      for (int i = 0; i < kPieces; ++i) {
+        const int r = q0 + kRowsPer * i + sub;
+        x[i] = qs[(uint32_t)(r < N ? r : N - 1) * vw.st16 + chunk];
+      }
+#pragma unroll
+      for (int i = 0; i < kPieces; ++i) {
+        const int r = q0 + kRowsPer * i + sub;
+        if (r < N) __builtin_nontemporal_store(x[i], qd + (uint32_t)r * vw.st16 + chunk);
+      }
+      if (in_tile == 0 && tid == 0) has_cache[tile] = 1;
     }
   }
 }
@@ -669,6 +722,8 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
 int launch_attention_bf16(const TileView& tv, int heads, int head_dim, float scale, const AttnBatch& b, hipStream_t s) {
   if (head_dim != 128 && head_dim != 64) return SG_ERR_UNSUPPORTED;
   if (b.n_tiles <= 0) return SG_OK;
+  // three stages of 128 keys and fewer do not fill the pipeline: measured in attention_bf16_short.hip
+  if (head_dim == 64 && tv.window && tv.N <= 384) return launch_attention_bf16_short(tv, heads, scale, b, s);
   const View16 vw = make_view16(tv);
   // a packed tile whose tokens are so far apart that 16 of them span 4 GiB is read like a window (of itself)
   const bool window = tv.window || !(vw.reach & kReachLane);
@@ -676,14 +731,11 @@ int launch_attention_bf16(const TileView& tv, int heads, int head_dim, float sca
   const float c_log2 = scale * 1.4426950408889634f;
   // the kernels need more dynamic LDS than the default limit; the attribute is set once per device and kernel
   constexpr int kMaxDevices = 64;
-  static std::atomic<bool> attr_set[kMaxDevices][4];   // zero-initialised; set twice by racing threads is harmless
-  int dev = 0, n_cu = 0;
+  static std::atomic<bool> attr_set[kMaxDevices][6];   // zero-initialised; set twice by racing threads is harmless
+  int dev = 0;
   SG_HIP_TRY(hipGetDevice(&dev));
-  SG_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-  if (n_cu < 4) n_cu = 4;
   // the cache refresh rides on this launch for packed tiles (their inputs are one contiguous run each)
-  const bool fuse_refresh = b.refresh_dst && b.has_cache && b.refresh_bytes > 0 && (b.refresh_bytes & 15) == 0 && !window;
-  bool tab_refresh_ok = false;
+  const bool fuse_refresh = b.refresh_dst && b.has_cache && !window;
   for (int t0 = 0; t0 < b.n_tiles; t0 += kAttnTilesPerLaunch) {
     const int n = (b.n_tiles - t0 < kAttnTilesPerLaunch) ? b.n_tiles - t0 : kAttnTilesPerLaunch;
     AttnTable tab;
@@ -698,16 +750,8 @@ int launch_attention_bf16(const TileView& tv, int heads, int head_dim, float sca
     }
     const int64_t total = (int64_t)n * heads * n_qblocks;   // the grid covers every tile; skipped tiles' share exits at once
     const int64_t attn_blocks = ((total + kXcd - 1) / kXcd) * kXcd;
-    // fused cache refresh: as many copy workgroups as the attention's last round leaves compute units idle (at least
-    // a quarter of the device), appended to the grid
-    int64_t copy_blocks = 0;
-    if (fuse_refresh) {
-      copy_blocks = n_cu - attn_blocks % n_cu;
-      if (copy_blocks < n_cu / 4) copy_blocks += n_cu;
-      tab_refresh_ok = true;
-    }
-    if (attn_blocks + copy_blocks > (1ll << 31) - 1) return SG_ERR_UNSUPPORTED;
-    const dim3 grid((unsigned)(attn_blocks + copy_blocks));
+    if (attn_blocks > (1ll << 31) - 1) return SG_ERR_UNSUPPORTED;
+    const dim3 grid((unsigned)attn_blocks);
     const uint8_t* flags = b.run_flags ? b.run_flags + t0 : nullptr;
     for (int i = 0; i < kAttnTilesPerLaunch; ++i) tab.refresh[i] = (fuse_refresh && i < n) ? b.refresh_dst[t0 + i] : nullptr;
     auto launch = [&](auto kern, int slot) -> int {
@@ -715,18 +759,21 @@ int launch_attention_bf16(const TileView& tv, int heads, int head_dim, float sca
         SG_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes));
         if (dev >= 0 && dev < kMaxDevices) attr_set[dev][slot].store(true, std::memory_order_release);
       }
-      kern<<<grid, kThreads, kLdsBytes, s>>>(vw, c_log2, heads, n_qblocks, n, tab, flags, (int)attn_blocks,
-                                             fuse_refresh ? b.refresh_bytes / 16 : 0,
+      kern<<<grid, kThreads, kLdsBytes, s>>>(vw, c_log2, heads, n_qblocks, n, tab, flags,
                                              fuse_refresh ? b.has_cache + t0 : nullptr);
       return SG_OK;
     };
     int st = SG_OK;
-    if (head_dim == 64) st = window ? launch(attention_bf16_kernel<64, kWindow>, 0) : launch(attention_bf16_kernel<64, kLinear>, 1);
-    else st = window ? launch(attention_bf16_kernel<128, kWindow>, 2) : launch(attention_bf16_kernel<128, kLinear>, 3);
+    if (head_dim == 64)
+      st = window ? launch(attention_bf16_kernel<64, kWindow, false>, 0)
+           : fuse_refresh ? launch(attention_bf16_kernel<64, kLinear, true>, 1) : launch(attention_bf16_kernel<64, kLinear, false>, 2);
+    else
+      st = window ? launch(attention_bf16_kernel<128, kWindow, false>, 3)
+           : fuse_refresh ? launch(attention_bf16_kernel<128, kLinear, true>, 4) : launch(attention_bf16_kernel<128, kLinear, false>, 5);
     if (st != SG_OK) return st;
     SG_HIP_TRY(hipGetLastError());
   }
-  if (b.refreshed) *b.refreshed = tab_refresh_ok;
+  if (b.refreshed) *b.refreshed = fuse_refresh;
   return SG_OK;
 }
 

@@ -47,6 +47,7 @@ struct AttnBatch {
 // Launchers (each validates nothing: the API layer has already done so).
 int launch_attention_f32(const TileView& tv, int heads, int head_dim, float scale, const AttnBatch& b, hipStream_t s);
 int launch_attention_bf16(const TileView& tv, int heads, int head_dim, float scale, const AttnBatch& b, hipStream_t s);
+int launch_attention_bf16_short(const TileView& tv, int heads, float scale, const AttnBatch& b, hipStream_t s);   // head_dim 64, windows
 int launch_blend(const sg_problem& p, const void* const* tile_out, void* grid_out, const void* latent, float c_latent,
                  float c_noise, hipStream_t s);
 int launch_slice(const sg_problem& p, const void* const* src, int n_src, int tile_row, int tile_col, void* dst,

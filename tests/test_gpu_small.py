@@ -392,6 +392,34 @@ def test_step_cached_mode_bf16_three_steps(d):
             assert np.array_equal(to_f64(cache_x[i]).ravel(), state.cache_x[i])
 
 
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("T,th,tw", [(1, 5, 8), (1, 1, 255), (1, 16, 16), (1, 1, 257), (3, 20, 25), (5, 13, 21), (9, 16, 17), (11, 16, 29)])
+def test_step_refreshes_the_cache_while_it_attends(T, th, tw, d):
+    """The cache refresh that rides on the attention launch, bit for bit: one to twenty query blocks, whose stages lie in the
+    first iterations, the steady loop and the last ones; ragged and whole last stages (N = 40 ... 5,104); the tile that is
+    reused keeps its cache."""
+    g = _geom("rf", T, 2 * th, tw, th, tw, th, tw, 2, d, "bf16", 77 + tw)
+    x = [randn_tensor((3,) + g.tile_shape, "bf16", g.seed + i).cuda() for i in range(2)]
+    cache = [torch.full_like(x[0], 3.0), x[1].clone()]          # tile 0 has drifted, tile 1 has not
+    has = torch.tensor([1, 1], dtype=torch.uint8, device="cuda")
+    out = [torch.full(g.tile_shape, 7.0, dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    cache[1].view(-1)[0] += 1.0                                 # ... measurably: a refresh of tile 1 would show
+    kept = cache[1].clone()
+    canvas = torch.empty(g.grid_shape, dtype=torch.bfloat16, device="cuda")
+    scores, rec = torch.empty(2, device="cuda"), torch.empty(2, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(sg.sg_workspace_bytes(2), dtype=torch.uint8, device="cuda")
+    for step in range(2):
+        if step == 1:
+            has.zero_()
+        sg.sg_denoise_step_tiled(sg.make_problem(g), canvas, out, tile_x=x, cache_x=cache, has_cache=has, threshold=0.5,
+                                 scores=scores, recompute=rec, workspace=ws)
+        assert rec.tolist() == ([1, 0] if step == 0 else [1, 1])
+        assert torch.equal(cache[0], x[0]) and has.tolist() == [1, 1]
+        assert torch.equal(cache[1], kept if step == 0 else x[1])
+    one = g.single_tile()
+    assert torch.equal(out[0], gpu_tile_attention(one, x[0][0], x[0][1], x[0][2], 0, 0))
+
+
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_step_cached_mode_many_tiles_one_launch_skips_on_the_device(dtype):
     """40 packed tiles (more than one launch's table of 32) through the cached step: the attention launches number

@@ -55,7 +55,7 @@ __global__ __launch_bounds__(kThreads) void gate_partial_kernel(GatePtrs ptrs, c
   const int64_t per_blk = (n_vec + n_blk - 1) / n_blk;
   const int64_t v0 = (int64_t)blk * per_blk;
   const int64_t v1 = (v0 + per_blk < n_vec) ? v0 + per_blk : n_vec;
-  for (int tile = 0; tile < n_tiles; ++tile) {
+  for (int tile = blockIdx.y; tile < n_tiles; tile += gridDim.y) {
     double* out = partial + ((size_t)(tile0 + tile) * kGateSlots + blk * kWavesPerBlock) * 2;
     if (!has_cache[tile0 + tile]) {  // no cached input: nothing to compare, buffers are not read
       if ((threadIdx.x & 63) == 0) { out[2 * (threadIdx.x >> 6)] = 0.0; out[2 * (threadIdx.x >> 6) + 1] = 0.0; }
@@ -212,7 +212,6 @@ constexpr int kRefreshTilesPerLaunch = 32;
 // halves 4.9 TB/s; chunks dealt round-robin 5.1; round-robin chunks with the lanes exchanging halves (below) 5.35,
 // the plain copy rate of the same device.  Unroll 1 / 4 and 2 - 4 workgroups per compute unit are no faster.
 constexpr int kRefreshUnroll = 2;
-constexpr int kRefreshBlocksPerCu = 1;
 
 // The eight fp32 residuals of a thread's 16-byte bf16 vector are 32 contiguous bytes, so a wavefront's 64 vectors
 // map to one 2 KiB run of delta.  Accessed as "every lane its own two 16-byte halves" each instruction would touch
@@ -305,7 +304,7 @@ __global__ __launch_bounds__(kThreads) void gain_refresh_kernel(GainPtrs ptrs, c
   const int64_t tail_first = (blk == (int)(n_chunks % n_blk)) ? main_end + threadIdx.x : n_vec, tail_end = n_vec;
   auto main_ok = [&](int64_t i) __attribute__((always_inline)) { return i - threadIdx.x < main_end; };
   auto tail_begin = [&](int64_t) __attribute__((always_inline)) { return tail_first; };
-  for (int tile = 0; tile < n_tiles; ++tile) {
+  for (int tile = blockIdx.y; tile < n_tiles; tile += gridDim.y) {
     double* out = partial + ((size_t)(tile0 + tile) * kGateSlots + blk * kWavesPerBlock) * 2;
     u32x4* __restrict__ oc = (u32x4*)ptrs.out_cur[tile];
     const u32x4* __restrict__ lat = (const u32x4*)ptrs.latent[tile];
@@ -449,17 +448,18 @@ static int launch_partials(const void* const* a, const void* const* b, const uin
   int dev = 0, n_cu = 0;
   SG_HIP_TRY(hipGetDevice(&dev));
   SG_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-  const int n_blk = n_cu < 1 ? 1 : (n_cu > kGateSlots / kWavesPerBlock ? kGateSlots / kWavesPerBlock : n_cu);
-  *n_slots = n_blk * kWavesPerBlock;
+  const int64_t n_vec = elems / (dtype == SG_BF16 ? 8 : 4);
+  *n_slots = (int)pass_grid(n_vec, 1, n_cu, kGateSlots / kWavesPerBlock).x * kWavesPerBlock;
   for (int t0 = 0; t0 < n_tiles; t0 += kTilesPerLaunch) {
     const int n = (n_tiles - t0 < kTilesPerLaunch) ? n_tiles - t0 : kTilesPerLaunch;
     GatePtrs ptrs;
     for (int i = 0; i < n; ++i) { ptrs.cur[i] = a[t0 + i]; ptrs.cached[i] = b[t0 + i]; }
     for (int i = n; i < kTilesPerLaunch; ++i) { ptrs.cur[i] = nullptr; ptrs.cached[i] = nullptr; }
+    const dim3 grid = pass_grid(n_vec, n, n_cu, kGateSlots / kWavesPerBlock);
     if (dtype == SG_BF16)
-      gate_partial_kernel<SG_BF16><<<n_blk, kThreads, 0, s>>>(ptrs, active, t0, n, elems, partial);
+      gate_partial_kernel<SG_BF16><<<grid, kThreads, 0, s>>>(ptrs, active, t0, n, elems, partial);
     else
-      gate_partial_kernel<SG_F32><<<n_blk, kThreads, 0, s>>>(ptrs, active, t0, n, elems, partial);
+      gate_partial_kernel<SG_F32><<<grid, kThreads, 0, s>>>(ptrs, active, t0, n, elems, partial);
     SG_HIP_TRY(hipGetLastError());
   }
   return SG_OK;
@@ -500,8 +500,8 @@ int launch_gain_refresh(void* const* out_cur, const void* const* out_prev, const
   int dev = 0, n_cu = 0;
   SG_HIP_TRY(hipGetDevice(&dev));
   SG_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-  int n_blk = (n_cu < 1 ? 1 : n_cu) * kRefreshBlocksPerCu;
-  if (n_blk > kGateSlots / kWavesPerBlock) n_blk = kGateSlots / kWavesPerBlock;
+  const int64_t n_vec = elems / (dtype == SG_BF16 ? 8 : 4);
+  const int n_blk = (int)pass_grid(n_vec, 1, n_cu, kGateSlots / kWavesPerBlock).x;
   for (int t0 = 0; t0 < n_tiles; t0 += kRefreshTilesPerLaunch) {
     const int n = (n_tiles - t0 < kRefreshTilesPerLaunch) ? n_tiles - t0 : kRefreshTilesPerLaunch;
     GainPtrs ptrs;
@@ -511,10 +511,11 @@ int launch_gain_refresh(void* const* out_cur, const void* const* out_prev, const
       ptrs.latent[i] = i < n ? latent[t0 + i] : nullptr;
       ptrs.delta[i] = i < n ? delta[t0 + i] : nullptr;
     }
+    const dim3 grid = pass_grid(n_vec, n, n_cu, kGateSlots / kWavesPerBlock);
     if (dtype == SG_BF16)
-      gain_refresh_kernel<SG_BF16><<<n_blk, kThreads, 0, s>>>(ptrs, recompute, gs.has_prev, t0, n, elems, partial);
+      gain_refresh_kernel<SG_BF16><<<grid, kThreads, 0, s>>>(ptrs, recompute, gs.has_prev, t0, n, elems, partial);
     else
-      gain_refresh_kernel<SG_F32><<<n_blk, kThreads, 0, s>>>(ptrs, recompute, gs.has_prev, t0, n, elems, partial);
+      gain_refresh_kernel<SG_F32><<<grid, kThreads, 0, s>>>(ptrs, recompute, gs.has_prev, t0, n, elems, partial);
     SG_HIP_TRY(hipGetLastError());
   }
   gain_refresh_finalize_kernel<<<n_tiles, kFinalThreads, 0, s>>>(partial, n_blk * kWavesPerBlock, recompute, step_change, gs.has_prev,

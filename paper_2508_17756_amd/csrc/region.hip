@@ -46,7 +46,7 @@ __global__ __launch_bounds__(kThreads) void tile_moments_kernel(StdPtrs ptrs, in
   const int64_t per_blk = (n_vec + n_blk - 1) / n_blk;
   const int64_t v0 = (int64_t)blk * per_blk;
   const int64_t v1 = (v0 + per_blk < n_vec) ? v0 + per_blk : n_vec;
-  for (int tile = 0; tile < n_tiles; ++tile) {
+  for (int tile = blockIdx.y; tile < n_tiles; tile += gridDim.y) {
     const u32x4* __restrict__ x = (const u32x4*)ptrs.x[tile];
     float pivot;
     if (DT == SG_BF16) pivot = bf16_bits_to_f32(((const uint16_t*)ptrs.x[tile])[0]);
@@ -156,13 +156,15 @@ int launch_tile_std(const void* const* x, int n_tiles, int64_t elems, int dtype,
   SG_HIP_TRY(hipGetDevice(&dev));
   SG_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
   constexpr int kWavesPerBlock = kThreads / 64;   // one partial slot per wavefront
-  const int n_blk = n_cu < 1 ? 1 : (n_cu > kGateSlots / kWavesPerBlock ? kGateSlots / kWavesPerBlock : n_cu);
+  const int64_t n_vec = elems / (dtype == SG_BF16 ? 8 : 4);
+  const int n_blk = (int)pass_grid(n_vec, 1, n_cu, kGateSlots / kWavesPerBlock).x;
   for (int t0 = 0; t0 < n_tiles; t0 += kTilesPerLaunch) {
     const int n = (n_tiles - t0 < kTilesPerLaunch) ? n_tiles - t0 : kTilesPerLaunch;
     StdPtrs ptrs;
     for (int i = 0; i < kTilesPerLaunch; ++i) ptrs.x[i] = i < n ? x[t0 + i] : nullptr;
-    if (dtype == SG_BF16) tile_moments_kernel<SG_BF16><<<n_blk, kThreads, 0, s>>>(ptrs, t0, n, elems, partial);
-    else tile_moments_kernel<SG_F32><<<n_blk, kThreads, 0, s>>>(ptrs, t0, n, elems, partial);
+    const dim3 grid = pass_grid(n_vec, n, n_cu, kGateSlots / kWavesPerBlock);
+    if (dtype == SG_BF16) tile_moments_kernel<SG_BF16><<<grid, kThreads, 0, s>>>(ptrs, t0, n, elems, partial);
+    else tile_moments_kernel<SG_F32><<<grid, kThreads, 0, s>>>(ptrs, t0, n, elems, partial);
     SG_HIP_TRY(hipGetLastError());
   }
   tile_std_finalize_kernel<<<n_tiles, kFinalThreads, 0, s>>>(partial, n_blk * kWavesPerBlock, elems, tile_std);

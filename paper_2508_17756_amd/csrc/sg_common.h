@@ -76,6 +76,22 @@ inline size_t gate_workspace_bytes(int n_tiles) {
   return (size_t)(n_tiles > 0 ? n_tiles : 1) * kGateSlots * 2 * sizeof(double);
 }
 
+// Grid of the streaming passes over tiles (x: workgroups that share a tile, y: tiles side by side).  Large tiles: one resident
+// workgroup per compute unit walks the tiles one after the other, y = 1 (no tail of late workgroups).  A tile with less than
+// kPassVecs 16-byte vectors for each of those is instead cut into workgroups of kPassVecs and all tiles run side by side: walked
+// in turn, every small tile costs each workgroup a round trip to memory and a reduction with nothing beside it.
+// Measured, walked -> cut (gate, similarity, tile statistics, gain refresh, us a call): 20 tiles of 1 MiB 30, 36, 26, 42 -> 14,
+// 14, 12, 24; 9 of 4 MiB 22, 36, 29, 36 -> 16, 17, 12, 34; 9 of 8 MiB 32, 33, 48, 61 -> 27, 27, 16, 60; from 16 MiB (4,096 vectors
+// for each of 256 compute units) the two are within 2 %.  2,048 vectors are 10 - 15 % slower at 8 MiB, 8,192 leave a single tile
+// of 4 - 16 MiB 20 - 40 % slower in the refresh.
+constexpr int64_t kPassVecs = 4096;
+inline dim3 pass_grid(int64_t n_vec, int n_tiles, int n_cu, int max_blk) {
+  const int64_t cut = (n_vec + kPassVecs - 1) / kPassVecs;
+  const int most = n_cu < 1 ? 1 : (n_cu > max_blk ? max_blk : n_cu);
+  if (cut >= most) return dim3((unsigned)most, 1);
+  return dim3((unsigned)(cut < 1 ? 1 : cut), (unsigned)n_tiles);
+}
+
 // bf16 <-> fp32 on the device.
 __device__ __forceinline__ float bf16_bits_to_f32(uint32_t bits16) {
   return __uint_as_float(bits16 << 16);

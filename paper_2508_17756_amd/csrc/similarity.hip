@@ -55,7 +55,7 @@ __global__ __launch_bounds__(kThreads) void similarity_partial_kernel(SimPtrs pt
   const int64_t per_blk = (n_vec + n_blk - 1) / n_blk;
   const int64_t v0 = (int64_t)blk * per_blk;
   const int64_t v1 = (v0 + per_blk < n_vec) ? v0 + per_blk : n_vec;
-  for (int tile = 0; tile < n_tiles; ++tile) {
+  for (int tile = blockIdx.y; tile < n_tiles; tile += gridDim.y) {
     const u32x4* __restrict__ a = (const u32x4*)ptrs.a[tile];
     const u32x4* __restrict__ b = (const u32x4*)ptrs.b[tile];
     float s0[kSums] = {0.f, 0.f, 0.f, 0.f, 0.f}, s1[kSums] = {0.f, 0.f, 0.f, 0.f, 0.f};
@@ -137,13 +137,15 @@ int launch_similarity(const void* const* x_new, const void* const* x_old, int n_
   SG_HIP_TRY(hipGetDevice(&dev));
   SG_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
   constexpr int kMaxBlk = kGateSlots * 2 / kSums;   // the tile's share of the workspace holds this many workgroups' sums
-  const int n_blk = n_cu < 1 ? 1 : (n_cu > kMaxBlk ? kMaxBlk : n_cu);
+  const int64_t n_vec = elems / (dtype == SG_BF16 ? 8 : 4);
+  const int n_blk = (int)pass_grid(n_vec, 1, n_cu, kMaxBlk).x;
   for (int t0 = 0; t0 < n_tiles; t0 += kTilesPerLaunch) {
     const int n = (n_tiles - t0 < kTilesPerLaunch) ? n_tiles - t0 : kTilesPerLaunch;
     SimPtrs ptrs;
     for (int i = 0; i < kTilesPerLaunch; ++i) { ptrs.a[i] = i < n ? x_new[t0 + i] : nullptr; ptrs.b[i] = i < n ? x_old[t0 + i] : nullptr; }
-    if (dtype == SG_BF16) similarity_partial_kernel<SG_BF16><<<n_blk, kThreads, 0, s>>>(ptrs, t0, n, elems, partial);
-    else similarity_partial_kernel<SG_F32><<<n_blk, kThreads, 0, s>>>(ptrs, t0, n, elems, partial);
+    const dim3 grid = pass_grid(n_vec, n, n_cu, kMaxBlk);
+    if (dtype == SG_BF16) similarity_partial_kernel<SG_BF16><<<grid, kThreads, 0, s>>>(ptrs, t0, n, elems, partial);
+    else similarity_partial_kernel<SG_F32><<<grid, kThreads, 0, s>>>(ptrs, t0, n, elems, partial);
     SG_HIP_TRY(hipGetLastError());
   }
   similarity_finalize_kernel<<<n_tiles, kFinalThreads, 0, s>>>(partial, n_blk, l1_rel, cos_sim);

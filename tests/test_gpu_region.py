@@ -146,3 +146,43 @@ def test_similarity_zero_tensors_many_tiles_and_arguments():
         sg.sg_tile_similarity([x], [x], torch.empty(1, device="cuda"), torch.empty(1, device="cuda"),
                               torch.empty(16, dtype=torch.uint8, device="cuda"))
     assert e.value.status == sg.SG_ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("vecs", [4095, 4096, 4097, 3 * 4096, 255 * 4096, 255 * 4096 + 1, 256 * 4096 + 7])
+def test_passes_over_tiles_cut_side_by_side_or_walked(dtype, vecs):
+    """Both grids of the streaming passes around the size where they change (4,096 vectors per workgroup, a device of 256 compute
+    units), over three tiles: every element is counted exactly once.  Small integers keep all sums exact in fp32 per thread
+    and fp64 across threads; the results below are those sums, rounded once (2^-24)."""
+    n = (vecs * (8 if dtype == "bf16" else 4) + 7) // 8 * 8
+    tiles, olds = [], []
+    for i in range(3):
+        x = (torch.arange(n, device="cuda") % (5 + i)).to(torch_dtype(dtype))
+        tiles.append(x)
+        olds.append((x.float() + 1).to(x.dtype))
+    ws = torch.empty(sg.sg_workspace_bytes(3), dtype=torch.uint8, device="cuda").fill_(255)
+    f = lambda: torch.full((3,), float("nan"), device="cuda")
+    std, l1, cs, scores, change = f(), f(), f(), f(), f()
+    has, rec = torch.ones(3, dtype=torch.uint8, device="cuda"), torch.empty(3, dtype=torch.uint8, device="cuda")
+    sg.sg_tile_std(tiles, std, ws)
+    sg.sg_tile_similarity(tiles, olds, l1, cs, ws)
+    sg.sg_cache_gate(tiles, olds, has, 0.5, scores, rec, ws)
+    state = sg.GainState(3)
+    state.has_prev.fill_(1)
+    out = [t.clone() for t in tiles]
+    delta = [torch.full((n,), 9.0, device="cuda") for _ in tiles]
+    recompute = torch.tensor([1, 0, 1], dtype=torch.uint8, device="cuda")
+    change.fill_(0.25)
+    sg.sg_gain_refresh(out, olds, olds, delta, recompute, change, state, ws)
+    for i, (x, y) in enumerate(zip(tiles, olds)):
+        x, y = x.double(), y.double()
+        want_l1 = float(n / y.sum())                       # |x - y| = 1 everywhere
+        want_cos = float((x * y).sum() / (x.norm() * y.norm()))
+        for got, want in ((std[i], float(x.std(unbiased=False))), (l1[i], want_l1), (cs[i], want_cos), (scores[i], want_l1)):
+            assert abs(float(got) - want) <= 2e-6 * max(1.0, abs(want)), (i, float(got), want)
+        if recompute[i]:
+            assert torch.equal(delta[i], torch.full((n,), -1.0, device="cuda")) and torch.equal(out[i], tiles[i])
+            assert abs(float(state.gain[i]) - want_l1 / 0.25) <= 2e-6 * want_l1 / 0.25
+        else:
+            assert torch.equal(delta[i], torch.full((n,), 9.0, device="cuda"))
+            assert torch.equal(out[i], (olds[i].float() + 9.0).to(olds[i].dtype))

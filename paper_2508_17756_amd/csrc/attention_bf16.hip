@@ -579,7 +579,7 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
     if (b < n_blocks) issue_any(b, b);
   wait_stage(n_blocks >= 3 ? 2 : (n_blocks == 2 ? 1 : 0));
   meet();
-  if (q0 >= N) {   // a wavefront without a query (the last query block) moves its share of the stages and leaves the matrix
+  if (__builtin_expect(q0 >= N, 0)) {   // a wavefront without a query (the last query block) moves its share of the stages and leaves the matrix
                    // pipe and the vector ALU to the other wavefront of its SIMD
     wait_stage(n_blocks >= 3 ? 1 : 0);
     meet();

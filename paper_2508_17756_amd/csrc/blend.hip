@@ -196,34 +196,40 @@ __global__ __launch_bounds__(kThreads) void blend_any_kernel(const BlendArgs a, 
   }
 }
 
-// SliceTile under a (possibly shifted, wrapping) partition: gathers the window of tile (tile_row, tile_col)
-// out of up to three canvas tensors into one packed buffer [n_src][heads][T][tile_h][tile_w][d].  A plain
-// copy, one 16-byte vector per thread, the packed side fully coalesced.
+// SliceTile under a (possibly shifted, wrapping) partition: gathers the windows of up to kSliceTiles tiles out of up to
+// three canvas tensors into packed buffers [n_src][heads][T][tile_h][tile_w][d], one per tile.  A plain copy, one 16-byte
+// vector per thread, the packed side fully coalesced.  One launch for all tiles: launched tile by tile, small tiles leave the
+// chip idle between them (a gathered step of 9 tiles of 920 tokens, 8 heads x 128: 110 -> 87 us; of 100 tokens, 2 heads: 35 -> 15).
+constexpr int kSliceTiles = 64;
 struct SliceArgs {
   const void* src[3];
-  int32_t n_src, T, H, W, th, tw, r0, c0;     // r0, c0: canvas position of the tile's token (0, 0), before wrapping
+  void* dst[kSliceTiles];
+  int16_t row[kSliceTiles], col[kSliceTiles];   // of the partition
+  int32_t n_src, T, H, W, th, tw, sh, sw, shift_h, shift_w;
   int32_t vec_per_token_log2;
   int64_t stride_token, stride_head;          // canvas strides in elements
   int32_t elem_bytes;
   uint32_t tile_plane_vecs;                   // th * tw * vectors per token
   int32_t heads;
 };
-__global__ __launch_bounds__(kThreads) void slice_kernel(const SliceArgs a, u32x4* __restrict__ dst) {
+__global__ __launch_bounds__(kThreads) void slice_kernel(const SliceArgs a) {
   const uint32_t v = blockIdx.x * kThreads + threadIdx.x;
   if (v >= a.tile_plane_vecs) return;
   const int plane = blockIdx.y;                 // head * T + t
-  const int which = blockIdx.z;
+  const int tile = blockIdx.z / a.n_src, which = blockIdx.z - tile * a.n_src;
   const int head = plane / a.T, t = plane - head * a.T;
   const uint32_t token = v >> a.vec_per_token_log2;
   const int cv = v & ((1u << a.vec_per_token_log2) - 1);
   const int i = token / (uint32_t)a.tw, j = token - i * a.tw;
-  int y = a.r0 + i; if (y >= a.H) y -= a.H;
-  int x = a.c0 + j; if (x >= a.W) x -= a.W;
+  int y = a.row[tile] * a.sh + a.shift_h; if (y >= a.H) y -= a.H;
+  int x = a.col[tile] * a.sw + a.shift_w; if (x >= a.W) x -= a.W;
+  y += i; if (y >= a.H) y -= a.H;
+  x += j; if (x >= a.W) x -= a.W;
   const int64_t n = ((int64_t)t * a.H + y) * a.W + x;
   const int64_t off_bytes = ((int64_t)head * a.stride_head + n * a.stride_token) * a.elem_bytes + (int64_t)cv * 16;
   const u32x4 val = __builtin_nontemporal_load((const u32x4*)((const char*)a.src[which] + off_bytes));
   const int64_t planes = (int64_t)a.heads * a.T;
-  __builtin_nontemporal_store(val, dst + ((int64_t)which * planes + plane) * a.tile_plane_vecs + v);
+  __builtin_nontemporal_store(val, (u32x4*)a.dst[tile] + ((int64_t)which * planes + plane) * a.tile_plane_vecs + v);
 }
 
 }  // namespace
@@ -271,22 +277,30 @@ int launch_blend(const sg_problem& p, const void* const* tile_out, void* grid_ou
   return SG_OK;
 }
 
-int launch_slice(const sg_problem& p, const void* const* src, int n_src, int tile_row, int tile_col, void* dst,
+// dst[i] <- the window of tiles[i] (row-major index) of every source
+int launch_slice(const sg_problem& p, const void* const* src, int n_src, const int* tiles, void* const* dst, int n_tiles,
                  hipStream_t s) {
   SliceArgs a;
   for (int i = 0; i < 3; ++i) a.src[i] = i < n_src ? src[i] : nullptr;
   a.n_src = n_src; a.T = p.T; a.H = p.H; a.W = p.W; a.th = p.tile_h; a.tw = p.tile_w; a.heads = p.heads;
-  a.r0 = (tile_row * p.stride_h + p.shift_h) % p.H;
-  a.c0 = (tile_col * p.stride_w + p.shift_w) % p.W;
+  a.sh = p.stride_h; a.sw = p.stride_w; a.shift_h = p.shift_h; a.shift_w = p.shift_w;
   a.elem_bytes = (p.dtype == SG_BF16) ? 2 : 4;
   const int vpt = p.head_dim * a.elem_bytes / 16;
   int lg = 0; while ((1 << lg) < vpt) ++lg;
   a.vec_per_token_log2 = lg;
   a.stride_token = p.grid_stride_token; a.stride_head = p.grid_stride_head;
   a.tile_plane_vecs = (uint32_t)((int64_t)p.tile_h * p.tile_w * vpt);
-  dim3 grid((a.tile_plane_vecs + kThreads - 1) / kThreads, p.heads * p.T, n_src);
-  slice_kernel<<<grid, kThreads, 0, s>>>(a, (u32x4*)dst);
-  SG_HIP_TRY(hipGetLastError());
+  for (int t0 = 0; t0 < n_tiles; t0 += kSliceTiles) {
+    const int n = n_tiles - t0 < kSliceTiles ? n_tiles - t0 : kSliceTiles;
+    for (int i = 0; i < kSliceTiles; ++i) {
+      a.dst[i] = i < n ? dst[t0 + i] : nullptr;
+      a.row[i] = i < n ? (int16_t)(tiles[t0 + i] / p.n_tile_cols) : 0;
+      a.col[i] = i < n ? (int16_t)(tiles[t0 + i] % p.n_tile_cols) : 0;
+    }
+    const dim3 grid((a.tile_plane_vecs + kThreads - 1) / kThreads, p.heads * p.T, n_src * n);
+    slice_kernel<<<grid, kThreads, 0, s>>>(a);
+    SG_HIP_TRY(hipGetLastError());
+  }
   return SG_OK;
 }
 

@@ -211,7 +211,8 @@ int sg_tile_slice(const sg_problem* p, const void* const* src, int32_t n_src, in
     if (!src[i] || !aligned16(src[i])) return SG_ERR_INVALID_ARG;
   if (tile_row < 0 || tile_row >= p->n_tile_rows || tile_col < 0 || tile_col >= p->n_tile_cols)
     return SG_ERR_INVALID_ARG;
-  return launch_slice(*p, src, n_src, tile_row, tile_col, dst, (hipStream_t)stream);
+  const int tile = tile_row * p->n_tile_cols + tile_col;
+  return launch_slice(*p, src, n_src, &tile, &dst, 1, (hipStream_t)stream);
 }
 
 int sg_cache_gate(const void* const* x_cur, const void* const* x_cached, const uint8_t* has_cache, int32_t n_tiles,
@@ -261,16 +262,17 @@ int sg_denoise_step_tiled(const sg_problem* p, const sg_step_io* io, void* strea
     } else {
       const int group = room < (size_t)n_tiles ? (int)room : n_tiles;
       const void* src[3] = {io->q, io->k, io->v};
-      const void* x[SG_MAX_TILES];
+      void* x[SG_MAX_TILES];
+      int tiles[SG_MAX_TILES];
+      for (int i = 0; i < n_tiles; ++i) {
+        tiles[i] = i;
+        x[i] = i < group ? (char*)io->workspace + (size_t)i * packed_bytes : nullptr;
+      }
       for (int t0 = 0; t0 < n_tiles; t0 += group) {
         const int n = n_tiles - t0 < group ? n_tiles - t0 : group;
-        for (int i = 0; i < n; ++i) {
-          char* dst = (char*)io->workspace + (size_t)i * packed_bytes;
-          st = launch_slice(*p, src, 3, (t0 + i) / p->n_tile_cols, (t0 + i) % p->n_tile_cols, dst, s);
-          if (st != SG_OK) return st;
-          x[i] = dst;
-        }
-        st = attention_packed_tiles(*p, x, n, io->cache_out + t0, nullptr, s);
+        st = launch_slice(*p, src, 3, tiles + t0, x, n, s);
+        if (st != SG_OK) return st;
+        st = attention_packed_tiles(*p, (const void* const*)x, n, io->cache_out + t0, nullptr, s);
         if (st != SG_OK) return st;
       }
     }
@@ -424,11 +426,10 @@ int sg_refine_step_canvas(const sg_problem* p, const void* q, const void* k, con
   st = refine_step_check(p, io, region, update);
   if (st != SG_OK) return st;
   const void* src[3] = {q, k, v};
-  for (int tr = 0; tr < p->n_tile_rows; ++tr)
-    for (int tc = 0; tc < p->n_tile_cols; ++tc) {
-      st = launch_slice(*p, src, 3, tr, tc, tile_x[tr * p->n_tile_cols + tc], (hipStream_t)stream);
-      if (st != SG_OK) return st;
-    }
+  int tiles[SG_MAX_TILES];
+  for (int i = 0; i < n_tiles; ++i) tiles[i] = i;
+  st = launch_slice(*p, src, 3, tiles, tile_x, n_tiles, (hipStream_t)stream);
+  if (st != SG_OK) return st;
   return refine_step(p, io, region, update, stream);
 }
 

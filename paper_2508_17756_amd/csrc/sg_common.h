@@ -50,7 +50,7 @@ int launch_attention_bf16(const TileView& tv, int heads, int head_dim, float sca
 int launch_attention_bf16_short(const TileView& tv, int heads, float scale, const AttnBatch& b, hipStream_t s);   // head_dim 64, windows
 int launch_blend(const sg_problem& p, const void* const* tile_out, void* grid_out, const void* latent, float c_latent,
                  float c_noise, hipStream_t s);
-int launch_slice(const sg_problem& p, const void* const* src, int n_src, int tile_row, int tile_col, void* dst,
+int launch_slice(const sg_problem& p, const void* const* src, int n_src, const int* tiles, void* const* dst, int n_tiles,
                  hipStream_t s);
 int launch_gate(const void* const* x_cur, const void* const* x_cached, const uint8_t* has_cache,
                 int n_tiles, int64_t elems, int dtype, float threshold, float* scores,

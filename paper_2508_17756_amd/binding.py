@@ -146,8 +146,21 @@ def load_library():
 
 
 # ------------------------------------------------------------------ marshalling helpers
+# A call costs the host as much as the device where tiles are small, so these take the shortest way: torch is looked up once, the
+# stream's handle comes without a Stream object, addresses go to ctypes as plain integers (the argument types convert them).
+_TORCH = None
+
+
+def _torch():
+    global _TORCH
+    if _TORCH is None:
+        import torch
+        _TORCH = torch
+    return _TORCH
+
+
 def _dtype_code(t):
-    import torch
+    torch = _torch()
     if t.dtype == torch.float32:
         return SG_F32
     if t.dtype == torch.bfloat16:
@@ -156,19 +169,20 @@ def _dtype_code(t):
 
 
 def _stream():
-    import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """hipStream_t of the current stream of the current device, as an integer."""
+    c = _torch()._C
+    if not _TORCH.cuda.is_initialized():
+        _TORCH.cuda.init()
+    return c._cuda_getCurrentRawStream(c._cuda_getDevice())
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else ctypes.c_void_p(0)
+    return t.data_ptr() if t is not None else None
 
 
 def _ptr_array(tensors):
-    arr = (ctypes.c_void_p * max(1, len(tensors)))()
-    for i, t in enumerate(tensors):
-        arr[i] = t.data_ptr()
-    return arr
+    n = len(tensors)
+    return (ctypes.c_void_p * (n or 1))(*[t.data_ptr() for t in tensors])
 
 
 def _check(status, where):

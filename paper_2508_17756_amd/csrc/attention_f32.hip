@@ -2,14 +2,14 @@
 // problems, on the fp32 matrix instruction (32x32x2: fp32 operands, fp32 accumulation, 64 FLOP per cycle and
 // SIMD; a large fp32 matrix product reaches 154 TFLOP/s on the same device).
 //
-// A workgroup owns QB x 32 query rows of one head and its 8 wavefronts split the keys (wavefront w takes the
-// 32-key blocks w, w + 8, ...), so that even one tile of a few hundred tokens gives every SIMD of its compute
+// A workgroup owns QB x 32 query rows of one head and its KS wavefronts split the keys (wavefront w takes the
+// 32-key blocks w, w + KS, ...), so that even one tile of a few hundred tokens gives every SIMD of its compute
 // units work, and no workgroup barrier stands in the key loop: every wavefront moves its own K blocks into
 // its own part of LDS (direct global->LDS transfers; K of the next block is requested when QK is done and has the
 // length of PV to arrive), reads its V rows straight into registers a few key pairs ahead, and keeps its own softmax
-// state; the 8 states of a query are merged through LDS at the end.  Two wavefronts per SIMD cover each other's softmax
+// state; the KS states of a query are merged through LDS at the end.  Two wavefronts per SIMD cover each other's softmax
 // and waits.  (One wavefront per SIMD with 64 queries and V in LDS as well, which halves what is read per FLOP, spills
-// its 512 registers around the rescaling of the accumulators: 2.14 ms where this takes 1.30.)
+// its 512 registers around the rescaling of the accumulators: 2.14 ms where this takes 1.20.)
 //
 // Transposed products, S^T = K Q^T and O^T = V^T P^T, keep the probabilities in their lanes: accumulator register r
 // of S^T holds, for the lane's query, key 8 (r >> 2) + (r & 3) in the lower and that key + 4 in the upper half of the
@@ -19,7 +19,7 @@
 //
 // Bound: matrix pipe (per 32 x 32 block and head_dim 128: 128 instructions of 64 cycles against 32 fragment reads
 // and 16 exponentials a lane).  Measured, before (vector ALU, keys and values broadcast from LDS) -> now, whole steps:
-// 4 tiles of 2,880 tokens, 8 heads x 128: 7.35 -> 1.30 ms (106 TFLOP/s in the kernel); 4 tiles of 300 tokens,
+// 4 tiles of 2,880 tokens, 8 heads x 128: 7.35 -> 1.20 ms (115 TFLOP/s in the kernel); 4 tiles of 300 tokens,
 // 2 heads x 64: 75.6 -> 17.6 us.
 #include <atomic>
 #include "attention_common.h"
@@ -36,16 +36,15 @@ constexpr float kLog2e = 1.4426950408889634f;
 // nothing in fp32, and the output accumulators are not rescaled for every new maximum.
 constexpr float kSlack = 8.0f;
 
-constexpr int KS = 8;          // wavefronts of a workgroup = shares of the keys: two per SIMD
-constexpr int kThreads = KS * 64;
 constexpr int kWaveBytes = 16384;   // LDS of a wavefront: its K block, after the key loop its partial output
-template <int QB>
+template <int QB, int KS>
 constexpr int kLds = KS * kWaveBytes + 2 * KS * QB * 32 * 4;   // and (reference, sum) per wavefront and query
 
 enum { kLinear = 0, kWindow = 1 };   // how a tile token is found
 
-template <int D, int QB, int MODE>
-__global__ __launch_bounds__(kThreads) void attention_f32_kernel(
+// KS wavefronts = shares of the keys; two wavefronts per SIMD either way: one workgroup of 8 per compute unit, or two of 4
+template <int D, int QB, int KS, int MODE>
+__global__ __launch_bounds__(64 * KS, 2) void attention_f32_kernel(
     const View16 vw, const float scale, const int heads, const int n_qblocks, const int n_tiles, const AttnTable tab,
     const uint8_t* __restrict__ run_flags) {
   static_assert(kKeys * D * 4 <= kWaveBytes && QB * 32 * D * 4 <= kWaveBytes, "K block and partial output");
@@ -273,7 +272,7 @@ __global__ __launch_bounds__(kThreads) void attention_f32_kernel(
   }
   __syncthreads();
   float* const out = (float*)tab.out[tile] + (size_t)head * N * D;
-  for (int e = threadIdx.x; e < QB * 32 * 32; e += kThreads) {   // (query, group of kPer channels), group fastest
+  for (int e = threadIdx.x; e < QB * 32 * 32; e += 64 * KS) {   // (query, group of kPer channels), group fastest
     const int q = e >> 5, m = e & 31;
     if (q0 + q >= N) break;   // queries rise with e
     float o[kPer];
@@ -299,7 +298,7 @@ int launch_attention_f32(const TileView& tv, int heads, int head_dim, float scal
   if (b.n_tiles <= 0) return SG_OK;
   const View16 vw = make_view16(tv);
   constexpr int kMaxDevices = 64;
-  static std::atomic<bool> attr_set[kMaxDevices][6];   // zero-initialised; set twice by racing threads is harmless
+  static std::atomic<bool> attr_set[kMaxDevices][12];   // zero-initialised; set twice by racing threads is harmless
   int dev = 0, n_cu = 0;
   SG_HIP_TRY(hipGetDevice(&dev));
   SG_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
@@ -318,28 +317,33 @@ int launch_attention_f32(const TileView& tv, int heads, int head_dim, float scal
       tab.refresh[i] = nullptr;   // the cache refresh is not carried by this kernel
     }
     const uint8_t* flags = b.run_flags ? b.run_flags + t0 : nullptr;
-    // One workgroup runs per compute unit at a time.  64 queries per workgroup (head_dim 64: the registers hold them) read
-    // K and V half as often as 32 but make half as many workgroups: taken where their rounds over the device are not longer.
+    // 64 queries per workgroup (head_dim 64: the registers hold them) read K and V half as often as 32 but make half as many
+    // workgroups: taken where their rounds over the device are not longer.  Then 4 shares of the keys, two workgroups per
+    // compute unit, where there are that many workgroups: one's start, end and uneven last blocks run beside the other's loop.
+    // Fewer workgroups take 8 shares, which halves the time of each.  (4 x 2,880 tokens, 8 heads x 128, 2,880 workgroups: 1.30 ms
+    // a step with 8 shares, 1.20 with 4.)
     const int64_t wg1 = (int64_t)n * heads * ((tv.N + 31) / 32), wg2 = (int64_t)n * heads * ((tv.N + 63) / 64);
     const bool wide = head_dim == 64 && 2 * ((wg2 + n_cu - 1) / n_cu) <= (wg1 + n_cu - 1) / n_cu;
     const int64_t total = wide ? wg2 : wg1;
+    const bool pairs = total >= 2 * n_cu;
     if (total > (1ll << 31) - 2 * kXcd) return SG_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)(((total + kXcd - 1) / kXcd) * kXcd));
     const int n_qblocks = (tv.N + (wide ? 63 : 31)) / (wide ? 64 : 32);
-    auto launch = [&](auto kern, int lds, int slot) -> int {
+    auto launch = [&](auto kern, int shares, int lds, int slot) -> int {
       if (dev < 0 || dev >= kMaxDevices || !attr_set[dev][slot].load(std::memory_order_acquire)) {
         SG_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
         if (dev >= 0 && dev < kMaxDevices) attr_set[dev][slot].store(true, std::memory_order_release);
       }
-      kern<<<grid, kThreads, lds, s>>>(vw, scale, heads, n_qblocks, n, tab, flags);
+      kern<<<grid, 64 * shares, lds, s>>>(vw, scale, heads, n_qblocks, n, tab, flags);
       return SG_OK;
     };
     int st;
-#define SG_F32_MODES(D, QB, SLOT)                                                   \
-  (tv.window ? launch(attention_f32_kernel<D, QB, kWindow>, kLds<QB>, SLOT)          \
-             : launch(attention_f32_kernel<D, QB, kLinear>, kLds<QB>, SLOT + 1))
-    if (head_dim == 128) st = SG_F32_MODES(128, 1, 0);
-    else st = wide ? SG_F32_MODES(64, 2, 2) : SG_F32_MODES(64, 1, 4);
+#define SG_F32_MODES(D, QB, KS, SLOT)                                                        \
+  (tv.window ? launch(attention_f32_kernel<D, QB, KS, kWindow>, KS, kLds<QB, KS>, SLOT)      \
+             : launch(attention_f32_kernel<D, QB, KS, kLinear>, KS, kLds<QB, KS>, SLOT + 1))
+    if (head_dim == 128) st = pairs ? SG_F32_MODES(128, 1, 4, 0) : SG_F32_MODES(128, 1, 8, 2);
+    else if (wide) st = pairs ? SG_F32_MODES(64, 2, 4, 4) : SG_F32_MODES(64, 2, 8, 6);
+    else st = pairs ? SG_F32_MODES(64, 1, 4, 8) : SG_F32_MODES(64, 1, 8, 10);
 #undef SG_F32_MODES
     if (st != SG_OK) return st;
     SG_HIP_TRY(hipGetLastError());

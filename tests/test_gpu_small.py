@@ -49,12 +49,14 @@ def test_attention_f32_key_split(th, tw):
     assert_close(to_f64(gpu_tile_attention(g, q, k, v, 0, 0)), oracle_tile_attention_full(g, q, k, v, 0, 0), "f32")
 
 
-@pytest.mark.parametrize("d,heads,th,tw", [(64, 9, 25, 40), (64, 9, 23, 43), (128, 3, 16, 17), (128, 1, 5, 51), (128, 1, 8, 32)])
+@pytest.mark.parametrize("d,heads,th,tw", [(64, 9, 25, 40), (64, 9, 23, 43), (128, 3, 16, 17), (128, 1, 5, 51), (128, 1, 8, 32),
+                                             (64, 32, 31, 33), (64, 32, 10, 103), (128, 16, 10, 103)])
 @pytest.mark.parametrize("view", [False, True], ids=["packed", "wrapped"])
 def test_attention_f32_growing_scores(d, heads, th, tw, view):
     """Scores that grow along the key axis, so that the softmax reference has to move past its slack in every share of the
     keys; 9 heads of about 1,000 tokens take 64 queries per workgroup (head_dim 64), the others 32; 255, 256, 272, 989 and
-    1,000 tokens end in partial and whole 32-key blocks.  The logits reach 12: their rounding, a few times 12 * 2^-24,
+    1,000 tokens end in partial and whole 32-key blocks; 16 and 32 heads of 1,023 and 1,030 tokens make enough workgroups for
+    four shares of the keys instead of eight, with 64 and with 32 queries each.  The logits reach 12: their rounding, a few times 12 * 2^-24,
     is the relative error of the probabilities (the bound below leaves a factor of three)."""
     g = _geom("f32g", 1, 2 * th, 2 * tw, th, tw, th, tw, heads, d, "f32", 900 + th) if view else _geom(
         "f32g", 1, th, tw, th, tw, th, tw, heads, d, "f32", 900 + th)

@@ -395,6 +395,22 @@ def test_step_cached_mode_bf16_three_steps(d):
 
 
 @pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("heads,N", [(1, 100), (2, 129), (25, 1124), (26, 1124), (40, 1030), (56, 1030), (52, 1281)])
+def test_attention_bf16_whole_and_halved_rounds(heads, N, d):
+    """Query blocks dealt whole and, in a last round that fills at most half of the compute units, as halves: 5 to 130 workgroups
+    (halved up to 128 on 256 compute units), 200 (whole), 280 and 312 (a whole round, and 24 / 56 halved), with last blocks of 1,
+    6 and 100 rows, so that second halves are empty; every row of the first, the middle and the last head."""
+    g = _geom("hv", 1, 1, N, 1, N, 1, N, heads, d, "bf16", 4000 + heads)
+    q, k, v = canvas_qkv(g)
+    out = torch.full(g.tile_shape, float("nan"), dtype=torch.bfloat16, device="cuda")
+    sg.sg_tile_attention(sg.make_problem(g), q, k, v, 0, 0, out)
+    assert torch.isfinite(out.float()).all()
+    for a in sorted({0, heads // 2, heads - 1}):
+        one = [to_f64(t[a]).reshape(N, d) for t in (q, k, v)]
+        assert_close(to_f64(out[a]).reshape(N, d), oracle.attention(*one, g.scale), "bf16", a)
+
+
+@pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("T,th,tw", [(1, 5, 8), (1, 1, 255), (1, 16, 16), (1, 1, 257), (3, 20, 25), (5, 13, 21), (9, 16, 17), (11, 16, 29)])
 def test_step_refreshes_the_cache_while_it_attends(T, th, tw, d):
     """The cache refresh that rides on the attention launch, bit for bit: one to twenty query blocks, whose stages lie in the

@@ -63,7 +63,7 @@ __device__ __forceinline__ void meet() {  // workgroup barrier that nothing is s
 // taken against).  M is an online-softmax running maximum that is refreshed lazily: as long as no
 // exponential of a stage exceeds 2^16 the reference stays, so the common path needs no row maximum, no
 // subtraction and no rescaling of the output accumulators; the result is the same softmax, since any
-// common reference cancels in sum(p v) / sum(p).
+// common reference cancels in sum(p v) / sum(p).  (Sums of p v stay finite for |v| below 2^111: p < 2^16.)
 // Score and probability arrays have this fixed extent for either head_dim (NB <= kMaxSB blocks are used):
 // their types then do not depend on a template parameter, which the register-pinning asm statements need.
 constexpr int kMaxSB = 4;

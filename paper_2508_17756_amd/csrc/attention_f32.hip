@@ -32,9 +32,10 @@ namespace {
 constexpr int kKeys = 32;    // keys per block
 constexpr int kXcd = 8;
 constexpr float kLog2e = 1.4426950408889634f;
-// The softmax reference moves only when a score exceeds it by this much (log2 domain): exponentials up to 2^8 lose
-// nothing in fp32, and the output accumulators are not rescaled for every new maximum.
-constexpr float kSlack = 8.0f;
+// The softmax reference moves only when a score exceeds it by this much: exponentials up to e^5 lose nothing in fp32, and the
+// output accumulators are not rescaled for every new maximum.  (It is subtracted before the factor log2(e) of the exponent, so
+// that scores up to the largest fp32 number stay finite.)
+constexpr float kSlack = 5.0f;
 
 constexpr int kWaveBytes = 16384;   // LDS of a wavefront: its K block, after the key loop its partial output
 template <int QB, int KS>
@@ -130,7 +131,7 @@ __global__ __launch_bounds__(64 * KS, 2) void attention_f32_kernel(
     for (int db = 0; db < kPer; ++db)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[qb][db][r] = 0.f;
-    ref[qb] = -__builtin_inff();   // log2 domain
+    ref[qb] = -__builtin_inff();
     l[qb] = 0.f;
   }
   uint32_t kaddr[8];   // chunk 2 c + half of row lq; bit 4 of the chunk is not swizzled: chunk 16 and on lie 256 bytes behind
@@ -198,10 +199,10 @@ __global__ __launch_bounds__(64 * KS, 2) void attention_f32_kernel(
       for (int r = 1; r < 16; ++r) mx = fmaxf(mx, p[qb][r]);
       const uint32_t mu = __float_as_uint(mx);
       const auto sw = __builtin_amdgcn_permlane32_swap(mu, mu, false, false);
-      mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * kLog2e;
+      mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
       if (__any(!(mx <= ref[qb] + kSlack))) {   // also the first block, where the reference is -inf
         const float moved = fmaxf(ref[qb], mx);
-        const float alpha = (ref[qb] == moved) ? 1.f : __builtin_amdgcn_exp2f(ref[qb] - moved);
+        const float alpha = (ref[qb] == moved) ? 1.f : __builtin_amdgcn_exp2f((ref[qb] - moved) * kLog2e);
         ref[qb] = moved;
         l[qb] *= alpha;
 #pragma unroll
@@ -209,7 +210,7 @@ __global__ __launch_bounds__(64 * KS, 2) void attention_f32_kernel(
       }
       float l0 = 0.f, l1 = 0.f;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) p[qb][r] = __builtin_amdgcn_exp2f(fmaf(p[qb][r], kLog2e, -ref[qb]));
+      for (int r = 0; r < 16; ++r) p[qb][r] = __builtin_amdgcn_exp2f((p[qb][r] - ref[qb]) * kLog2e);
 #pragma unroll
       for (int r = 0; r < 16; r += 2) { l0 += p[qb][r]; l1 += p[qb][r + 1]; }
       l[qb] += l0 + l1;
@@ -263,7 +264,7 @@ __global__ __launch_bounds__(64 * KS, 2) void attention_f32_kernel(
 #pragma unroll
     for (int w = 0; w < KS; ++w) {
       const float rw = s_ref[w * (QB * 32) + q];
-      wgt[w] = (rw == -__builtin_inff()) ? 0.f : __builtin_amdgcn_exp2f(rw - top);
+      wgt[w] = (rw == -__builtin_inff()) ? 0.f : __builtin_amdgcn_exp2f((rw - top) * kLog2e);
       sum += wgt[w] * s_sum[w * (QB * 32) + q];
     }
     const float inv = 1.0f / sum;

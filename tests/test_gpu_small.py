@@ -74,6 +74,19 @@ def test_attention_f32_growing_scores(d, heads, th, tw, view):
     assert errors(to_f64(out), ref)[1] <= 1e-5
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_attention_f32_scores_near_the_largest_number(d):
+    """One key whose scores reach 1e38: a query with a positive score attends to it alone, one with a negative score to the
+    others; nothing overflows (the logits of the others are of order one)."""
+    g = _geom("f32b", 1, 10, 20, 10, 20, 10, 20, 1, d, "f32", 61)
+    q, k, v = canvas_qkv(g)
+    k.view(-1, d)[77] = 0.0
+    k.view(-1, d)[77, 5] = 3e38
+    out = gpu_tile_attention(g, q, k, v, 0, 0)
+    assert torch.isfinite(out).all()
+    assert errors(to_f64(out), oracle_tile_attention_full(g, q, k, v, 0, 0))[1] <= 1e-5
+
+
 BF16_CASES = [
     # name, T, H, W, th, tw, sh, sw, heads: packed tiles (linear addressing) and canvas views
     ("packed_n576", 3, 12, 16, 12, 16, 12, 16, 2),      # 576 = 2*256 + 64, 9 full key blocks

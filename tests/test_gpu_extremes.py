@@ -1,0 +1,60 @@
+"""Attention at the ends of the value range: one dominating key, the largest finite values, infinities, NaN."""
+import math
+
+import pytest
+import torch
+
+import paper_2508_17756_amd as sg
+from synthetic import TileGeometry, torch_dtype
+
+pytestmark = pytest.mark.gpu
+
+LOG2E = math.log2(math.e)
+
+
+def _attend_window(dtype, d, heads, T, th, tw, q, k, v, shift=(0, 0), packed=False):
+    """Attention of tile (0, 0) of a canvas of 2 x 2 tiles (packed: of one), whose tokens are q, k, v [heads][N][d]."""
+    rows, cols = (1, 1) if packed else (2, 2)
+    g = TileGeometry("ends", T, rows * th, cols * tw, th, tw, th, tw, rows, cols, heads, d, dtype, 0)
+    canvases = []
+    for x in (q, k, v):
+        c = torch.zeros(g.grid_shape, dtype=torch_dtype(dtype))
+        c[:, :, :th, :tw] = x.reshape(heads, T, th, tw, d).to(c.dtype)
+        canvases.append(torch.roll(c, shift, dims=(2, 3)).cuda())
+    out = torch.empty(g.tile_shape, dtype=torch_dtype(dtype), device="cuda")
+    sg.sg_tile_attention(sg.make_problem(g, shift=shift), *canvases, 0, 0, out)
+    return out.cpu().reshape(heads, -1, d)
+
+
+def _dominated(d, n, key):
+    """Queries 0 .. n-1 whose score of `key` is 14 to 15.9 in the log2 domain, that of key 0 is 0 and the others' is below -40: the
+    softmax is 1 - 2^-14 or more at `key`, whatever the other keys hold."""
+    q, k = torch.zeros(1, n, d), torch.zeros(1, n, d)
+    step = 0.5                                             # bf16 holds these
+    first = math.ceil(14.0 * math.sqrt(d) / LOG2E / step)
+    last = math.floor(15.9 * math.sqrt(d) / LOG2E / step)
+    q[0, :, 0] = step * (first + torch.arange(n) % (last - first + 1))
+    q[0, :, 1] = 255.0
+    k[0, :, 1] = -1.0 * math.sqrt(d / 64)
+    k[0, 0] = 0.0
+    k[0, key] = 0.0
+    k[0, key, 0] = 1.0
+    return q, k
+
+
+@pytest.mark.parametrize("shift", [(0, 0), (7, 13)], ids=["fixed", "wrapped"])
+@pytest.mark.parametrize("T,th,tw,key", [(1, 15, 20, 299), (2, 10, 21, 200), (2, 10, 21, 419), (5, 20, 25, 1300)])
+def test_head_dim_64_windows_hold_the_dominating_probability_exactly(T, th, tw, key, shift):
+    """The probability of a dominating key far above the first stage's maximum is 1: its output is its value, rounded to bf16 once
+    (half a unit in the last place, 2^-9 below 1, and the 2^-14 of key 0).  A probability that is itself rounded to bf16 would add
+    up to as much again.  For the same reason the largest finite value comes back finite.  300 tokens take the short kernel."""
+    n = T * th * tw
+    q, k = _dominated(64, n, key)
+    v = torch.zeros(1, n, 64)
+    v[0, key] = torch.where(torch.arange(64) % 2 == 0, 1.0, 3e38)
+    got = _attend_window("bf16", 64, 1, T, th, tw, q, k, v, shift).double()[0]
+    p = torch.softmax((q[0].double() @ k[0].double().T) / 8.0, dim=1)[:, key]
+    assert float((got[:, 0::2] - p[:, None]).abs().max()) <= 2 ** -9
+    assert bool(torch.isfinite(got).all())
+    big = float(torch.tensor(3e38).bfloat16())
+    assert float((got[:, 1::2] / big - p[:, None]).abs().max()) <= 2 ** -8     # one bf16 unit: 3e38 is rounded as well

@@ -574,9 +574,23 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
     else if (younger_stages == 1) wait_vmcnt<4>();
     else wait_vmcnt<0>();
   };
+  // Keys at or beyond N stand in for the last one with probability 0; their value rows are cleared, so that an infinite last value
+  // does not become 0 * inf (late scaling only: with 64 keys a stage such rows were rarer than with 128).
+  auto clear_tail = [&]() SG_INLINE {
+    const int last = n_blocks - 1;
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      uint32_t c;
+      if (last * kKeys + kTok * wave + slot_token(lane, u, true, c) >= N)
+        *(SG_LDS u32x4*)(uintptr_t)(dma_dst + (last % kStages) * kTileBytes + kVRegion + u * (4 * kRowBytes) + lane * 16) = u32x4{0, 0, 0, 0};
+    }
+  };
   // end of iteration k: the stage issued last but one has landed.  Behind its transfers stand those of the last stage and the
   // four stores of every stage copied in this iteration and the one before (whole stages: none of them is skipped).
-  auto wait_iteration = [&](int k, bool issued) SG_INLINE { wait_stage(issued ? 1 + copies(k) + copies(k - 1) : 0); };
+  auto wait_iteration = [&](int k, bool issued) SG_INLINE {
+    wait_stage(issued ? 1 + copies(k) + copies(k - 1) : 0);
+    if (kLate && tail && k == n_blocks - 2) clear_tail();
+  };
   bf16x8 p[2 * kMaxSB];   // the first 2 kSB entries
   // keeps the score registers live across the phase boundary (a macro: the statement has to sit in the
   // lambdas that are its call sites)
@@ -617,6 +631,7 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
   for (int b = 1; b < 3; ++b)
     if (b < n_blocks) issue_any(b, b);
   wait_stage(n_blocks >= 3 ? 2 : (n_blocks == 2 ? 1 : 0));
+  if (kLate && tail && n_blocks == 1) clear_tail();
   meet();
   if (__builtin_expect(q0 >= N, 0)) {   // a wavefront without a query (the last query block) moves its share of the stages and leaves the matrix
                    // pipe and the vector ALU to the other wavefront of its SIMD

@@ -58,3 +58,22 @@ def test_head_dim_64_windows_hold_the_dominating_probability_exactly(T, th, tw, 
     assert bool(torch.isfinite(got).all())
     big = float(torch.tensor(3e38).bfloat16())
     assert float((got[:, 1::2] / big - p[:, None]).abs().max()) <= 2 ** -8     # one bf16 unit: 3e38 is rounded as well
+
+
+def _infinite_last_value(dtype, d, heads, T, th, tw, **where):
+    n = T * th * tw
+    gen = torch.Generator().manual_seed(n + d)
+    q, k, v = (torch.randn(heads, n, d, generator=gen) for _ in range(3))
+    v[:, n - 1, 3] = math.inf
+    got = _attend_window(dtype, d, heads, T, th, tw, q, k, v, **where)
+    assert bool((got[:, :, 3] == math.inf).all())
+    got[:, :, 3] = 0.0
+    assert bool(torch.isfinite(got).all())
+
+
+@pytest.mark.parametrize("shift", [(0, 0), (7, 13)], ids=["fixed", "wrapped"])
+@pytest.mark.parametrize("T,th,tw", [(1, 16, 28), (1, 20, 23), (1, 16, 32), (2, 17, 40), (5, 20, 25)])
+def test_head_dim_64_windows_take_an_infinite_last_value(T, th, tw, shift):
+    """448, 460, 512, 1,360, 2,500 tokens: the keys that fill up the last stage stand in for the last one and must not turn its
+    infinity into 0 * inf."""
+    _infinite_last_value("bf16", 64, 2, T, th, tw, shift=shift)

@@ -20,7 +20,7 @@
 // A SIMD overlaps MFMA and vector work only across wavefronts, never inside one, so the two
 // wavefronts of each SIMD run half an iteration apart (see "Schedule" in the kernel).
 //
-// Built with -fno-honor-nans: a NaN in Q, K or V gives unspecified (not necessarily NaN) output.
+// A NaN in Q, K or V reaches every output that depends on it: maxima pass it by, exponentials and sums carry it.
 #include <type_traits>
 #include <atomic>
 #include "attention_common.h"

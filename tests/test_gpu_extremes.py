@@ -77,3 +77,26 @@ def test_head_dim_64_windows_take_an_infinite_last_value(T, th, tw, shift):
     """448, 460, 512, 1,360, 2,500 tokens: the keys that fill up the last stage stand in for the last one and must not turn its
     infinity into 0 * inf."""
     _infinite_last_value("bf16", 64, 2, T, th, tw, shift=shift)
+
+
+@pytest.mark.parametrize("dtype,d,packed,shape", [("bf16", 64, False, (1, 15, 20)), ("bf16", 64, False, (3, 20, 23)), ("bf16", 64, True, (3, 20, 23)),
+                                                  ("bf16", 128, False, (3, 20, 24)), ("bf16", 128, False, (3, 20, 23)),
+                                                  ("bf16", 128, True, (3, 20, 23)), ("f32", 64, False, (3, 20, 23)), ("f32", 128, True, (3, 20, 23))])
+@pytest.mark.parametrize("where,token", [("q", 77), ("k", 0), ("k", 299), ("v", 5), ("v", 260)])
+def test_nan_reaches_what_depends_on_it_and_nothing_else(dtype, d, packed, shape, where, token):
+    """A NaN in a query reaches that query's output, one in a key every output, one in a value its channel of every output; in the
+    first stage of keys, where the softmax reference is set, and behind it.  Every kernel."""
+    T, th, tw = shape
+    n = T * th * tw
+    gen = torch.Generator().manual_seed(n + d)
+    x = {name: torch.randn(2, n, d, generator=gen) for name in "qkv"}
+    x[where][1, token, 9] = math.nan
+    got = _attend_window(dtype, d, 2, T, th, tw, x["q"], x["k"], x["v"], packed=packed).isnan()
+    want = torch.zeros(2, n, d, dtype=torch.bool)
+    if where == "q":
+        want[1, token] = True
+    elif where == "k":
+        want[1] = True
+    else:
+        want[1, :, 9] = True
+    assert torch.equal(got, want)

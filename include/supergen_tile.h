@@ -111,7 +111,8 @@ int sg_workspace_bytes(int32_t n_tiles, size_t* out_bytes);
  * problem (the score then leaves the matrix cores as the exponent): one extra bf16 rounding of the
  * scores' left factor on top of "multiply in bf16, accumulate in fp32".  Its softmax reference is refreshed lazily:
  * outputs stay finite for |V| below 2^111.  Tiles of head_dim 64 that are read in place from a larger canvas (or under a shifted
- * partition) are scaled in fp32 behind the product instead, against the true running maximum, and take any finite V.
+ * partition), and those of head_dim 128 whose head spans 4 GiB or more and whose window wraps or is no multiple of 8 tokens wide,
+ * are scaled in fp32 behind the product instead, against the true running maximum, and take any finite V.
  */
 int sg_tile_attention(const sg_problem* p, const void* q, const void* k, const void* v,
                       int32_t tile_row, int32_t tile_col, void* out_tile, void* stream);

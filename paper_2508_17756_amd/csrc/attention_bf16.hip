@@ -64,7 +64,7 @@ __device__ __forceinline__ void meet() {  // workgroup barrier that nothing is s
 // exponential of a stage exceeds 2^16 the reference stays, so the common path needs no row maximum, no
 // subtraction and no rescaling of the output accumulators; the result is the same softmax, since any
 // common reference cancels in sum(p v) / sum(p).  (Sums of p v stay finite for |v| below 2^111: p < 2^16.)
-// Windows of head_dim 64 keep Q as stored, scale behind the product and take M as the true running maximum (see softmax_phase).
+// LATE kernels keep Q as stored, scale behind the product and take M as the true running maximum (see late_half).
 // Score and probability arrays have this fixed extent for either head_dim (NB <= kMaxSB blocks are used):
 // their types then do not depend on a template parameter, which the register-pinning asm statements need.
 constexpr int kMaxSB = 4;
@@ -142,9 +142,11 @@ constexpr float kOverflowGuard = 65536.0f;   // a stage's exponentials may grow 
 
 enum { kLinear = 0, kWindow = 1 };   // packed tile, or window of a canvas (see the DMA loader)
 
+// LATE: Q is multiplied as stored and the scores by log2(e) * scale in fp32, against the true running maximum; the other forms scale
+// Q first and keep a lazy reference.
 // REFRESH: the launch also refreshes the cache of the tiles it attends (packed tiles: refresh <- the tile's Q, K, V,
 // has_cache <- 1).
-template <int D, int MODE, bool REFRESH>
+template <int D, int MODE, bool LATE, bool REFRESH>
 __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 vw, const float c_log2, const int heads,
                                                                   const int n_qblocks, const int n_tiles, const int cu_per_xcd,
                                                                   const AttnTable tab, const uint8_t* __restrict__ run_flags,
@@ -157,9 +159,6 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
   // fragments with accumulators differs (see qk and pv).
   constexpr int kSB = (D == 128) ? 2 : 4;   // 32-key score blocks per stage
   constexpr int kKeys = 32 * kSB;           // keys per stage
-  // Windows of head_dim 64 keep Q as stored and multiply the scores by log2(e) * scale in fp32, against the true running maximum;
-  // the other forms scale Q first and keep a lazy reference.
-  constexpr bool kLate = (D == 64 && MODE == kWindow);
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
   SG_LDS uint8_t* const lds = (SG_LDS uint8_t*)smem;
   const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
@@ -394,7 +393,7 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
 #pragma unroll
     for (int kk = 0; kk < D / 16; ++kk) {
       const u32x4 raw = src[2 * kk + half];
-      if (kLate) { qf[kk] = __builtin_bit_cast(bf16x8, raw); continue; }
+      if (LATE) { qf[kk] = __builtin_bit_cast(bf16x8, raw); continue; }
       u32x4 scaled;   // q * log2(e) * scale, rounded to bf16 once
 #pragma unroll
       for (int e = 0; e < 4; ++e)
@@ -409,7 +408,7 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
 #pragma unroll
     for (int r = 0; r < 16; ++r) oacc[db][r] = 0.f;
   Softmax sm;
-  sm.M = kLate ? -__builtin_inff() : 0.f;
+  sm.M = LATE ? -__builtin_inff() : 0.f;
   sm.l = 0.f;
   f32x16 cinit;   // accumulator start of every score chain: -M in all registers
 #pragma unroll
@@ -452,8 +451,8 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
       const int b1 = b0 + kSB / 2;
       const int qi = kk % kPerChain;
       if (qi == 0) {
-        s[b0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk][0], qf[qi], kLate ? zero16() : cinit, 0, 0, 0);
-        s[b1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk][1], qf[qi], kLate ? zero16() : cinit, 0, 0, 0);
+        s[b0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk][0], qf[qi], LATE ? zero16() : cinit, 0, 0, 0);
+        s[b1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk][1], qf[qi], LATE ? zero16() : cinit, 0, 0, 0);
       } else {
         s[b0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk][0], qf[qi], s[b0], 0, 0, 0);
         s[b1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kk][1], qf[qi], s[b1], 0, 0, 0);
@@ -472,7 +471,7 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
     for (int i = 0; i < 2 * kPF; ++i) a[i] = vfrag(i >> 2, i & 3, off);
 #pragma unroll
     for (int i = 0; i < 16; i += 2) {
-      if (kLate && kSB == 4 && i == 8 && __any(mid != 1.f)) {   // the keys behind raised the maximum
+      if (LATE && kSB == 4 && i == 8 && __any(mid != 1.f)) {   // the keys behind raised the maximum
 #pragma unroll
         for (int db = 0; db < D / 32; ++db) oacc[db] *= mid;
       }
@@ -521,7 +520,7 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
   // reference moves by delta per query: scores, running sum and output accumulators are brought to the new
   // reference and the exponentials are retaken.  One copy of the code, looped at most twice.
   auto softmax_phase = [&](int key0, bool masked, bool first, bf16x8 (&p)[2 * kMaxSB]) SG_INLINE {
-    if constexpr (kLate) {
+    if constexpr (LATE) {
       if (masked) mask_tail<kSB>(s, key0, N);
       late_half(std::integral_constant<int, 0>{}, p);
       if constexpr (kSB == 4) late_half(std::integral_constant<int, 1>{}, p);
@@ -589,7 +588,7 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
   // four stores of every stage copied in this iteration and the one before (whole stages: none of them is skipped).
   auto wait_iteration = [&](int k, bool issued) SG_INLINE {
     wait_stage(issued ? 1 + copies(k) + copies(k - 1) : 0);
-    if (kLate && tail && k == n_blocks - 2) clear_tail();
+    if (LATE && tail && k == n_blocks - 2) clear_tail();
   };
   bf16x8 p[2 * kMaxSB];   // the first 2 kSB entries
   // keeps the score registers live across the phase boundary (a macro: the statement has to sit in the
@@ -621,7 +620,7 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
   auto softmax_pinned = [&](int j, bool masked, bool first) SG_INLINE {
     softmax_phase(j * kKeys, masked, first, p);
     asm volatile("" : : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[3]), "v"(sm.l));
-    if constexpr (!kLate) asm volatile("" : : "v"(cinit));
+    if constexpr (!LATE) asm volatile("" : : "v"(cinit));
     if constexpr (kSB == 4) asm volatile("" : : "v"(p[kSB]), "v"(p[kSB + 1]), "v"(p[kSB + 2]), "v"(p[kSB + 3]));
     __builtin_amdgcn_sched_barrier(0);
   };
@@ -631,7 +630,7 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
   for (int b = 1; b < 3; ++b)
     if (b < n_blocks) issue_any(b, b);
   wait_stage(n_blocks >= 3 ? 2 : (n_blocks == 2 ? 1 : 0));
-  if (kLate && tail && n_blocks == 1) clear_tail();
+  if (LATE && tail && n_blocks == 1) clear_tail();
   meet();
   if (__builtin_expect(q0 >= N, 0)) {   // a wavefront without a query (the last query block) moves its share of the stages and leaves the matrix
                    // pipe and the vector ALU to the other wavefront of its SIMD
@@ -779,13 +778,18 @@ int launch_attention_bf16(const TileView& tv, int heads, int head_dim, float sca
   // three stages of 128 keys and fewer do not fill the pipeline: measured in attention_bf16_short.hip
   if (head_dim == 64 && tv.window && tv.N <= 384) return launch_attention_bf16_short(tv, heads, scale, b, s);
   const View16 vw = make_view16(tv);
+  // Windows of head_dim 64 and windows whose offsets inside a head leave 32 bits are scaled late: these calls have always had the
+  // smaller error (2.2e-3 against fp64, scaled first 2.9e-3).
+  bool wraps = false;
+  for (int i = 0; i < b.n_tiles && tv.window; ++i) wraps = wraps || b.y0[i] + tv.th > tv.H || b.x0[i] + tv.tw > tv.W;
+  const bool late = head_dim == 64 || (!(vw.reach & kReachHead) && (wraps || tv.tw % 8 != 0));
   // a packed tile whose tokens are so far apart that 16 of them span 4 GiB is read like a window (of itself)
   const bool window = tv.window || !(vw.reach & kReachLane);
   const int n_qblocks = (tv.N + kBR - 1) / kBR;
   const float c_log2 = scale * 1.4426950408889634f;
   // the kernels need more dynamic LDS than the default limit; the attribute is set once per device and kernel
   constexpr int kMaxDevices = 64;
-  static std::atomic<bool> attr_set[kMaxDevices][6];   // zero-initialised; set twice by racing threads is harmless
+  static std::atomic<bool> attr_set[kMaxDevices][7];   // zero-initialised; set twice by racing threads is harmless
   int dev = 0, n_cu = 0;
   SG_HIP_TRY(hipGetDevice(&dev));
   SG_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
@@ -821,11 +825,12 @@ int launch_attention_bf16(const TileView& tv, int heads, int head_dim, float sca
     };
     int st = SG_OK;
     if (head_dim == 64)
-      st = window ? launch(attention_bf16_kernel<64, kWindow, false>, 0)
-           : fuse_refresh ? launch(attention_bf16_kernel<64, kLinear, true>, 1) : launch(attention_bf16_kernel<64, kLinear, false>, 2);
+      st = window ? launch(attention_bf16_kernel<64, kWindow, true, false>, 0)
+           : fuse_refresh ? launch(attention_bf16_kernel<64, kLinear, false, true>, 1) : launch(attention_bf16_kernel<64, kLinear, false, false>, 2);
+    else if (window)
+      st = late ? launch(attention_bf16_kernel<128, kWindow, true, false>, 3) : launch(attention_bf16_kernel<128, kWindow, false, false>, 4);
     else
-      st = window ? launch(attention_bf16_kernel<128, kWindow, false>, 3)
-           : fuse_refresh ? launch(attention_bf16_kernel<128, kLinear, true>, 4) : launch(attention_bf16_kernel<128, kLinear, false>, 5);
+      st = fuse_refresh ? launch(attention_bf16_kernel<128, kLinear, false, true>, 5) : launch(attention_bf16_kernel<128, kLinear, false, false>, 6);
     if (st != SG_OK) return st;
     SG_HIP_TRY(hipGetLastError());
   }

@@ -12,17 +12,27 @@ pytestmark = pytest.mark.gpu
 LOG2E = math.log2(math.e)
 
 
-def _attend_window(dtype, d, heads, T, th, tw, q, k, v, shift=(0, 0), packed=False):
-    """Attention of tile (0, 0) of a canvas of 2 x 2 tiles (packed: of one), whose tokens are q, k, v [heads][N][d]."""
+def _attend_window(dtype, d, heads, T, th, tw, q, k, v, wrapped=False, packed=False, token_stride=0):
+    """Attention of tile (0, 0) of a canvas of 2 x 2 tiles (packed: of one), whose tokens are q, k, v [heads][N][d]; wrapped:
+    shifted so far that the window crosses both canvas edges.  With a token stride (one head) the three canvases lie in one
+    buffer of tokens that far apart, side by side in every token."""
     rows, cols = (1, 1) if packed else (2, 2)
     g = TileGeometry("ends", T, rows * th, cols * tw, th, tw, th, tw, rows, cols, heads, d, dtype, 0)
+    shift = (2 * th - 3, 2 * tw - 5) if wrapped else (0, 0)
     canvases = []
     for x in (q, k, v):
         c = torch.zeros(g.grid_shape, dtype=torch_dtype(dtype))
         c[:, :, :th, :tw] = x.reshape(heads, T, th, tw, d).to(c.dtype)
         canvases.append(torch.roll(c, shift, dims=(2, 3)).cuda())
     out = torch.empty(g.tile_shape, dtype=torch_dtype(dtype), device="cuda")
-    sg.sg_tile_attention(sg.make_problem(g, shift=shift), *canvases, 0, 0, out)
+    p = sg.make_problem(g, shift=shift)
+    if token_stride:
+        buf = torch.empty(g.grid_tokens * token_stride, dtype=out.dtype, device="cuda")
+        p.grid_stride_token, p.grid_stride_head = token_stride, d
+        for i, c in enumerate(canvases):
+            canvases[i] = buf[i * d:]
+            canvases[i].as_strided((g.grid_tokens, d), (token_stride, 1)).copy_(c.reshape(g.grid_tokens, d))
+    sg.sg_tile_attention(p, *canvases, 0, 0, out)
     return out.cpu().reshape(heads, -1, d)
 
 
@@ -42,22 +52,32 @@ def _dominated(d, n, key):
     return q, k
 
 
-@pytest.mark.parametrize("shift", [(0, 0), (7, 13)], ids=["fixed", "wrapped"])
-@pytest.mark.parametrize("T,th,tw,key", [(1, 15, 20, 299), (2, 10, 21, 200), (2, 10, 21, 419), (5, 20, 25, 1300)])
-def test_head_dim_64_windows_hold_the_dominating_probability_exactly(T, th, tw, key, shift):
-    """The probability of a dominating key far above the first stage's maximum is 1: its output is its value, rounded to bf16 once
-    (half a unit in the last place, 2^-9 below 1, and the 2^-14 of key 0).  A probability that is itself rounded to bf16 would add
-    up to as much again.  For the same reason the largest finite value comes back finite.  300 tokens take the short kernel."""
+def _check_dominated(d, T, th, tw, key, **where):
     n = T * th * tw
-    q, k = _dominated(64, n, key)
-    v = torch.zeros(1, n, 64)
-    v[0, key] = torch.where(torch.arange(64) % 2 == 0, 1.0, 3e38)
-    got = _attend_window("bf16", 64, 1, T, th, tw, q, k, v, shift).double()[0]
-    p = torch.softmax((q[0].double() @ k[0].double().T) / 8.0, dim=1)[:, key]
+    q, k = _dominated(d, n, key)
+    v = torch.zeros(1, n, d)
+    v[0, key] = torch.where(torch.arange(d) % 2 == 0, 1.0, 3e38)
+    got = _attend_window("bf16", d, 1, T, th, tw, q, k, v, **where).double()[0]
+    p = torch.softmax((q[0].double() @ k[0].double().T) / math.sqrt(d), dim=1)[:, key]
     assert float((got[:, 0::2] - p[:, None]).abs().max()) <= 2 ** -9
     assert bool(torch.isfinite(got).all())
     big = float(torch.tensor(3e38).bfloat16())
     assert float((got[:, 1::2] / big - p[:, None]).abs().max()) <= 2 ** -8     # one bf16 unit: 3e38 is rounded as well
+
+
+@pytest.mark.parametrize("wrapped", [False, True], ids=["fixed", "wrapped"])
+@pytest.mark.parametrize("T,th,tw,key", [(1, 15, 20, 299), (2, 10, 21, 200), (2, 10, 21, 419), (5, 20, 25, 1300)])
+def test_head_dim_64_windows_hold_the_dominating_probability_exactly(T, th, tw, key, wrapped):
+    """The probability of a dominating key far above the first stage's maximum is 1: its output is its value, rounded to bf16 once
+    (half a unit in the last place, 2^-9 below 1, and the 2^-14 of key 0).  A probability that is itself rounded to bf16 would add
+    up to as much again.  For the same reason the largest finite value comes back finite.  300 tokens take the short kernel."""
+    _check_dominated(64, T, th, tw, key, wrapped=wrapped)
+
+
+@pytest.mark.parametrize("tw,wrapped", [(21, False), (21, True), (24, True)], ids=["w21", "w21_wrapped", "w24_wrapped"])
+def test_windows_of_heads_beyond_4_gib_hold_the_dominating_probability_exactly(tw, wrapped):
+    """The same of head_dim 128 where a head spans 4 GiB or more and the window wraps or is no multiple of 8 tokens wide."""
+    _check_dominated(128, 2, 10, tw, 2 * 10 * tw - 1, wrapped=wrapped, token_stride=1 << 21)
 
 
 def _infinite_last_value(dtype, d, heads, T, th, tw, **where):
@@ -71,12 +91,12 @@ def _infinite_last_value(dtype, d, heads, T, th, tw, **where):
     assert bool(torch.isfinite(got).all())
 
 
-@pytest.mark.parametrize("shift", [(0, 0), (7, 13)], ids=["fixed", "wrapped"])
+@pytest.mark.parametrize("wrapped", [False, True], ids=["fixed", "wrapped"])
 @pytest.mark.parametrize("T,th,tw", [(1, 16, 28), (1, 20, 23), (1, 16, 32), (2, 17, 40), (5, 20, 25)])
-def test_head_dim_64_windows_take_an_infinite_last_value(T, th, tw, shift):
+def test_head_dim_64_windows_take_an_infinite_last_value(T, th, tw, wrapped):
     """448, 460, 512, 1,360, 2,500 tokens: the keys that fill up the last stage stand in for the last one and must not turn its
     infinity into 0 * inf."""
-    _infinite_last_value("bf16", 64, 2, T, th, tw, shift=shift)
+    _infinite_last_value("bf16", 64, 2, T, th, tw, wrapped=wrapped)
 
 
 @pytest.mark.parametrize("dtype,d,packed,shape", [("bf16", 64, False, (1, 15, 20)), ("bf16", 64, False, (3, 20, 23)), ("bf16", 64, True, (3, 20, 23)),

@@ -140,7 +140,8 @@ __device__ __forceinline__ f32x16 zero16() {
 }
 constexpr float kOverflowGuard = 65536.0f;   // a stage's exponentials may grow to 2^16 before the reference moves
 
-enum { kLinear = 0, kWindow = 1 };   // packed tile, or window of a canvas (see the DMA loader)
+// Packed tile; window of a canvas; window that does not cross a canvas edge and whose width is a multiple of 8 (see the DMA loader).
+enum { kLinear = 0, kWindow = 1, kWalk = 2 };
 
 // LATE: Q is multiplied as stored and the scores by log2(e) * scale in fp32, against the true running maximum; the other forms scale
 // Q first and keep a lazy reference.
@@ -153,6 +154,7 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
                                                                   uint8_t* __restrict__ has_cache) {
   static_assert(D == 128 || D == 64, "head_dim 64 or 128");
   static_assert(!REFRESH || MODE == kLinear, "a packed tile's input is refreshed");
+  static_assert(MODE != kWalk || (D == 128 && !LATE), "head_dim 64 and late scaling: packed tiles and planned windows");
   // LDS rows ("slots") are always 256 bytes.  With head_dim 128 a slot is one key and a stage 64 keys; with
   // head_dim 64 a stage is 128 keys and slot s holds the keys 2 s and 2 s + 1, neighbours in a tile row, so the
   // transfers, the fragment reads and the MFMA count per stage are the same and only the pairing of
@@ -189,7 +191,7 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
   const u32x4* const kg = (const u32x4*)tab.k[tile];
   const u32x4* const vg = (const u32x4*)tab.v[tile];
   uint16_t* const out = (uint16_t*)tab.out[tile];
-  const int wy0 = (MODE == kWindow) ? tab.y0[tile] : 0, wx0 = (MODE == kWindow) ? tab.x0[tile] : 0;
+  const int wy0 = (MODE != kLinear) ? tab.y0[tile] : 0, wx0 = (MODE != kLinear) ? tab.x0[tile] : 0;
   // offset of tile token n from the head's first element, in 16-byte units
   auto token_off16 = [&](int n) SG_INLINE -> uint32_t {
     return (MODE == kLinear) ? (uint32_t)n * vw.st16 : window_token(vw, n, wy0, wx0).off16;
@@ -224,13 +226,15 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
   //
   // A wavefront's slots are a run of kTok consecutive tokens.  Where they lie side by side in memory - always in a packed
   // tile - the address is a wave-uniform 64-bit pointer plus a per-lane byte offset that never changes, and the transfer
-  // spends no vector instructions on addressing.  In a window a run is broken where a tile row ends and where the row crosses
-  // the canvas edge, at most once each if the tile is at least kTok wide; such a run adds the two jumps to the lanes behind them.
-  // Where the runs start and break is worked out for 64 stages at a time, one lane per stage, and read back lane by lane: on
-  // the scalar unit the same arithmetic costs 2 % of the loop before the transfers of a stage and 5 % between its MFMAs.
-  // Measured on 3 x 3 tiles of 11,520 tokens, 40 heads x 128: 18.46 ms a step, 18.50 under a shift that makes windows wrap,
-  // 17.87 packed (19.1 shifted when every lane formed its token's offset from wrapped coordinates each stage); on 2 x 2 shifted
-  // tiles of 17,550 tokens, 48 heads x 64: 18.5 ms (22.3 with register-staged loads).
+  // spends no vector instructions on addressing.  The runs of an unbroken window of a width that is a multiple of kTok lie side by
+  // side too: kWalk moves that pointer over the tile rows on the scalar unit.  In any other window a run is broken where a tile row
+  // ends and where the row crosses the canvas edge, at most once each if the tile is at least kTok wide; such a run adds the two
+  // jumps to the lanes behind them.  Where the runs start and break is worked out for 64 stages at a time, one lane per stage, and
+  // read back lane by lane: on the scalar unit the same arithmetic costs 2 % of the loop before the transfers of a stage and 5 %
+  // between its MFMAs.
+  // Measured on 4 x 5 tiles of 75,600 tokens, 40 heads x 128: 1,744 ms a step walked, 1,764 under a shift that makes windows wrap
+  // and so planned (1,792 when every lane formed its token's offset from wrapped coordinates each stage), 1,731 gathered and packed;
+  // on 2 x 2 shifted tiles of 17,550 tokens, 48 heads x 64: 18.5 ms (22.3 with register-staged loads).
   constexpr int kTok = kKeys / kWaves;   // tokens per wavefront and stage: 8 (head_dim 64: 16)
   auto slot_token = [&](int l, int u, bool is_v, uint32_t& chunk) SG_INLINE -> int {   // what lane l moves: token of the run, chunk of it
     const int slot_w = 4 * u + (l >> 4), row = 8 * wave + slot_w;
@@ -301,10 +305,46 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
       dma16(vp, vlane[u], dst + kVRegion + u * (4 * kRowBytes));
     }
   };
-  // packed tiles: pointers to the run of the stage to issue
+  // packed tiles and walked windows: pointers to the run of the stage to issue; a walk also knows its tile row and column
+  uint32_t run16 = (uint32_t)(kTok * wave) * vw.st16;
+  int32_t walk_i = 0, walk_j = 0;
+  if (MODE == kWalk) {   // (a run at or beyond N is looked up instead)
+    const int t = (int)divide((uint32_t)(kTok * wave), vw.by_plane), in_plane = kTok * wave - t * (vw.th * vw.tw);
+    walk_i = (int)divide((uint32_t)in_plane, vw.by_row);
+    walk_j = in_plane - walk_i * vw.tw;
+    run16 = (uint32_t)((t * vw.H + wy0 + walk_i) * vw.W + wx0 + walk_j) * vw.st16;
+  }
+  const char* kcur = (const char*)kh + ((uint64_t)run16 << 4);
+  const char* vcur = (const char*)vh + ((uint64_t)run16 << 4);
   const uint64_t stage_bytes = (uint64_t)(kKeys * 16) * vw.st16;
-  const char* kcur = (const char*)kh + (uint64_t)(kTok * wave * 16) * vw.st16;
-  const char* vcur = (const char*)vh + (uint64_t)(kTok * wave * 16) * vw.st16;
+  // in units of 16 bytes, which keeps the scalar registers few: from a tile row's end to the next row, and, behind the last row, on
+  // to the next frame
+  const uint32_t row_jump16 = (uint32_t)(vw.W - vw.tw) * vw.st16, frame_jump16 = (uint32_t)((vw.H - vw.th) * vw.W) * vw.st16;
+  auto move_next = [&](uint32_t dst) SG_INLINE {   // move the run, go one stage on
+    move_run(kcur, vcur, dst);
+    uint64_t by = stage_bytes;
+    if (MODE == kWalk) {
+      uint32_t by16 = kKeys * vw.st16;
+      walk_j += kKeys;
+      if (vw.tw >= kKeys) {   // at most one tile row ends: no branch
+        const bool ends = walk_j >= vw.tw;
+        walk_j -= ends ? vw.tw : 0;
+        walk_i += ends ? 1 : 0;
+        const bool over = walk_i == vw.th;
+        walk_i = over ? 0 : walk_i;
+        by16 += (ends ? row_jump16 : 0u) + (over ? frame_jump16 : 0u);
+      } else {
+        while (walk_j >= vw.tw) {
+          walk_j -= vw.tw;
+          by16 += row_jump16;
+          if (++walk_i == vw.th) { walk_i = 0; by16 += frame_jump16; }
+        }
+      }
+      by = (uint64_t)by16 << 4;
+    }
+    kcur += by;
+    vcur += by;
+  };
   auto move_planned = [&](int blk, uint32_t dst) SG_INLINE {
     if (run_info == 0) {
       const uint64_t first = (uint64_t)run_first16 << 4;
@@ -328,10 +368,8 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
   // issue stage `blk`, whose keys are all below N, into ring slot `st` = blk % 4
   auto issue_full = [&](int blk, int st) SG_INLINE {
     const uint32_t dst = dma_dst + st * kTileBytes;
-    if (MODE == kLinear) {
-      move_run(kcur, vcur, dst);
-      kcur += stage_bytes;
-      vcur += stage_bytes;
+    if (MODE != kWindow) {
+      move_next(dst);
     } else {
       move_planned(blk, dst);
       if (st == kStages - 1 && (blk & 63) == 63) plan64(blk + 1);
@@ -371,12 +409,8 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
       fetch_plan(blk);
     }
     if (blk * kKeys + kTok * (wave + 1) > N) look_up(blk, dst);
-    else if (MODE == kLinear) move_run(kcur, vcur, dst);
+    else if (MODE != kWindow) move_next(dst);   // (a wavefront looks up all stages behind one that it looked up)
     else move_planned(blk, dst);
-    if (MODE == kLinear) {
-      kcur += stage_bytes;
-      vcur += stage_bytes;
-    }
   };
 
   // The first stage is requested before Q, so that the two latencies run side by side; the next two stages follow when Q is
@@ -778,18 +812,23 @@ int launch_attention_bf16(const TileView& tv, int heads, int head_dim, float sca
   // three stages of 128 keys and fewer do not fill the pipeline: measured in attention_bf16_short.hip
   if (head_dim == 64 && tv.window && tv.N <= 384) return launch_attention_bf16_short(tv, heads, scale, b, s);
   const View16 vw = make_view16(tv);
-  // Windows of head_dim 64 and windows whose offsets inside a head leave 32 bits are scaled late: these calls have always had the
-  // smaller error (2.2e-3 against fp64, scaled first 2.9e-3).
+  // Windows of head_dim 128 whose runs of 8 tokens all lie side by side (width a multiple of 8, none of the launch crosses a canvas
+  // edge) are walked.  A step of 20 tiles of 75,600 tokens, 40 heads: 1,744 ms walked, 1,793 - 1,817 planned, 1,731 gathered and
+  // packed; 9 tiles of 3,840 tokens 2.245 and 2.263 ms.  (A launch in which some windows wrap is planned as a whole: walking the
+  // others in a launch of their own costs small steps a partial last round, 4 % at 9 tiles of 3,840 tokens.)
   bool wraps = false;
   for (int i = 0; i < b.n_tiles && tv.window; ++i) wraps = wraps || b.y0[i] + tv.th > tv.H || b.x0[i] + tv.tw > tv.W;
-  const bool late = head_dim == 64 || (!(vw.reach & kReachHead) && (wraps || tv.tw % 8 != 0));
+  const bool walk = head_dim == 128 && tv.window && !wraps && tv.tw % 8 == 0 && (vw.reach & kReachLane);
+  // Windows of head_dim 64 and others whose offsets inside a head leave 32 bits are scaled late: these calls have always had the
+  // smaller error (2.2e-3 against fp64, scaled first 2.9e-3).
+  const bool late = head_dim == 64 || (!walk && !(vw.reach & kReachHead));
   // a packed tile whose tokens are so far apart that 16 of them span 4 GiB is read like a window (of itself)
   const bool window = tv.window || !(vw.reach & kReachLane);
   const int n_qblocks = (tv.N + kBR - 1) / kBR;
   const float c_log2 = scale * 1.4426950408889634f;
   // the kernels need more dynamic LDS than the default limit; the attribute is set once per device and kernel
   constexpr int kMaxDevices = 64;
-  static std::atomic<bool> attr_set[kMaxDevices][7];   // zero-initialised; set twice by racing threads is harmless
+  static std::atomic<bool> attr_set[kMaxDevices][8];   // zero-initialised; set twice by racing threads is harmless
   int dev = 0, n_cu = 0;
   SG_HIP_TRY(hipGetDevice(&dev));
   SG_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
@@ -827,6 +866,8 @@ int launch_attention_bf16(const TileView& tv, int heads, int head_dim, float sca
     if (head_dim == 64)
       st = window ? launch(attention_bf16_kernel<64, kWindow, true, false>, 0)
            : fuse_refresh ? launch(attention_bf16_kernel<64, kLinear, false, true>, 1) : launch(attention_bf16_kernel<64, kLinear, false, false>, 2);
+    else if (walk)
+      st = launch(attention_bf16_kernel<128, kWalk, false, false>, 7);
     else if (window)
       st = late ? launch(attention_bf16_kernel<128, kWindow, true, false>, 3) : launch(attention_bf16_kernel<128, kWindow, false, false>, 4);
     else

@@ -180,6 +180,27 @@ def test_attention_bf16_wide_token_stride_takes_general_addressing(tw):
     assert_close(to_f64(out), oracle_tile_attention_full(g, *dense, 1, 1), "bf16")
 
 
+@pytest.mark.parametrize("T,th,tw", [(9, 10, 8), (1, 1, 704), (5, 1, 136), (3, 20, 16), (2, 9, 56), (1, 11, 64), (3, 5, 72), (2, 3, 128),
+                                     (3, 20, 9), (2, 8, 63), (1, 13, 65)])
+@pytest.mark.parametrize("where", ["fixed", "inside", "wrapped"])
+def test_attention_bf16_windows_equal_the_packed_tile_bit_for_bit(T, th, tw, where):
+    """Windows of head_dim 128 through the loaders for unbroken runs (widths that are multiples of 8, at and below and above a
+    stage of 64, one to many tile rows and frames per stage) and for broken ones (other widths, wrapping windows) carry out the
+    arithmetic of the packed tile.  The rest of the canvas is NaN: nothing outside the window is read."""
+    g = _geom("walk", T, 2 * th, 2 * tw, th, tw, th, tw, 3, 128, "bf16", 37 + tw)
+    shift = {"fixed": (0, 0), "inside": (th // 3, 5), "wrapped": (2 * th - (th + 1) // 2, 2 * tw - 3)}[where]
+    tile = [randn_tensor(g.tile_shape, "bf16", g.seed + i).cuda() for i in range(3)]
+    canvas = []
+    for t in tile:
+        c = torch.full(g.grid_shape, float("nan"), dtype=torch.bfloat16, device="cuda")
+        c[:, :, :th, :tw] = t
+        canvas.append(torch.roll(c, shift, dims=(2, 3)))
+    got, want = torch.empty_like(tile[0]), torch.empty_like(tile[0])
+    sg.sg_tile_attention(sg.make_problem(g, shift=shift), *canvas, 0, 0, got)
+    sg.sg_tile_attention(sg.make_problem(_geom("walk", T, th, tw, th, tw, th, tw, 3, 128, "bf16", 0)), *tile, 0, 0, want)
+    assert torch.isfinite(want.float()).all() and torch.equal(got, want)
+
+
 def test_attention_bf16_large_logits_and_constant_v():
     """Scores far from N(0,1): softmax concentrates; constant V must come back exactly-ish."""
     g = _geom("sharp", 2, 10, 16, 10, 16, 10, 16, 2, 128, "bf16", 41)

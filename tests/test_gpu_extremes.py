@@ -158,3 +158,19 @@ def test_fp32_attention_is_as_close_to_fp64_as_plain_fp32(th, tw, d):
     got = _attend_window("f32", d, heads, 1, th, tw, q, k, v, packed=True).double()
     plain = _fp32_attention(q, k, v, scale).double()
     assert float((got - ref).norm()) <= 1.05 * float((plain - ref).norm())
+
+
+# 1 head: eight shares of the keys; 48 heads: enough workgroups for four.  400 tokens are 13 blocks of 32 keys, dealt to the shares in turn.
+@pytest.mark.parametrize("heads", [1, 48])
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_attention_takes_values_up_to_the_largest_number(d, heads):
+    """Scores that rise by 4.9 from a share's first block of keys to its second or third: no probability may exceed 1, or
+    3e38 times it would overflow."""
+    n, key = 400, 261                                       # block 8, that of share 0 in either split
+    q, k, v = torch.zeros(heads, n, d), torch.zeros(heads, n, d), torch.zeros(heads, n, d)
+    q[:, :, 0] = math.sqrt(d)
+    k[:, key, 0] = 4.9
+    v[:, key] = 3e38
+    got = _attend_window("f32", d, heads, 1, 16, 25, q, k, v, packed=True).double()
+    want = 3e38 * math.exp(4.9) / (math.exp(4.9) + n - 1)
+    assert float((got / want - 1.0).abs().max()) <= 1e-5

@@ -216,8 +216,9 @@ __global__ __launch_bounds__(64 * KS, 2) void attention_f32_kernel(
         for (int db = 0; db < kPer; ++db) acc[qb][db] *= alpha;
       }
       float l0 = 0.f, l1 = 0.f;
+      const float base = (ref[qb] == -__builtin_inff()) ? 0.f : ref[qb];   // all scores of this share -inf so far: probabilities 0
 #pragma unroll
-      for (int r = 0; r < 16; ++r) p[qb][r] = __builtin_amdgcn_exp2f((p[qb][r] - ref[qb]) * kLog2e);
+      for (int r = 0; r < 16; ++r) p[qb][r] = __builtin_amdgcn_exp2f((p[qb][r] - base) * kLog2e);
 #pragma unroll
       for (int r = 0; r < 16; r += 2) { l0 += p[qb][r]; l1 += p[qb][r + 1]; }
       l[qb] += l0 + l1;

@@ -174,3 +174,22 @@ def test_fp32_attention_takes_values_up_to_the_largest_number(d, heads):
     got = _attend_window("f32", d, heads, 1, 16, 25, q, k, v, packed=True).double()
     want = 3e38 * math.exp(4.9) / (math.exp(4.9) + n - 1)
     assert float((got / want - 1.0).abs().max()) <= 1e-5
+
+
+@pytest.mark.parametrize("block", [0, 1, 4, 11, 12])
+@pytest.mark.parametrize("heads", [1, 48])
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_attention_ignores_a_block_of_scores_at_minus_infinity(d, heads, block):
+    """Keys whose scores overflow to -inf have probability 0, also where they are all that a share of the keys has seen so far."""
+    n = 400
+    gen = torch.Generator().manual_seed(n + d)
+    q, k, v = (torch.randn(heads, n, d, generator=gen) for _ in range(3))
+    q[:, :, 7] = 1e20
+    k[:, :, 7] = 0.0
+    gone = slice(32 * block, min(32 * block + 32, n))
+    k[:, gone, 7] = -1e20
+    got = _attend_window("f32", d, heads, 1, 16, 25, q, k, v, packed=True).double()
+    s = q.double() @ k.double().transpose(1, 2) / math.sqrt(d)
+    s[:, :, gone] = -math.inf
+    ref = torch.softmax(s, dim=2) @ v.double()
+    assert float((got - ref).norm() / ref.norm()) <= 1e-5

@@ -19,7 +19,7 @@
 //
 // Bound: matrix pipe (per 32 x 32 block and head_dim 128: 128 instructions of 64 cycles against 32 fragment reads
 // and 16 exponentials a lane).  Measured, before (vector ALU, keys and values broadcast from LDS) -> now, whole steps:
-// 4 tiles of 2,880 tokens, 8 heads x 128: 7.35 -> 1.20 ms (115 TFLOP/s in the kernel); 4 tiles of 300 tokens,
+// 4 tiles of 2,880 tokens, 8 heads x 128: 7.35 -> 1.21 ms (114 TFLOP/s in the kernel); 4 tiles of 300 tokens,
 // 2 heads x 64: 75.6 -> 17.6 us.
 #include <atomic>
 #include "attention_common.h"
@@ -32,6 +32,8 @@ namespace {
 constexpr int kKeys = 32;    // keys per block
 constexpr int kXcd = 8;
 constexpr float kLog2e = 1.4426950408889634f;
+constexpr uint32_t kNowhere8 = 0x07ffff00;   // an offset (32-byte units) beyond every head that is not WIDE, whose bytes still fit 32 bits
+
 constexpr int kWaveBytes = 16384;   // LDS of a wavefront: its K block, after the key loop its partial output
 template <int QB, int KS>
 constexpr int kLds = KS * kWaveBytes + 2 * KS * QB * 32 * 4;   // and (reference, sum) per wavefront and query
@@ -39,10 +41,11 @@ constexpr int kLds = KS * kWaveBytes + 2 * KS * QB * 32 * 4;   // and (reference
 enum { kLinear = 0, kWindow = 1 };   // how a tile token is found
 
 // KS wavefronts = shares of the keys; two wavefronts per SIMD either way: one workgroup of 8 per compute unit, or two of 4
-template <int D, int QB, int KS, int MODE>
+// WIDE: offsets inside a head leave 32 bits
+template <int D, int QB, int KS, int MODE, bool WIDE>
 __global__ __launch_bounds__(64 * KS, 2) void attention_f32_kernel(
     const View16 vw, const float scale, const int heads, const int n_qblocks, const int n_tiles, const AttnTable tab,
-    const uint8_t* __restrict__ run_flags) {
+    const uint32_t head_bytes, const uint8_t* __restrict__ run_flags) {
   static_assert(kKeys * D * 4 <= kWaveBytes && QB * 32 * D * 4 <= kWaveBytes, "K block and partial output");
   constexpr int kPer = D / 32;   // channels a lane holds of one V row: output blocks
   extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
@@ -106,11 +109,18 @@ __global__ __launch_bounds__(64 * KS, 2) void attention_f32_kernel(
       dma16_addr(kh + (size_t)o * 32 + ((slot ^ (row & 15)) << 4), lds_k + i * 1024);
     }
   };
-  // V straight into registers, one coalesced load per key pair (k, k + 4): the upper half of the wavefront reads row k + 4
+  // V straight into registers, one coalesced load per key pair (k, k + 4): the upper half of the wavefront reads row k + 4.  Keys >= N
+  // stand in for the last one with probability 0, and their values have to be zeros, or an infinite last value becomes 0 * inf: they
+  // get an offset beyond the head, for which a buffer load returns zeros.  (Selecting zeros for every pair costs 5 %; only heads
+  // whose offsets leave 32 bits do.)
   typedef float vrow __attribute__((ext_vector_type(kPer)));
+  const __amdgpu_buffer_rsrc_t vbuf = __builtin_amdgcn_make_buffer_rsrc((void*)vh, 0, WIDE ? 0 : (int)head_bytes, 0x00020000);
+  auto value_off8 = [&](int b, uint32_t off8) SG_INLINE -> uint32_t { return (WIDE || b * kKeys + lq < N) ? off8 : kNowhere8; };
   auto load_v = [&](uint32_t off8, int r) SG_INLINE -> vrow {
     const uint32_t o = (uint32_t)__shfl((int)off8, 8 * (r >> 2) + (r & 3) + 4 * half, 64);
-    return *(const vrow*)(vh + (size_t)o * 32 + lq * (kPer * 4));
+    if constexpr (WIDE) return *(const vrow*)(vh + (size_t)o * 32 + lq * (kPer * 4));
+    else if constexpr (kPer == 4) return __builtin_bit_cast(vrow, __builtin_amdgcn_raw_buffer_load_b128(vbuf, o * 32 + lq * 16, 0, 0));
+    else return __builtin_bit_cast(vrow, __builtin_amdgcn_raw_buffer_load_b64(vbuf, o * 32 + lq * 8, 0, 0));
   };
   constexpr int kAhead = 4;   // key pairs whose V rows are in flight: 1,024 cycles of matrix work
   auto reads_done = [&]() SG_INLINE {   // this wavefront's fragment reads have returned: the block may be overwritten
@@ -137,10 +147,11 @@ __global__ __launch_bounds__(64 * KS, 2) void attention_f32_kernel(
   };
 
   const int n_blocks = (N + kKeys - 1) / kKeys;
-  uint32_t off = 0;   // block_off8 of the block in work
+  uint32_t off = 0;   // value_off8 of the block in work
   if (wave < n_blocks) {
-    off = block_off8(wave);
-    issue_k(off);
+    const uint32_t first = block_off8(wave);
+    issue_k(first);
+    off = value_off8(wave, first);
   }
   for (int b = wave; b < n_blocks; b += KS) {
     const bool more = b + KS < n_blocks;
@@ -181,8 +192,9 @@ __global__ __launch_bounds__(64 * KS, 2) void attention_f32_kernel(
     reads_done();
     uint32_t next = 0;
     if (more) {
-      next = block_off8(b + KS);
-      issue_k(next);
+      const uint32_t first = block_off8(b + KS);
+      issue_k(first);
+      next = value_off8(b + KS, first);
     }
     vrow v[16];
 #pragma unroll
@@ -228,6 +240,11 @@ __global__ __launch_bounds__(64 * KS, 2) void attention_f32_kernel(
     for (int r = 0; r < 16; ++r) {
       if (r + kAhead < 16) v[r + kAhead] = load_v(off, r + kAhead);
       __builtin_amdgcn_sched_barrier(0);
+      if constexpr (WIDE) {
+        const bool gone = b * kKeys + 8 * (r >> 2) + 4 * half + (r & 3) >= N;
+#pragma unroll
+        for (int x = 0; x < kPer; ++x) v[r][x] = gone ? 0.f : v[r][x];
+      }
 #pragma unroll
       for (int db = 0; db < kPer; ++db)
 #pragma unroll
@@ -307,11 +324,13 @@ int launch_attention_f32(const TileView& tv, int heads, int head_dim, float scal
   if (b.n_tiles <= 0) return SG_OK;
   const View16 vw = make_view16(tv);
   constexpr int kMaxDevices = 64;
-  static std::atomic<bool> attr_set[kMaxDevices][12];   // zero-initialised; set twice by racing threads is harmless
+  static std::atomic<bool> attr_set[kMaxDevices][20];   // zero-initialised; set twice by racing threads is harmless
   int dev = 0, n_cu = 0;
   SG_HIP_TRY(hipGetDevice(&dev));
   SG_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
   if (n_cu < 1) n_cu = 1;
+  const int64_t head_units = (int64_t)tv.T * tv.H * tv.W * (tv.stride_token / 8);   // an upper bound of a head's extent, in 32 bytes
+  const bool far = head_units > kNowhere8;
   for (int t0 = 0; t0 < b.n_tiles; t0 += kAttnTilesPerLaunch) {
     const int n = (b.n_tiles - t0 < kAttnTilesPerLaunch) ? b.n_tiles - t0 : kAttnTilesPerLaunch;
     AttnTable tab;
@@ -326,33 +345,35 @@ int launch_attention_f32(const TileView& tv, int heads, int head_dim, float scal
       tab.refresh[i] = nullptr;   // the cache refresh is not carried by this kernel
     }
     const uint8_t* flags = b.run_flags ? b.run_flags + t0 : nullptr;
-    // 64 queries per workgroup (head_dim 64: the registers hold them) read K and V half as often as 32 but make half as many
+    // 64 queries per workgroup (head_dim 64, heads within 32-bit offsets: the registers hold them) read K and V half as often as 32 but make half as many
     // workgroups: taken where their rounds over the device are not longer.  Then 4 shares of the keys, two workgroups per
     // compute unit, where there are that many workgroups: one's start, end and uneven last blocks run beside the other's loop.
     // Fewer workgroups take 8 shares, which halves the time of each.  (4 x 2,880 tokens, 8 heads x 128, 2,880 workgroups: 1.30 ms
     // a step with 8 shares, 1.20 with 4.)
     const int64_t wg1 = (int64_t)n * heads * ((tv.N + 31) / 32), wg2 = (int64_t)n * heads * ((tv.N + 63) / 64);
-    const bool wide = head_dim == 64 && 2 * ((wg2 + n_cu - 1) / n_cu) <= (wg1 + n_cu - 1) / n_cu;
-    const int64_t total = wide ? wg2 : wg1;
+    const bool two_blocks = head_dim == 64 && !far && 2 * ((wg2 + n_cu - 1) / n_cu) <= (wg1 + n_cu - 1) / n_cu;
+    const int64_t total = two_blocks ? wg2 : wg1;
     const bool pairs = total >= 2 * n_cu;
     if (total > (1ll << 31) - 2 * kXcd) return SG_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)(((total + kXcd - 1) / kXcd) * kXcd));
-    const int n_qblocks = (tv.N + (wide ? 63 : 31)) / (wide ? 64 : 32);
+    const int n_qblocks = (tv.N + (two_blocks ? 63 : 31)) / (two_blocks ? 64 : 32);
     auto launch = [&](auto kern, int shares, int lds, int slot) -> int {
       if (dev < 0 || dev >= kMaxDevices || !attr_set[dev][slot].load(std::memory_order_acquire)) {
         SG_HIP_TRY(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
         if (dev >= 0 && dev < kMaxDevices) attr_set[dev][slot].store(true, std::memory_order_release);
       }
-      kern<<<grid, 64 * shares, lds, s>>>(vw, scale, heads, n_qblocks, n, tab, flags);
+      kern<<<grid, 64 * shares, lds, s>>>(vw, scale, heads, n_qblocks, n, tab, (uint32_t)(head_units * 32), flags);
       return SG_OK;
     };
     int st;
-#define SG_F32_MODES(D, QB, KS, SLOT)                                                        \
-  (tv.window ? launch(attention_f32_kernel<D, QB, KS, kWindow>, KS, kLds<QB, KS>, SLOT)      \
-             : launch(attention_f32_kernel<D, QB, KS, kLinear>, KS, kLds<QB, KS>, SLOT + 1))
-    if (head_dim == 128) st = pairs ? SG_F32_MODES(128, 1, 4, 0) : SG_F32_MODES(128, 1, 8, 2);
-    else if (wide) st = pairs ? SG_F32_MODES(64, 2, 4, 4) : SG_F32_MODES(64, 2, 8, 6);
-    else st = pairs ? SG_F32_MODES(64, 1, 4, 8) : SG_F32_MODES(64, 1, 8, 10);
+#define SG_F32_MODES(D, QB, KS, WIDE, SLOT)                                                        \
+  (tv.window ? launch(attention_f32_kernel<D, QB, KS, kWindow, WIDE>, KS, kLds<QB, KS>, SLOT)      \
+             : launch(attention_f32_kernel<D, QB, KS, kLinear, WIDE>, KS, kLds<QB, KS>, SLOT + 1))
+    if (far && head_dim == 128) st = pairs ? SG_F32_MODES(128, 1, 4, true, 0) : SG_F32_MODES(128, 1, 8, true, 2);
+    else if (far) st = pairs ? SG_F32_MODES(64, 1, 4, true, 4) : SG_F32_MODES(64, 1, 8, true, 6);
+    else if (head_dim == 128) st = pairs ? SG_F32_MODES(128, 1, 4, false, 8) : SG_F32_MODES(128, 1, 8, false, 10);
+    else if (two_blocks) st = pairs ? SG_F32_MODES(64, 2, 4, false, 12) : SG_F32_MODES(64, 2, 8, false, 14);
+    else st = pairs ? SG_F32_MODES(64, 1, 4, false, 16) : SG_F32_MODES(64, 1, 8, false, 18);
 #undef SG_F32_MODES
     if (st != SG_OK) return st;
     SG_HIP_TRY(hipGetLastError());

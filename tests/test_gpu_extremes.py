@@ -14,8 +14,8 @@ LOG2E = math.log2(math.e)
 
 def _attend_window(dtype, d, heads, T, th, tw, q, k, v, wrapped=False, packed=False, token_stride=0):
     """Attention of tile (0, 0) of a canvas of 2 x 2 tiles (packed: of one), whose tokens are q, k, v [heads][N][d]; wrapped:
-    shifted so far that the window crosses both canvas edges.  With a token stride (one head) the three canvases lie in one
-    buffer of tokens that far apart, side by side in every token."""
+    shifted so far that the window crosses both canvas edges.  With a token stride the three canvases lie in one
+    buffer of tokens that far apart, their heads side by side in every token."""
     rows, cols = (1, 1) if packed else (2, 2)
     g = TileGeometry("ends", T, rows * th, cols * tw, th, tw, th, tw, rows, cols, heads, d, dtype, 0)
     shift = (2 * th - 3, 2 * tw - 5) if wrapped else (0, 0)
@@ -30,8 +30,9 @@ def _attend_window(dtype, d, heads, T, th, tw, q, k, v, wrapped=False, packed=Fa
         buf = torch.empty(g.grid_tokens * token_stride, dtype=out.dtype, device="cuda")
         p.grid_stride_token, p.grid_stride_head = token_stride, d
         for i, c in enumerate(canvases):
-            canvases[i] = buf[i * d:]
-            canvases[i].as_strided((g.grid_tokens, d), (token_stride, 1)).copy_(c.reshape(g.grid_tokens, d))
+            canvases[i] = buf[i * heads * d:]
+            view = canvases[i].as_strided((heads, g.grid_tokens, d), (d, token_stride, 1))
+            view.copy_(c.reshape(heads, g.grid_tokens, d))
     sg.sg_tile_attention(p, *canvases, 0, 0, out)
     return out.cpu().reshape(heads, -1, d)
 
@@ -193,3 +194,25 @@ def test_fp32_attention_ignores_a_block_of_scores_at_minus_infinity(d, heads, bl
     s[:, :, gone] = -math.inf
     ref = torch.softmax(s, dim=2) @ v.double()
     assert float((got - ref).norm() / ref.norm()) <= 1e-5
+
+
+@pytest.mark.parametrize("heads", [1, 48])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("T,th,tw", [(1, 1, 7), (1, 3, 11), (1, 16, 25), (1, 16, 26)])
+def test_fp32_attention_takes_an_infinite_last_value(T, th, tw, d, heads):
+    """7, 33, 400 and 416 tokens: the keys that fill up the last block of 32 stand in for the last one."""
+    _infinite_last_value("f32", d, heads, T, th, tw)
+
+
+@pytest.mark.parametrize("heads", [1, 48])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("wrapped", [False, True], ids=["fixed", "wrapped"])
+def test_fp32_attention_of_heads_beyond_4_gib(wrapped, d, heads):
+    """Offsets inside a head that leave 32 bits, with either split of the keys."""
+    n = 400
+    gen = torch.Generator().manual_seed(n + d)
+    q, k, v = (torch.randn(heads, n, d, generator=gen) for _ in range(3))
+    got = _attend_window("f32", d, heads, 1, 16, 25, q, k, v, wrapped=wrapped, token_stride=1 << 20).double()
+    ref = torch.softmax(q.double() @ k.double().transpose(1, 2) / math.sqrt(d), dim=2) @ v.double()
+    assert float((got - ref).norm() / ref.norm()) <= 1e-6           # measured 2.3e-7
+    _infinite_last_value("f32", d, heads, 1, 16, 25, wrapped=wrapped, token_stride=1 << 20)

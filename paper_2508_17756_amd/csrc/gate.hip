@@ -40,12 +40,19 @@ __device__ __forceinline__ void accum_vec(const u32x4 a, const u32x4 b, float& n
     }
   }
 }
+template <int DT>
+__device__ __forceinline__ void accum_vec(const u32x4 a, const u32x4 b, double& num_sum, double& den_sum) {
+  float num = 0.f, den = 0.f;
+  accum_vec<DT>(a, b, num, den);
+  num_sum += (double)num;
+  den_sum += (double)den;
+}
 
 // One resident workgroup per compute unit walks the tiles of the launch one after the other; within a tile
 // workgroup b streams the b-th of gridDim.x equal contiguous slabs of both buffers.  Every workgroup
 // therefore carries the same load, no tail of late workgroups forms, and each buffer is read as
 // gridDim.x long sequential streams.
-template <int DT>
+template <int DT, bool CUT>
 __global__ __launch_bounds__(kThreads) void gate_partial_kernel(GatePtrs ptrs, const uint8_t* __restrict__ has_cache,
                                                                 int tile0, int n_tiles, int64_t elems,
                                                                 double* __restrict__ partial) {
@@ -63,7 +70,7 @@ __global__ __launch_bounds__(kThreads) void gate_partial_kernel(GatePtrs ptrs, c
     }
     const u32x4* __restrict__ a = (const u32x4*)ptrs.cur[tile];
     const u32x4* __restrict__ b = (const u32x4*)ptrs.cached[tile];
-    float num0 = 0.f, den0 = 0.f, num1 = 0.f, den1 = 0.f;
+    PassSum<CUT> num0 = 0, den0 = 0, num1 = 0, den1 = 0;
     int64_t i = v0 + threadIdx.x;
     for (; i + (kGateUnroll - 1) * kThreads < v1; i += kGateUnroll * kThreads) {
       u32x4 av[kGateUnroll], bv[kGateUnroll];
@@ -288,7 +295,7 @@ struct GainPtrs {
 // One workgroup per compute unit; the workgroups walk each tile's buffers together, chunk by chunk.
 // delta is kept in fp32: its magnitude follows the latent's and can exceed the output's by orders, so
 // the output's storage type would lose O_c.
-template <int DT>
+template <int DT, bool CUT>
 __global__ __launch_bounds__(kThreads) void gain_refresh_kernel(GainPtrs ptrs, const uint8_t* __restrict__ recompute,
                                                                 const uint8_t* __restrict__ has_prev, int tile0, int n_tiles,
                                                                 int64_t elems, double* __restrict__ partial) {
@@ -348,7 +355,7 @@ __global__ __launch_bounds__(kThreads) void gain_refresh_kernel(GainPtrs ptrs, c
     // recompute: store the residual; relative change of the output against the previous step's
     const bool sums = has_prev[tile0 + tile] != 0;
     const u32x4* __restrict__ op = (const u32x4*)ptrs.out_prev[tile];
-    float num0 = 0.f, den0 = 0.f, num1 = 0.f, den1 = 0.f;
+    PassSum<CUT> num0 = 0, den0 = 0, num1 = 0, den1 = 0;
     int64_t i = first;
     for (; main_ok(i); i += step) {
       u32x4 a[kRefreshUnroll], l[kRefreshUnroll], b[kRefreshUnroll];
@@ -456,10 +463,10 @@ static int launch_partials(const void* const* a, const void* const* b, const uin
     for (int i = 0; i < n; ++i) { ptrs.cur[i] = a[t0 + i]; ptrs.cached[i] = b[t0 + i]; }
     for (int i = n; i < kTilesPerLaunch; ++i) { ptrs.cur[i] = nullptr; ptrs.cached[i] = nullptr; }
     const dim3 grid = pass_grid(n_vec, n, n_cu, kGateSlots / kWavesPerBlock);
-    if (dtype == SG_BF16)
-      gate_partial_kernel<SG_BF16><<<grid, kThreads, 0, s>>>(ptrs, active, t0, n, elems, partial);
-    else
-      gate_partial_kernel<SG_F32><<<grid, kThreads, 0, s>>>(ptrs, active, t0, n, elems, partial);
+    const bool cut = pass_cut(n_vec, n_cu, kGateSlots / kWavesPerBlock);
+    auto kern = dtype == SG_BF16 ? (cut ? gate_partial_kernel<SG_BF16, true> : gate_partial_kernel<SG_BF16, false>)
+                                 : (cut ? gate_partial_kernel<SG_F32, true> : gate_partial_kernel<SG_F32, false>);
+    kern<<<grid, kThreads, 0, s>>>(ptrs, active, t0, n, elems, partial);
     SG_HIP_TRY(hipGetLastError());
   }
   return SG_OK;
@@ -512,10 +519,10 @@ int launch_gain_refresh(void* const* out_cur, const void* const* out_prev, const
       ptrs.delta[i] = i < n ? delta[t0 + i] : nullptr;
     }
     const dim3 grid = pass_grid(n_vec, n, n_cu, kGateSlots / kWavesPerBlock);
-    if (dtype == SG_BF16)
-      gain_refresh_kernel<SG_BF16><<<grid, kThreads, 0, s>>>(ptrs, recompute, gs.has_prev, t0, n, elems, partial);
-    else
-      gain_refresh_kernel<SG_F32><<<grid, kThreads, 0, s>>>(ptrs, recompute, gs.has_prev, t0, n, elems, partial);
+    const bool cut = pass_cut(n_vec, n_cu, kGateSlots / kWavesPerBlock);
+    auto kern = dtype == SG_BF16 ? (cut ? gain_refresh_kernel<SG_BF16, true> : gain_refresh_kernel<SG_BF16, false>)
+                                 : (cut ? gain_refresh_kernel<SG_F32, true> : gain_refresh_kernel<SG_F32, false>);
+    kern<<<grid, kThreads, 0, s>>>(ptrs, recompute, gs.has_prev, t0, n, elems, partial);
     SG_HIP_TRY(hipGetLastError());
   }
   gain_refresh_finalize_kernel<<<n_tiles, kFinalThreads, 0, s>>>(partial, n_blk * kWavesPerBlock, recompute, step_change, gs.has_prev,

@@ -35,9 +35,17 @@ __device__ __forceinline__ void moments_vec(const u32x4 a, const float pivot, fl
   }
 }
 
+template <int DT>
+__device__ __forceinline__ void moments_vec(const u32x4 a, const float pivot, double& sum1, double& sum2) {
+  float s1 = 0.f, s2 = 0.f;
+  moments_vec<DT>(a, pivot, s1, s2);
+  sum1 += (double)s1;
+  sum2 += (double)s2;
+}
+
 // Sums of (x - pivot) and (x - pivot)^2 per tile and workgroup; pivot = the tile's first element, which
 // keeps the variance free of cancellation when the mean is large against the spread.
-template <int DT>
+template <int DT, bool CUT>
 __global__ __launch_bounds__(kThreads) void tile_moments_kernel(StdPtrs ptrs, int tile0, int n_tiles, int64_t elems,
                                                                 double* __restrict__ partial) {
   constexpr int kPerVec = (DT == SG_BF16) ? 8 : 4;
@@ -51,7 +59,7 @@ __global__ __launch_bounds__(kThreads) void tile_moments_kernel(StdPtrs ptrs, in
     float pivot;
     if (DT == SG_BF16) pivot = bf16_bits_to_f32(((const uint16_t*)ptrs.x[tile])[0]);
     else pivot = ((const float*)ptrs.x[tile])[0];
-    float a0 = 0.f, b0 = 0.f, a1 = 0.f, b1 = 0.f;
+    PassSum<CUT> a0 = 0, b0 = 0, a1 = 0, b1 = 0;
     int64_t i = v0 + threadIdx.x;
     for (; i + (kMomentsUnroll - 1) * kThreads < v1; i += kMomentsUnroll * kThreads) {
       u32x4 xv[kMomentsUnroll];
@@ -163,8 +171,10 @@ int launch_tile_std(const void* const* x, int n_tiles, int64_t elems, int dtype,
     StdPtrs ptrs;
     for (int i = 0; i < kTilesPerLaunch; ++i) ptrs.x[i] = i < n ? x[t0 + i] : nullptr;
     const dim3 grid = pass_grid(n_vec, n, n_cu, kGateSlots / kWavesPerBlock);
-    if (dtype == SG_BF16) tile_moments_kernel<SG_BF16><<<grid, kThreads, 0, s>>>(ptrs, t0, n, elems, partial);
-    else tile_moments_kernel<SG_F32><<<grid, kThreads, 0, s>>>(ptrs, t0, n, elems, partial);
+    const bool cut = pass_cut(n_vec, n_cu, kGateSlots / kWavesPerBlock);
+    auto kern = dtype == SG_BF16 ? (cut ? tile_moments_kernel<SG_BF16, true> : tile_moments_kernel<SG_BF16, false>)
+                                 : (cut ? tile_moments_kernel<SG_F32, true> : tile_moments_kernel<SG_F32, false>);
+    kern<<<grid, kThreads, 0, s>>>(ptrs, t0, n, elems, partial);
     SG_HIP_TRY(hipGetLastError());
   }
   tile_std_finalize_kernel<<<n_tiles, kFinalThreads, 0, s>>>(partial, n_blk * kWavesPerBlock, elems, tile_std);

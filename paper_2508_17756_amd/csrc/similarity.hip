@@ -44,8 +44,16 @@ __device__ __forceinline__ void sim_vec(const u32x4 a, const u32x4 b, float (&s)
   }
 }
 
-// partial: per tile kGateSlots * 2 doubles; workgroup blk of a tile writes its five sums at [blk * kSums, +kSums)
 template <int DT>
+__device__ __forceinline__ void sim_vec(const u32x4 a, const u32x4 b, double (&sum)[kSums]) {
+  float s[kSums] = {0.f, 0.f, 0.f, 0.f, 0.f};
+  sim_vec<DT>(a, b, s);
+#pragma unroll
+  for (int j = 0; j < kSums; ++j) sum[j] += (double)s[j];
+}
+
+// partial: per tile kGateSlots * 2 doubles; workgroup blk of a tile writes its five sums at [blk * kSums, +kSums)
+template <int DT, bool CUT>
 __global__ __launch_bounds__(kThreads) void similarity_partial_kernel(SimPtrs ptrs, int tile0, int n_tiles, int64_t elems,
                                                                       double* __restrict__ partial) {
   constexpr int kPerVec = (DT == SG_BF16) ? 8 : 4;
@@ -58,7 +66,7 @@ __global__ __launch_bounds__(kThreads) void similarity_partial_kernel(SimPtrs pt
   for (int tile = blockIdx.y; tile < n_tiles; tile += gridDim.y) {
     const u32x4* __restrict__ a = (const u32x4*)ptrs.a[tile];
     const u32x4* __restrict__ b = (const u32x4*)ptrs.b[tile];
-    float s0[kSums] = {0.f, 0.f, 0.f, 0.f, 0.f}, s1[kSums] = {0.f, 0.f, 0.f, 0.f, 0.f};
+    PassSum<CUT> s0[kSums] = {0, 0, 0, 0, 0}, s1[kSums] = {0, 0, 0, 0, 0};
     int64_t i = v0 + threadIdx.x;
     for (; i + (kSimUnroll - 1) * kThreads < v1; i += kSimUnroll * kThreads) {
       u32x4 av[kSimUnroll], bv[kSimUnroll];
@@ -144,8 +152,10 @@ int launch_similarity(const void* const* x_new, const void* const* x_old, int n_
     SimPtrs ptrs;
     for (int i = 0; i < kTilesPerLaunch; ++i) { ptrs.a[i] = i < n ? x_new[t0 + i] : nullptr; ptrs.b[i] = i < n ? x_old[t0 + i] : nullptr; }
     const dim3 grid = pass_grid(n_vec, n, n_cu, kMaxBlk);
-    if (dtype == SG_BF16) similarity_partial_kernel<SG_BF16><<<grid, kThreads, 0, s>>>(ptrs, t0, n, elems, partial);
-    else similarity_partial_kernel<SG_F32><<<grid, kThreads, 0, s>>>(ptrs, t0, n, elems, partial);
+    const bool cut = pass_cut(n_vec, n_cu, kMaxBlk);
+    auto kern = dtype == SG_BF16 ? (cut ? similarity_partial_kernel<SG_BF16, true> : similarity_partial_kernel<SG_BF16, false>)
+                                 : (cut ? similarity_partial_kernel<SG_F32, true> : similarity_partial_kernel<SG_F32, false>);
+    kern<<<grid, kThreads, 0, s>>>(ptrs, t0, n, elems, partial);
     SG_HIP_TRY(hipGetLastError());
   }
   similarity_finalize_kernel<<<n_tiles, kFinalThreads, 0, s>>>(partial, n_blk, l1_rel, cos_sim);

@@ -186,3 +186,22 @@ def test_passes_over_tiles_cut_side_by_side_or_walked(dtype, vecs):
         else:
             assert torch.equal(delta[i], torch.full((n,), 9.0, device="cuda"))
             assert torch.equal(out[i], (olds[i].float() + 9.0).to(olds[i].dtype))
+
+
+def test_sums_of_small_tiles_are_rounded_once():
+    """bf16 tiles of 64 KiB to 4 MiB: standard deviation and cosine are fp64 sums of fp32 sums of 8 elements each, whose roundings
+    average out, so each is the exact value rounded once: half a unit in the last place of values just above and just
+    below 1 (2^-24 and 2^-25), a fifth more for the sums."""
+    for vecs in (1 << 12, 1 << 14, 1 << 16, 1 << 18):
+        old = [randn_tensor((8 * vecs,), "bf16", 3000 + i).cuda() for i in range(12)]
+        new = [perturb_(x.clone(), 0.1, 3100 + i) for i, x in enumerate(old)]
+        ws = torch.empty(sg.sg_workspace_bytes(12), dtype=torch.uint8, device="cuda")
+        std, l1, cs = (torch.empty(12, device="cuda") for _ in range(3))
+        sg.sg_tile_std(new, std, ws)
+        sg.sg_tile_similarity(new, old, l1, cs, ws)
+        for i in range(12):
+            a, b = new[i].double(), old[i].double()
+            want_std, want_cos = float(a.std(unbiased=False)), float((a * b).sum() / (a.norm() * b.norm()))
+            assert 0.98 < want_std < 1.03 and 0.99 < want_cos < 1.0
+            assert abs(float(std[i]) - want_std) <= 1.2 * 2 ** -24, (vecs, i)
+            assert abs(float(cs[i]) - want_cos) <= 1.2 * 2 ** -25, (vecs, i)

@@ -508,7 +508,7 @@ int launch_gain_refresh(void* const* out_cur, const void* const* out_prev, const
   SG_HIP_TRY(hipGetDevice(&dev));
   SG_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
   const int64_t n_vec = elems / (dtype == SG_BF16 ? 8 : 4);
-  const int n_blk = (int)pass_grid(n_vec, 1, n_cu, kGateSlots / kWavesPerBlock).x;
+  const int n_blk = (int)pass_grid(n_vec, 1, n_cu, kGateSlots / kWavesPerBlock, kRefreshVecs).x;
   for (int t0 = 0; t0 < n_tiles; t0 += kRefreshTilesPerLaunch) {
     const int n = (n_tiles - t0 < kRefreshTilesPerLaunch) ? n_tiles - t0 : kRefreshTilesPerLaunch;
     GainPtrs ptrs;
@@ -518,8 +518,8 @@ int launch_gain_refresh(void* const* out_cur, const void* const* out_prev, const
       ptrs.latent[i] = i < n ? latent[t0 + i] : nullptr;
       ptrs.delta[i] = i < n ? delta[t0 + i] : nullptr;
     }
-    const dim3 grid = pass_grid(n_vec, n, n_cu, kGateSlots / kWavesPerBlock);
-    const bool cut = pass_cut(n_vec, n_cu, kGateSlots / kWavesPerBlock);
+    const dim3 grid = pass_grid(n_vec, n, n_cu, kGateSlots / kWavesPerBlock, kRefreshVecs);
+    const bool cut = pass_cut(n_vec, n_cu, kGateSlots / kWavesPerBlock, kRefreshVecs);
     auto kern = dtype == SG_BF16 ? (cut ? gain_refresh_kernel<SG_BF16, true> : gain_refresh_kernel<SG_BF16, false>)
                                  : (cut ? gain_refresh_kernel<SG_F32, true> : gain_refresh_kernel<SG_F32, false>);
     kern<<<grid, kThreads, 0, s>>>(ptrs, recompute, gs.has_prev, t0, n, elems, partial);

@@ -78,12 +78,13 @@ inline size_t gate_workspace_bytes(int n_tiles) {
 
 // Grid of the streaming passes over tiles (x: workgroups that share a tile, y: tiles side by side).  Large tiles: one resident
 // workgroup per compute unit walks the tiles one after the other, y = 1 (no tail of late workgroups).  A tile with less than
-// kPassVecs 16-byte vectors for each of those is instead cut into workgroups of kPassVecs and all tiles run side by side: walked
+// `vecs` 16-byte vectors for each of those is instead cut into workgroups of that many and all tiles run side by side: walked
 // in turn, every small tile costs each workgroup a round trip to memory and a reduction with nothing beside it.
-// Measured, walked -> cut (gate, similarity, tile statistics, gain refresh, us a call): 20 tiles of 1 MiB 30, 36, 26, 42 -> 14,
-// 14, 12, 24; 9 of 4 MiB 22, 36, 29, 36 -> 16, 17, 12, 34; 9 of 8 MiB 32, 33, 48, 61 -> 27, 27, 16, 60; from 16 MiB (4,096 vectors
-// for each of 256 compute units) the two are within 2 %.  2,048 vectors are 10 - 15 % slower at 8 MiB, 8,192 leave a single tile
-// of 4 - 16 MiB 20 - 40 % slower in the refresh.
+// kPassVecs, the passes that only read.  Measured, walked -> cut (gate, similarity, tile statistics, us a call): 20 tiles of
+// 1 MiB 30, 36, 26 -> 14, 14, 12; 9 of 4 MiB 22, 36, 29 -> 16, 17, 12; 9 of 8 MiB 32, 33, 48 -> 27, 27, 16; from 16 MiB (4,096
+// vectors for each of 256 compute units) the two are within 2 %.  2,048 vectors leave 8 MiB walked, 16 - 200 % slower.
+// kRefreshVecs, the gain refresh, which writes as much as it reads: 20 tiles of 1 MiB 42 -> 22; of 4 MiB 73 -> 69; from
+// 8 MiB walked (130; cut into workgroups of 4,096 135).
 // In a cut tile a thread takes up to 16 vectors where a walked small tile gave it one: it hands the sums of every vector to fp64
 // (PassSum), so that no sum in fp32 is longer than 8 elements; in walked tiles, 16 MiB and larger, it keeps them in fp32 and hands
 // over once (fp64 for every vector slows the statistics of such tiles by a sixth: one wavefront per SIMD, nothing beside it).
@@ -93,12 +94,12 @@ template <bool CUT> struct PassSumType { typedef float type; };
 template <> struct PassSumType<true> { typedef double type; };
 template <bool CUT> using PassSum = typename PassSumType<CUT>::type;
 
-constexpr int64_t kPassVecs = 4096;
+constexpr int64_t kPassVecs = 4096, kRefreshVecs = 2048;
 inline int pass_most(int n_cu, int max_blk) { return n_cu < 1 ? 1 : (n_cu > max_blk ? max_blk : n_cu); }
-inline bool pass_cut(int64_t n_vec, int n_cu, int max_blk) { return (n_vec + kPassVecs - 1) / kPassVecs < pass_most(n_cu, max_blk); }
-inline dim3 pass_grid(int64_t n_vec, int n_tiles, int n_cu, int max_blk) {
-  if (!pass_cut(n_vec, n_cu, max_blk)) return dim3((unsigned)pass_most(n_cu, max_blk), 1);
-  const int64_t cut = (n_vec + kPassVecs - 1) / kPassVecs;
+inline bool pass_cut(int64_t n_vec, int n_cu, int max_blk, int64_t vecs = kPassVecs) { return (n_vec + vecs - 1) / vecs < pass_most(n_cu, max_blk); }
+inline dim3 pass_grid(int64_t n_vec, int n_tiles, int n_cu, int max_blk, int64_t vecs = kPassVecs) {
+  if (!pass_cut(n_vec, n_cu, max_blk, vecs)) return dim3((unsigned)pass_most(n_cu, max_blk), 1);
+  const int64_t cut = (n_vec + vecs - 1) / vecs;
   return dim3((unsigned)(cut < 1 ? 1 : cut), (unsigned)n_tiles);
 }
 

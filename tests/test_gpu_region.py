@@ -148,44 +148,78 @@ def test_similarity_zero_tensors_many_tiles_and_arguments():
     assert e.value.status == sg.SG_ERR_WORKSPACE
 
 
+def _probes(n, width, seed):
+    """Zeros but for integers 8 .. 15 in vectors where a pass may go wrong: both ends of every run of 256 (threads; unrolled steps and
+    chunks end there too), of every workgroup's slab under either rule of cutting and when walked, a few hundred more, the last
+    vector and every element of the tail behind it.  Element 0 stays 0: the deviation's pivot."""
+    vecs = n // width
+    at = set(range(0, vecs, 256)) | set(range(255, vecs, 256)) | {vecs - 1}
+    for blocks in {-(-vecs // 4096), -(-vecs // 2048), 256}:
+        slab = -(-vecs // blocks)
+        at |= {v for b in range(blocks + 1) for v in (b * slab - 1, b * slab) if 0 <= v < vecs}
+    rng = np.random.default_rng(seed)
+    at = np.array(sorted(at | set(rng.integers(0, vecs, 300).tolist())))
+    where = np.concatenate([at * width + 1 + rng.integers(0, width - 1, at.size), np.arange(vecs * width, n)])
+    x = torch.zeros(n, dtype=torch.float32)
+    x[torch.from_numpy(where)] = torch.from_numpy(rng.integers(8, 16, where.size).astype(np.float32))
+    return x.cuda()
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("vecs", [4095, 4096, 4097, 3 * 4096, 255 * 4096, 255 * 4096 + 1, 256 * 4096 + 7])
+@pytest.mark.parametrize("vecs", [2047, 2048, 2049, 4095, 4096, 4097, 3 * 4096, 255 * 2048, 255 * 2048 + 1, 256 * 2048 + 7,
+                                  255 * 4096, 255 * 4096 + 1, 256 * 4096 + 7])
 def test_passes_over_tiles_cut_side_by_side_or_walked(dtype, vecs):
-    """Both grids of the streaming passes around the size where they change (4,096 vectors per workgroup, a device of 256 compute
-    units), over three tiles: every element is counted exactly once.  Small integers keep all sums exact in fp32 per thread
-    and fp64 across threads; the results below are those sums, rounded once (2^-24)."""
-    n = (vecs * (8 if dtype == "bf16" else 4) + 7) // 8 * 8
-    tiles, olds = [], []
-    for i in range(3):
-        x = (torch.arange(n, device="cuda") % (5 + i)).to(torch_dtype(dtype))
-        tiles.append(x)
-        olds.append((x.float() + 1).to(x.dtype))
+    """Both grids of the streaming passes around the sizes where they change (4,096 vectors per workgroup, 2,048 in the gain refresh, a
+    device of 256 compute units), over three tiles: every element is counted exactly once.  Each sum is carried by a few thousand
+    probes (at most 11,000, of 8 to 15, on a background of zeros), so that one lost or repeated changes the results, which are ratios
+    and square roots of the sums, by 1e-5 of themselves or more.  All terms are small integers: the sums are exact, the results
+    rounded once (2^-24)."""
+    width = 8 if dtype == "bf16" else 4
+    dt = torch_dtype(dtype)
+    n = (vecs * width + 7) // 8 * 8
     ws = torch.empty(sg.sg_workspace_bytes(3), dtype=torch.uint8, device="cuda").fill_(255)
     f = lambda: torch.full((3,), float("nan"), device="cuda")
-    std, l1, cs, scores, change = f(), f(), f(), f(), f()
-    has, rec = torch.ones(3, dtype=torch.uint8, device="cuda"), torch.empty(3, dtype=torch.uint8, device="cuda")
-    sg.sg_tile_std(tiles, std, ws)
-    sg.sg_tile_similarity(tiles, olds, l1, cs, ws)
-    sg.sg_cache_gate(tiles, olds, has, 0.5, scores, rec, ws)
-    state = sg.GainState(3)
-    state.has_prev.fill_(1)
-    out = [t.clone() for t in tiles]
-    delta = [torch.full((n,), 9.0, device="cuda") for _ in tiles]
-    recompute = torch.tensor([1, 0, 1], dtype=torch.uint8, device="cuda")
-    change.fill_(0.25)
-    sg.sg_gain_refresh(out, olds, olds, delta, recompute, change, state, ws)
-    for i, (x, y) in enumerate(zip(tiles, olds)):
-        x, y = x.double(), y.double()
-        want_l1 = float(n / y.sum())                       # |x - y| = 1 everywhere
-        want_cos = float((x * y).sum() / (x.norm() * y.norm()))
-        for got, want in ((std[i], float(x.std(unbiased=False))), (l1[i], want_l1), (cs[i], want_cos), (scores[i], want_l1)):
-            assert abs(float(got) - want) <= 2e-6 * max(1.0, abs(want)), (i, float(got), want)
-        if recompute[i]:
-            assert torch.equal(delta[i], torch.full((n,), -1.0, device="cuda")) and torch.equal(out[i], tiles[i])
-            assert abs(float(state.gain[i]) - want_l1 / 0.25) <= 2e-6 * want_l1 / 0.25
-        else:
-            assert torch.equal(delta[i], torch.full((n,), 9.0, device="cuda"))
-            assert torch.equal(out[i], (olds[i].float() + 9.0).to(olds[i].dtype))
+    has = torch.ones(3, dtype=torch.uint8, device="cuda")
+
+    def near(got, want, what):
+        assert abs(float(got) - want) <= 2e-6 * want, (what, float(got), want)
+
+    # change: probes that differ from a background of ones; level: all ones away from a background of probes
+    for kind in ("change", "level"):
+        for tail in (0, 3):                                  # gate and similarity also take a ragged end
+            probes = [_probes(n + tail, width, 17 * i + vecs) for i in range(3)]
+            olds = [torch.ones_like(p).to(dt) if kind == "change" else p.to(dt) for p in probes]
+            tiles = [(p + 1).to(dt) for p in probes]
+            l1, cs, scores, rec = f(), f(), f(), torch.empty(3, dtype=torch.uint8, device="cuda")
+            sg.sg_tile_similarity(tiles, olds, l1, cs, ws)
+            sg.sg_cache_gate(tiles, olds, has, 0.5, scores, rec, ws)
+            for i, (x, y) in enumerate(zip(tiles, olds)):
+                x, y = x.double(), y.double()
+                want = float((x - y).abs().sum() / y.abs().sum())
+                near(l1[i], want, ("l1", kind, tail, i))
+                near(scores[i], want, ("gate", kind, tail, i))
+                if kind == "level":
+                    near(cs[i], float((x * y).sum() / (x.norm() * y.norm())), ("cosine", tail, i))
+        probes = [_probes(n, width, 17 * i + vecs) for i in range(3)]
+        olds = [torch.ones_like(p).to(dt) if kind == "change" else p.to(dt) for p in probes]
+        tiles = [(p + 1).to(dt) for p in probes]
+        std = f()
+        sg.sg_tile_std([p.to(dt) for p in probes], std, ws)
+        state = sg.GainState(3)
+        state.has_prev.fill_(1)
+        out = [t.clone() for t in tiles]
+        delta = [torch.full((n,), 9.0, device="cuda") for _ in tiles]
+        recompute = torch.tensor([1, 0, 1], dtype=torch.uint8, device="cuda")
+        change = torch.full((3,), 0.25, device="cuda")
+        sg.sg_gain_refresh(out, olds, olds, delta, recompute, change, state, ws)
+        for i, (x, y) in enumerate(zip(tiles, olds)):
+            near(std[i], float(probes[i].double().std(unbiased=False)), ("std", i))
+            if recompute[i]:
+                assert torch.equal(delta[i], x.float() - y.float()) and torch.equal(out[i], x)
+                near(state.gain[i], float((x.double() - y.double()).abs().sum() / y.double().abs().sum()) / 0.25, ("gain", kind, i))
+            else:
+                assert torch.equal(delta[i], torch.full((n,), 9.0, device="cuda"))
+                assert torch.equal(out[i], (y.float() + 9.0).to(dt))
 
 
 def test_sums_of_small_tiles_are_rounded_once():

@@ -169,7 +169,7 @@ def test_canvas_step_gathers_tiles_when_given_a_workspace(dtype, shift, room):
 WRAP_CASES = [
     # name, T, H, W, th, tw, sh, sw, heads, d, dtype, token_major, shift
     ("bf16_w16_rows_and_cols", 3, 20, 40, 12, 16, 8, 8, 2, 128, "bf16", False, (5, 9)),      # N = 576; tile width 16
-    ("bf16_w13_odd", 2, 17, 21, 9, 13, 8, 8, 2, 128, "bf16", False, (16, 20)),               # odd width: per-lane walk either way
+    ("bf16_w13_odd", 2, 17, 21, 9, 13, 8, 8, 2, 128, "bf16", False, (16, 20)),               # odd width: runs break either way
     ("bf16_paper_nonoverlap", 2, 12, 24, 6, 8, 6, 8, 2, 128, "bf16", False, (1, 1)),         # the paper's partition, shift tile/…
     ("bf16_token_major", 2, 12, 24, 6, 8, 6, 8, 3, 128, "bf16", True, (7, 3)),
     ("bf16_d64", 2, 12, 24, 6, 8, 6, 8, 2, 64, "bf16", False, (2, 21)),                      # head_dim 64 in place: register-staged kernel

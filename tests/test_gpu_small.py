@@ -97,7 +97,7 @@ BF16_CASES = [
     ("view_3x3", 2, 20, 40, 12, 24, 4, 8, 2),           # N = 576, triple row coverage; tile width 24: scalar walk, several row wraps per stage
     ("view_w72", 2, 8, 136, 6, 72, 2, 64, 2),           # N = 864, tile width 72 >= one stage: scalar walk, at most one wrap per stage
     ("view_w8", 3, 40, 12, 32, 8, 8, 4, 1),             # N = 768, tile width 8: eight row wraps per stage, frame wraps
-    ("view_w3", 7, 9, 5, 5, 3, 4, 2, 2),                # N = 105, tile width 3: per-lane cursors wrap many rows and frames per stage
+    ("view_w3", 7, 9, 5, 5, 3, 4, 2, 2),                # N = 105, tile width 3: narrower than a run of 8 tokens, which are looked up one by one
     ("view_w1", 9, 4, 3, 4, 1, 4, 1, 1),                # N = 36, tile width 1: every token is its own tile row
 ]
 
@@ -115,8 +115,8 @@ def test_attention_bf16_small(case):
 
 @pytest.mark.parametrize("case", BF16_CASES, ids=[c[0] for c in BF16_CASES])
 def test_attention_bf16_head_dim_64(case):
-    """head_dim 64 (the head width of CogVideoX-1.5, Section 8 "Workloads") in bf16: the same cases through the
-    register-staged kernel, packed and in place."""
+    """head_dim 64 (the head width of CogVideoX-1.5, Section 8 "Workloads") in bf16: the same cases, packed through
+    the streaming kernel; in place up to 384 tokens through the register-staged one."""
     name, T, H, W, th, tw, sh, sw, heads = case
     g = _geom(name, T, H, W, th, tw, sh, sw, heads, 64, "bf16", 23)
     q, k, v = canvas_qkv(g)
@@ -157,27 +157,49 @@ def test_attention_token_major_layout(dtype, d, tw):
     assert_close(to_f64(out), oracle_tile_attention_full(g, *qkv_hm, 1, 1), dtype)
 
 
-@pytest.mark.parametrize("tw", [20, 24], ids=["per_lane_rows", "scalar_walk"])
-def test_attention_bf16_wide_token_stride_takes_general_addressing(tw):
-    """A canvas whose per-head extent exceeds 4 GiB (token stride of 2^20 elements): a tile width that is
-    not a multiple of 8 goes to the kernel with 64-bit per-lane addressing, a multiple of 8 stays on the
-    streaming kernel, whose scalar walk is 64-bit; same numbers as the oracle either way."""
-    g = _geom("wide", 2, 32, 2 * tw, 16, tw, 16, tw, 1, 128, "bf16", 71)      # N = 640 / 768
-    stride = 1 << 20
+def _strided(canvases, g, stride):
+    """The canvases (one head) in one buffer, their tokens `stride` elements apart and side by side in every token."""
+    buf = torch.empty(g.grid_tokens * stride, dtype=canvases[0].dtype, device="cuda")
+    out = [buf[i * g.head_dim:] for i in range(3)]
+    for o, t in zip(out, canvases):
+        o.as_strided((g.grid_tokens, g.head_dim), (stride, 1)).copy_(t.reshape(g.grid_tokens, g.head_dim))
+    return out
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("tw", [20, 24, 13], ids=["broken_runs", "unbroken_runs", "narrow"])
+@pytest.mark.parametrize("shift", [(0, 0), (5, 7)], ids=["fixed", "wrapped"])
+def test_attention_bf16_wide_token_stride_takes_general_addressing(shift, tw, d):
+    """A canvas whose per-head extent exceeds 4 GiB (token stride of 2^21 elements), tiles of 416 to 768 tokens, so that head_dim 64 takes
+    the streaming kernel too.  Windows whose runs of tokens break (head_dim 128: width 20 and 13, or wrapping; head_dim 64, runs of 16:
+    any) look every such run's tokens up with 64-bit addresses; whole runs, and unbroken windows of head_dim 128 and width 24, go by
+    a wave-uniform 64-bit pointer.  13 tokens are fewer than a run of head_dim 64.  Same numbers as the oracle every time."""
+    g = _geom("wide", 2, 32, 2 * tw, 16, tw, 16, tw, 1, d, "bf16", 71)
     dense = canvas_qkv(g)
-    wide = []
-    for t in dense:
-        buf = torch.empty(g.grid_tokens * stride, dtype=torch.bfloat16, device="cuda")
-        view = buf.as_strided((g.grid_tokens, g.head_dim), (stride, 1))
-        view.copy_(t.reshape(g.grid_tokens, g.head_dim))
-        wide.append(buf)
-    p = sg.make_problem(g)
-    p.grid_stride_token = stride
-    p.grid_stride_head = 128                      # one head; any positive multiple of 8
+    wide = _strided(dense, g, 1 << 21)
+    p = sg.make_problem(g, shift=shift)
+    p.grid_stride_token = 1 << 21
+    p.grid_stride_head = d                        # one head; any positive multiple of 8
     assert sg.sg_problem_validate(p) == sg.SG_OK
     out = torch.empty(g.tile_shape, dtype=torch.bfloat16, device="cuda")
     sg.sg_tile_attention(p, *wide, 1, 1, out)
-    assert_close(to_f64(out), oracle_tile_attention_full(g, *dense, 1, 1), "bf16")
+    win = [oracle.slice_tile_shifted(to_f64(t), g, 1, 1, *shift).reshape(-1, d) for t in dense]
+    assert_close(to_f64(out), oracle.attention(*win, g.scale).reshape(g.tile_shape), "bf16")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("packed", [True, False], ids=["packed", "window"])
+def test_attention_bf16_tokens_too_far_apart_for_lane_offsets(packed, d):
+    """A token stride of 2^26 elements: the 16 tokens of a run span more than 4 GiB, so a lane's offset inside it leaves 32 bits.  A tile
+    that is the whole canvas is then read as a window of itself, and every token is looked up."""
+    g = _geom("far", 1, 10, 13, 10, 13, 10, 13, 1, d, "bf16", 73) if packed else _geom("far", 1, 10, 26, 10, 13, 10, 13, 1, d, "bf16", 73)
+    dense = canvas_qkv(g)
+    p = sg.make_problem(g)
+    p.grid_stride_token = 1 << 26
+    p.grid_stride_head = d
+    out = torch.empty(g.tile_shape, dtype=torch.bfloat16, device="cuda")
+    sg.sg_tile_attention(p, *_strided(dense, g, 1 << 26), 0, g.n_tile_cols - 1, out)
+    assert_close(to_f64(out), oracle_tile_attention_full(g, *dense, 0, g.n_tile_cols - 1), "bf16")
 
 
 @pytest.mark.parametrize("T,th,tw", [(9, 10, 8), (1, 1, 704), (5, 1, 136), (3, 20, 16), (2, 9, 56), (1, 11, 64), (3, 5, 72), (2, 3, 128),
@@ -431,7 +453,7 @@ def test_step_cached_mode_bf16_three_steps(d):
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("heads,N", [(1, 100), (2, 129), (25, 1124), (26, 1124), (40, 1030), (56, 1030), (52, 1281)])
 def test_attention_bf16_whole_and_halved_rounds(heads, N, d):
-    """Query blocks dealt whole and, in a last round that fills at most half of the compute units, as halves: 5 to 130 workgroups
+    """Query blocks dealt whole and, in a last round that fills at most half of the compute units, as halves: 1 to 130 workgroups
     (halved up to 128 on 256 compute units), 200 (whole), 280 and 312 (a whole round, and 24 / 56 halved), with last blocks of 1,
     6 and 100 rows, so that second halves are empty; every row of the first, the middle and the last head."""
     g = _geom("hv", 1, 1, N, 1, N, 1, N, heads, d, "bf16", 4000 + heads)

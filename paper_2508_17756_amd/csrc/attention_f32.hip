@@ -5,11 +5,11 @@
 // A workgroup owns QB x 32 query rows of one head and its KS wavefronts split the keys (wavefront w takes the
 // 32-key blocks w, w + KS, ...), so that even one tile of a few hundred tokens gives every SIMD of its compute
 // units work, and no workgroup barrier stands in the key loop: every wavefront moves its own K blocks into
-// its own part of LDS (direct global->LDS transfers; K of the next block is requested when QK is done and has the
-// length of PV to arrive), reads its V rows straight into registers a few key pairs ahead, and keeps its own softmax
-// state; the KS states of a query are merged through LDS at the end.  Two wavefronts per SIMD cover each other's softmax
-// and waits.  (One wavefront per SIMD with 64 queries and V in LDS as well, which halves what is read per FLOP, spills
-// its 512 registers around the rescaling of the accumulators: 2.14 ms where this takes 1.20.)
+// its own part of LDS (direct global->LDS transfers; K of the next block is requested when QK is done and, as
+// transfers complete in order, has to arrive before the first V rows, which are requested behind it: it has the length of
+// the softmax), reads its V rows straight into registers a few key pairs ahead, and keeps its own softmax state; the KS
+// states of a query are merged through LDS at the end.  Two wavefronts per SIMD cover each other's softmax and waits.  (One wavefront per SIMD with 64 queries and V in LDS as well, which halves what is read per FLOP, spills
+// its 512 registers around the rescaling of the accumulators: 2.14 ms where this takes 1.21.)
 //
 // Transposed products, S^T = K Q^T and O^T = V^T P^T, keep the probabilities in their lanes: accumulator register r
 // of S^T holds, for the lane's query, key 8 (r >> 2) + (r & 3) in the lower and that key + 4 in the upper half of the
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(64 * KS, 2) void attention_f32_kernel(
     else if constexpr (kPer == 4) return __builtin_bit_cast(vrow, __builtin_amdgcn_raw_buffer_load_b128(vbuf, o * 32 + lq * 16, 0, 0));
     else return __builtin_bit_cast(vrow, __builtin_amdgcn_raw_buffer_load_b64(vbuf, o * 32 + lq * 8, 0, 0));
   };
-  constexpr int kAhead = 4;   // key pairs whose V rows are in flight: 1,024 cycles of matrix work
+  constexpr int kAhead = 4;   // key pairs whose V rows are in flight: 1,024 cycles of matrix work (head_dim 64, one query block: 512)
   auto reads_done = [&]() SG_INLINE {   // this wavefront's fragment reads have returned: the block may be overwritten
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -348,8 +348,8 @@ int launch_attention_f32(const TileView& tv, int heads, int head_dim, float scal
     // 64 queries per workgroup (head_dim 64, heads within 32-bit offsets: the registers hold them) read K and V half as often as 32 but make half as many
     // workgroups: taken where their rounds over the device are not longer.  Then 4 shares of the keys, two workgroups per
     // compute unit, where there are that many workgroups: one's start, end and uneven last blocks run beside the other's loop.
-    // Fewer workgroups take 8 shares, which halves the time of each.  (4 x 2,880 tokens, 8 heads x 128, 2,880 workgroups: 1.30 ms
-    // a step with 8 shares, 1.20 with 4.)
+    // Fewer workgroups take 8 shares, which halves the time of each.  (4 x 2,880 tokens, 8 heads x 128, 2,880 workgroups: 8 % more
+    // a step with 8 shares than with 4.)
     const int64_t wg1 = (int64_t)n * heads * ((tv.N + 31) / 32), wg2 = (int64_t)n * heads * ((tv.N + 63) / 64);
     const bool two_blocks = head_dim == 64 && !far && 2 * ((wg2 + n_cu - 1) / n_cu) <= (wg1 + n_cu - 1) / n_cu;
     const int64_t total = two_blocks ? wg2 : wg1;

@@ -3,9 +3,9 @@
 // (Equation 7: score >= threshold recomputes).
 //
 // Pure HBM streaming: each input element is read once.  Stage 1 runs one workgroup per compute
-// unit; a thread sums |a-b| and |b| in fp32 over its 16-byte vectors, each wavefront adds its
-// threads in fp64 and stores one (num, den) pair per tile.  Stage 2 adds the pairs of a tile in
-// a fixed order in fp64, so the score is bit-reproducible run to run on a given device.
+// unit, or cuts small tiles into workgroups side by side (pass_grid); a thread sums |a-b| and |b| in fp32
+// over its 16-byte vectors (of a cut tile: per vector, and its vectors in fp64), each wavefront adds its threads
+// in fp64 and stores one (num, den) pair per tile.  Stage 2 adds the pairs of a tile in a fixed order in fp64, so the score is bit-reproducible run to run on a given device.
 #include "sg_common.h"
 
 namespace sg {
@@ -48,10 +48,9 @@ __device__ __forceinline__ void accum_vec(const u32x4 a, const u32x4 b, double& 
   den_sum += (double)den;
 }
 
-// One resident workgroup per compute unit walks the tiles of the launch one after the other; within a tile
-// workgroup b streams the b-th of gridDim.x equal contiguous slabs of both buffers.  Every workgroup
-// therefore carries the same load, no tail of late workgroups forms, and each buffer is read as
-// gridDim.x long sequential streams.
+// Workgroup (b, y) streams the b-th of gridDim.x equal contiguous slabs of both buffers of tiles y, y + gridDim.y, ...
+// Large tiles (gridDim.y = 1): one resident workgroup per compute unit walks them one after the other, so that
+// every workgroup carries the same load and no tail of late ones forms.  Small tiles: all side by side.
 template <int DT, bool CUT>
 __global__ __launch_bounds__(kThreads) void gate_partial_kernel(GatePtrs ptrs, const uint8_t* __restrict__ has_cache,
                                                                 int tile0, int n_tiles, int64_t elems,
@@ -292,7 +291,8 @@ struct GainPtrs {
 //   recomputed tile: delta_c = O_t - I_t (fp32) is stored and, if a previous output exists, the sums of
 //                    ||O_t - O_{t-1}||_1 and ||O_{t-1}||_1 are taken in the same pass (O_t is read once);
 //   reused tile:     O_t = I_t + delta_c is written (Residual Approximation).
-// One workgroup per compute unit; the workgroups walk each tile's buffers together, chunk by chunk.
+// The workgroups of a tile walk its buffers together, chunk by chunk: one per compute unit and the tiles one after the
+// other, or small tiles side by side (pass_grid).
 // delta is kept in fp32: its magnitude follows the latent's and can exceed the output's by orders, so
 // the output's storage type would lose O_c.
 template <int DT, bool CUT>

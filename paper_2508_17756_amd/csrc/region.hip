@@ -3,7 +3,7 @@
 // per-tile thresholds tau_i = tau_base * (1 + delta_i) of the "MaxMin" or "TopSelect" policy.
 //
 // The standard deviation is one streaming read of the tile outputs (HBM-bound, same layout as the
-// cache gate: one resident workgroup per compute unit, equal contiguous slabs per tile); the
+// cache gate: equal contiguous slabs per tile, large tiles walked, small ones side by side); the
 // tracker and the policy are a few operations per tile and run in a single workgroup, so that
 // nothing has to be read back between the steps.
 #include "sg_common.h"

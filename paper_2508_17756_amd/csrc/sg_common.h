@@ -36,11 +36,10 @@ struct AttnBatch {
   const int32_t* x0;
   const uint8_t* run_flags;  // device, n_tiles bytes: tiles with a 0 are skipped; nullptr = all tiles run
   // Cache refresh of the tiled step, carried out by the same launch where the kernel supports it (*refreshed is
-  // then set): for every tile that runs, refresh_dst[i] <- the refresh_bytes at q[i] (a packed tile input: Q, K, V
-  // one after the other) and has_cache[i] <- 1.  All nullptr / 0 when no refresh is asked for.
+  // then set): for every tile that runs, refresh_dst[i] <- its packed input (Q, K and V of all heads; k[i] and v[i] lie as far
+  // behind q[i] as their copies behind refresh_dst[i]) and has_cache[i] <- 1.  All nullptr when no refresh is asked for.
   void* const* refresh_dst;  // host array of n_tiles device pointers
   uint8_t* has_cache;        // device, n_tiles bytes
-  int64_t refresh_bytes;     // a multiple of 16
   bool* refreshed;           // host, out
 };
 
@@ -70,7 +69,7 @@ int launch_region_thresholds(const float* tile_std, double* track_mean, int32_t*
 int launch_cache_refresh(const void* const* src, void* const* dst, const uint8_t* recompute,
                          uint8_t* has_cache, int n_tiles, int64_t bytes_per_tile, hipStream_t s);
 
-// Gate scratch: per tile kGateSlots (num, den) fp64 pairs, one per workgroup of the partial-sum kernel.
+// Gate scratch: per tile kGateSlots (num, den) fp64 pairs, one per wavefront of the partial-sum kernel.
 constexpr int kGateSlots = 1024;
 inline size_t gate_workspace_bytes(int n_tiles) {
   return (size_t)(n_tiles > 0 ? n_tiles : 1) * kGateSlots * 2 * sizeof(double);

@@ -3,10 +3,10 @@
 // <x_new, x_old> / (||x_new||_2 ||x_old||_2).  The paper profiles predicted noise and cache residuals with this
 // pair to choose what to cache and where to put the thresholds (Section 3; Section 5.1).
 //
-// One streaming read of both tensors (HBM-bound, the cache gate's layout: one resident workgroup per compute
-// unit, equal contiguous slabs per tile).  A thread keeps the five sums in fp32 over its 16-byte vectors, the
-// wavefronts add them in fp64, the four wavefronts of a workgroup meet in LDS, and the finalize kernel adds the
-// workgroups' partials in a fixed order: bit-reproducible from run to run on a given device.
+// One streaming read of both tensors (HBM-bound, the cache gate's layout: equal contiguous slabs per tile, large tiles walked,
+// small ones side by side).  A thread keeps the five sums in fp32 over its 16-byte vectors (of a cut tile: per vector, and its
+// vectors in fp64), the wavefronts add them in fp64, the four wavefronts of a workgroup meet in LDS, and the finalize kernel adds
+// the workgroups' partials in a fixed order: bit-reproducible from run to run on a given device.
 #include "sg_common.h"
 
 namespace sg {

@@ -8,8 +8,9 @@
 // its own part of LDS (direct global->LDS transfers; K of the next block is requested when QK is done and, as
 // transfers complete in order, has to arrive before the first V rows, which are requested behind it: it has the length of
 // the softmax), reads its V rows straight into registers a few key pairs ahead, and keeps its own softmax state; the KS
-// states of a query are merged through LDS at the end.  Two wavefronts per SIMD cover each other's softmax and waits.  (One wavefront per SIMD with 64 queries and V in LDS as well, which halves what is read per FLOP, spills
-// its 512 registers around the rescaling of the accumulators: 2.14 ms where this takes 1.21.)
+// states of a query are merged through LDS at the end.  Two wavefronts per SIMD cover each other's softmax and waits.  (One
+// wavefront per SIMD with 64 queries and V in LDS as well, which halves what is read per FLOP, spills its 512 registers around
+// the rescaling of the accumulators: 2.14 ms where this takes 1.22.)
 //
 // Transposed products, S^T = K Q^T and O^T = V^T P^T, keep the probabilities in their lanes: accumulator register r
 // of S^T holds, for the lane's query, key 8 (r >> 2) + (r & 3) in the lower and that key + 4 in the upper half of the
@@ -19,7 +20,7 @@
 //
 // Bound: matrix pipe (per 32 x 32 block and head_dim 128: 128 instructions of 64 cycles against 32 fragment reads
 // and 16 exponentials a lane).  Measured, before (vector ALU, keys and values broadcast from LDS) -> now, whole steps:
-// 4 tiles of 2,880 tokens, 8 heads x 128: 7.35 -> 1.21 ms (114 TFLOP/s in the kernel); 4 tiles of 300 tokens,
+// 4 tiles of 2,880 tokens, 8 heads x 128: 7.35 -> 1.22 ms (113 TFLOP/s in the kernel); 4 tiles of 300 tokens,
 // 2 heads x 64: 75.6 -> 17.6 us.
 #include <atomic>
 #include "attention_common.h"
@@ -221,7 +222,7 @@ __global__ __launch_bounds__(64 * KS, 2) void attention_f32_kernel(
       mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
       if (__any(!(mx <= ref[qb]))) {   // also the first block, where the reference is -inf
         const float moved = fmaxf(ref[qb], mx);
-        const float alpha = (ref[qb] == moved) ? 1.f : __builtin_amdgcn_exp2f((ref[qb] - moved) * kLog2e);
+        const float alpha = (ref[qb] == moved) ? 1.f : exp2f((ref[qb] - moved) * kLog2e);
         ref[qb] = moved;
         l[qb] *= alpha;
 #pragma unroll
@@ -229,8 +230,19 @@ __global__ __launch_bounds__(64 * KS, 2) void attention_f32_kernel(
       }
       float l0 = 0.f, l1 = 0.f;
       const float base = (ref[qb] == -__builtin_inff()) ? 0.f : ref[qb];   // all scores of this share -inf so far: probabilities 0
+      // The exponential instruction returns 0 for results below 2^-126.  Where a score lies that far below the reference (or at -inf), the
+      // function that returns them is called: times a value near the largest number they still count.  (Called always it costs
+      // 2.5 %, this way 0.7 %.)
+      float mn = p[qb][0];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) p[qb][r] = __builtin_amdgcn_exp2f((p[qb][r] - base) * kLog2e);
+      for (int r = 1; r < 16; ++r) mn = fminf(mn, p[qb][r]);
+      if (__builtin_expect(__any(mn - base < -87.f), 0)) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) p[qb][r] = exp2f((p[qb][r] - base) * kLog2e);
+      } else {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) p[qb][r] = __builtin_amdgcn_exp2f((p[qb][r] - base) * kLog2e);
+      }
 #pragma unroll
       for (int r = 0; r < 16; r += 2) { l0 += p[qb][r]; l1 += p[qb][r + 1]; }
       l[qb] += l0 + l1;
@@ -289,7 +301,7 @@ __global__ __launch_bounds__(64 * KS, 2) void attention_f32_kernel(
 #pragma unroll
     for (int w = 0; w < KS; ++w) {
       const float rw = s_ref[w * (QB * 32) + q];
-      wgt[w] = (rw == -__builtin_inff()) ? 0.f : __builtin_amdgcn_exp2f((rw - top) * kLog2e);
+      wgt[w] = (rw == -__builtin_inff()) ? 0.f : exp2f((rw - top) * kLog2e);
       sum += wgt[w] * s_sum[w * (QB * 32) + q];
     }
     const float inv = 1.0f / sum;

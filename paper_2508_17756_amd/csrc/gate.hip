@@ -5,7 +5,8 @@
 // Pure HBM streaming: each input element is read once.  Stage 1 runs one workgroup per compute
 // unit, or cuts small tiles into workgroups side by side (pass_grid); a thread sums |a-b| and |b| in fp32
 // over its 16-byte vectors (of a cut tile: per vector, and its vectors in fp64), each wavefront adds its threads
-// in fp64 and stores one (num, den) pair per tile.  Stage 2 adds the pairs of a tile in a fixed order in fp64, so the score is bit-reproducible run to run on a given device.
+// in fp64 and stores one (num, den) pair per tile.  Stage 2 adds the pairs of a tile in a fixed order in fp64, so
+// the score is bit-reproducible run to run on a given device.
 #include "sg_common.h"
 
 namespace sg {

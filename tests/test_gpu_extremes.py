@@ -177,6 +177,23 @@ def test_fp32_attention_takes_values_up_to_the_largest_number(d, heads):
     assert float((got / want - 1.0).abs().max()) <= 1e-5
 
 
+@pytest.mark.parametrize("key", [1, 40, 261])
+@pytest.mark.parametrize("heads", [1, 48])
+@pytest.mark.parametrize("d", [64, 128])
+def test_fp32_attention_counts_probabilities_below_the_normal_range(d, heads, key):
+    """A key 90 below the maximum has probability 8e-40: times 3e38 it is 0.25, in the block of the maximum, another share of the keys and
+    a later block of the same share.  The rounding of the exponent (130 +- 2^-17) and of the probability (2^-150) allow 7e-6."""
+    n = 400
+    q, k, v = torch.zeros(heads, n, d), torch.zeros(heads, n, d), torch.zeros(heads, n, d)
+    q[:, :, 0] = math.sqrt(d)
+    k[:, :, 0] = -200.0
+    k[:, 0, 0] = 0.0
+    k[:, key, 0] = -90.0
+    v[:, key] = 3e38
+    got = _attend_window("f32", d, heads, 1, 16, 25, q, k, v, packed=True).double()
+    assert float((got / (3e38 * math.exp(-90.0)) - 1.0).abs().max()) <= 1.2e-5
+
+
 @pytest.mark.parametrize("block", [0, 1, 4, 11, 12])
 @pytest.mark.parametrize("heads", [1, 48])
 @pytest.mark.parametrize("d", [64, 128])

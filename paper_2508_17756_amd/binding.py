@@ -168,12 +168,30 @@ def _dtype_code(t):
     raise TypeError("tensors must be float32 or bfloat16")
 
 
+def _stream_getter(torch):
+    """The shortest way to the hipStream_t of the current stream of the current device that this torch has.  The raw getters are no
+    public interface: where they are missing the stream comes through a Stream object."""
+    cuda = torch.cuda
+    raw, device = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+    if raw is None or device is None:
+        return lambda: cuda.current_stream().cuda_stream
+
+    def get():
+        if not cuda.is_initialized():
+            cuda.init()
+        return raw(device())
+    return get
+
+
+_STREAM = None
+
+
 def _stream():
     """hipStream_t of the current stream of the current device, as an integer."""
-    c = _torch()._C
-    if not _TORCH.cuda.is_initialized():
-        _TORCH.cuda.init()
-    return c._cuda_getCurrentRawStream(c._cuda_getDevice())
+    global _STREAM
+    if _STREAM is None:
+        _STREAM = _stream_getter(_torch())
+    return _STREAM()
 
 
 def _ptr(t):

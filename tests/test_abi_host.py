@@ -205,3 +205,16 @@ def test_partition_tiles_follows_the_oracle_and_leaves_the_problem_alone_on_fail
     before = bytes(p)
     assert lib.sg_partition_tiles(ctypes.byref(p), 10, 10, 0, 0) == sg.SG_ERR_UNSUPPORTED and bytes(p) == before   # 900 tiles
     assert lib.sg_partition_tiles(None, 10, 10, 0, 0) == sg.SG_ERR_INVALID_ARG
+
+
+def test_stream_handle_without_the_raw_getters():
+    """The binding asks torch for the raw stream of the current device; a torch that lacks those private functions still gives it."""
+    from types import SimpleNamespace as NS
+    from paper_2508_17756_amd.binding import _stream_getter
+    started = []
+    cuda = NS(is_initialized=lambda: bool(started), init=lambda: started.append(1),
+              current_stream=lambda: NS(cuda_stream=77))
+    raw = NS(_cuda_getCurrentRawStream=lambda device: 100 + device, _cuda_getDevice=lambda: 3)
+    assert _stream_getter(NS(cuda=cuda, _C=raw))() == 103 and started == [1]
+    assert _stream_getter(NS(cuda=cuda, _C=NS()))() == 77
+    assert _stream_getter(NS(cuda=cuda, _C=NS(_cuda_getDevice=lambda: 3)))() == 77

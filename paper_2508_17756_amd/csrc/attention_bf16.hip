@@ -234,7 +234,7 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
   // between its MFMAs.
   // Measured on 4 x 5 tiles of 75,600 tokens, 40 heads x 128: 1,744 ms a step walked, 1,764 under a shift that makes windows wrap
   // and so planned (1,792 when every lane formed its token's offset from wrapped coordinates each stage), 1,731 gathered and packed;
-  // on 2 x 2 shifted tiles of 17,550 tokens, 48 heads x 64: 18.5 ms (22.3 with register-staged loads).
+  // on 2 x 2 shifted tiles of 17,550 tokens, 48 heads x 64: 17.7 ms (21.8 with register-staged loads).
   constexpr int kTok = kKeys / kWaves;   // tokens per wavefront and stage: 8 (head_dim 64: 16)
   auto slot_token = [&](int l, int u, bool is_v, uint32_t& chunk) SG_INLINE -> int {   // what lane l moves: token of the run, chunk of it
     const int slot_w = 4 * u + (l >> 4), row = 8 * wave + slot_w;
@@ -527,8 +527,8 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
   // Late scaling keeps the true running maximum, every 64 keys: the dominating probability of a query is then exactly 1, which
   // bf16 holds without an error, and none is above it, so sums of p v stay finite for every finite v.  Error against fp64 at
   // 400, 1,200 and 17,550 tokens: 2.17e-3, 2.22e-3, 2.30e-3; with one maximum per stage of 128 keys 2.18e-3, 2.23e-3, 2.30e-3; with
-  // the lazy reference below 2.28e-3, 2.32e-3, 2.34e-3.  The step of 4 x 17,550 tokens, 48 heads, is 1.20 times as fast as with
-  // the register-staged kernel (22.3 -> 18.5 ms); the other two would be 1.24 and 1.33 times as fast.
+  // the lazy reference below 2.28e-3, 2.32e-3, 2.34e-3.  The step of 4 x 17,550 tokens, 48 heads, is 1.20 - 1.23 times as fast as
+  // with the register-staged kernel (21.8 -> 17.7 ms); the other two would be 1.25 and 1.28 - 1.33 times as fast.
   auto late_half = [&](auto h_tag, bf16x8 (&p)[2 * kMaxSB]) SG_INLINE {
     constexpr int H = decltype(h_tag)::value;
     const float top = fmaxf(sm.M, block_max<2, 2 * H>(s) * c_log2);
@@ -809,8 +809,18 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
 int launch_attention_bf16(const TileView& tv, int heads, int head_dim, float scale, const AttnBatch& b, hipStream_t s) {
   if (head_dim != 128 && head_dim != 64) return SG_ERR_UNSUPPORTED;
   if (b.n_tiles <= 0) return SG_OK;
-  // three stages of 128 keys and fewer do not fill the pipeline: measured in attention_bf16_short.hip
-  if (head_dim == 64 && tv.window && tv.N <= 384) return launch_attention_bf16_short(tv, heads, scale, b, s);
+  int dev = 0, n_cu = 0;
+  SG_HIP_TRY(hipGetDevice(&dev));
+  SG_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
+  // Windows of head_dim 64 that do not fill the pipeline of the streaming kernel take the register-staged one: up to 448 tokens, and up to
+  // 1,200 where there are workgroups for more than half of the compute units.  (Fewer are dealt as halves here, which the other does
+  // not do.)  Register-staged and streaming, us a step: 9 tiles, 24 heads, of 400 tokens 34.4 and 42.9, of 600 57.7 and 64.4, of 900
+  // 103 and 109, of 1,200 152 and 155, of 1,500 224 and 218; 20 tiles of 1,200 308 and 327; 4 tiles, 8 heads, of 400 tokens 17.5 and
+  // 18.6, of 512 18.7 and 17.7, of 1,024 30.8 and 27.0.
+  if (head_dim == 64 && tv.window) {
+    const int64_t workgroups = (int64_t)b.n_tiles * heads * ((tv.N + kBR - 1) / kBR);
+    if (tv.N <= 448 || (tv.N <= 1200 && 2 * workgroups > n_cu)) return launch_attention_bf16_short(tv, heads, scale, b, s);
+  }
   const View16 vw = make_view16(tv);
   // Windows of head_dim 128 whose runs of 8 tokens all lie side by side (width a multiple of 8, none of the launch crosses a canvas
   // edge) are walked.  A step of 20 tiles of 75,600 tokens, 40 heads: 1,744 ms walked, 1,793 - 1,817 planned, 1,731 gathered and
@@ -829,9 +839,6 @@ int launch_attention_bf16(const TileView& tv, int heads, int head_dim, float sca
   // the kernels need more dynamic LDS than the default limit; the attribute is set once per device and kernel
   constexpr int kMaxDevices = 64;
   static std::atomic<bool> attr_set[kMaxDevices][8];   // zero-initialised; set twice by racing threads is harmless
-  int dev = 0, n_cu = 0;
-  SG_HIP_TRY(hipGetDevice(&dev));
-  SG_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
   const int cu_per_xcd = n_cu / kXcd > 0 ? n_cu / kXcd : 1;
   // the cache refresh rides on this launch for packed tiles (their inputs are one contiguous run each)
   const bool fuse_refresh = b.refresh_dst && b.has_cache && !window;

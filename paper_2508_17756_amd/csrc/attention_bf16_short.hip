@@ -1,9 +1,8 @@
 // Tile attention on the matrix cores for short tiles of head_dim 64 read in place from a canvas (paper Section 2.1 "full
 // attention" over one tile's T x tile_h x tile_w tokens; Section 3: tiles exchange no Q/K/V).  The streaming kernel in
 // attention_bf16.hip takes everything else: it has a pipeline of stages to fill and several times the code to fetch before its
-// loop runs at its rate, which tiles of up to three of its stages never reach.  9 tiles, 24 heads, a step, this kernel and that
-// one: 300 tokens 29.6 and 34.6 us, 600 tokens 65.0 and 61.0.  (Held to 128 registers for two workgroups per compute unit
-// it spills: 33.4 us.)
+// loop runs at its rate.  The sizes at which one takes over from the other, and both sides' times, stand at its launcher.  (Held to 128
+// registers for two workgroups per compute unit this kernel spills: 9 tiles of 300 tokens, 24 heads, 33.4 us for 29.6.)
 //
 // Flash-style: a workgroup owns 256 query rows of one head (8 wavefronts x 32 rows) and streams
 // the tile's keys and values through LDS 64 at a time; the N x N score matrix is never stored.

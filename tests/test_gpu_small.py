@@ -116,13 +116,25 @@ def test_attention_bf16_small(case):
 @pytest.mark.parametrize("case", BF16_CASES, ids=[c[0] for c in BF16_CASES])
 def test_attention_bf16_head_dim_64(case):
     """head_dim 64 (the head width of CogVideoX-1.5, Section 8 "Workloads") in bf16: the same cases, packed through
-    the streaming kernel; in place up to 384 tokens through the register-staged one."""
+    the streaming kernel; in place up to 448 tokens through the register-staged one."""
     name, T, H, W, th, tw, sh, sw, heads = case
     g = _geom(name, T, H, W, th, tw, sh, sw, heads, 64, "bf16", 23)
     q, k, v = canvas_qkv(g)
     for tr, tc in {(0, 0), (g.n_tile_rows - 1, g.n_tile_cols - 1)}:
         got = gpu_tile_attention(g, q, k, v, tr, tc)
         assert_close(to_f64(got), oracle_tile_attention_full(g, q, k, v, tr, tc), "bf16", f"{name} {tr},{tc}")
+
+
+@pytest.mark.parametrize("heads,th,tw", [(2, 16, 28), (2, 20, 23), (64, 14, 33), (65, 14, 33), (25, 24, 50), (26, 24, 50), (26, 25, 49)])
+def test_attention_bf16_head_dim_64_windows_around_the_kernels_sizes(heads, th, tw):
+    """Windows of head_dim 64 on either side of the rule that picks the kernel: 448 and 460 tokens with few workgroups; 462 tokens with 128
+    and 130 of them on 256 compute units, 1,200 with 125 and 130, 1,225 with 130."""
+    g = _geom("rule", 1, 2 * th, 2 * tw, th, tw, th, tw, heads, 64, "bf16", 29 + heads)
+    q, k, v = canvas_qkv(g)
+    out = gpu_tile_attention(g, q, k, v, 1, 0)
+    for a in (0, heads - 1):
+        win = [oracle.slice_tile(to_f64(t[a:a + 1]), g, 1, 0).reshape(-1, 64) for t in (q, k, v)]
+        assert_close(to_f64(out[a]).reshape(-1, 64), oracle.attention(*win, g.scale), "bf16", a)
 
 
 @pytest.mark.parametrize("shape", [(3, 20, 25), (2, 33, 37), (4, 16, 32)], ids=["n1500", "n2442", "n2048"])
@@ -170,11 +182,11 @@ def _strided(canvases, g, stride):
 @pytest.mark.parametrize("tw", [20, 24, 13], ids=["broken_runs", "unbroken_runs", "narrow"])
 @pytest.mark.parametrize("shift", [(0, 0), (5, 7)], ids=["fixed", "wrapped"])
 def test_attention_bf16_wide_token_stride_takes_general_addressing(shift, tw, d):
-    """A canvas whose per-head extent exceeds 4 GiB (token stride of 2^21 elements), tiles of 416 to 768 tokens, so that head_dim 64 takes
-    the streaming kernel too.  Windows whose runs of tokens break (head_dim 128: width 20 and 13, or wrapping; head_dim 64, runs of 16:
+    """A canvas whose per-head extent exceeds 4 GiB (token stride of 2^21 elements), tiles of 624 to 1,152 tokens, which head_dim 64 takes to the
+    streaming kernel too.  Windows whose runs of tokens break (head_dim 128: width 20 and 13, or wrapping; head_dim 64, runs of 16:
     any) look every such run's tokens up with 64-bit addresses; whole runs, and unbroken windows of head_dim 128 and width 24, go by
     a wave-uniform 64-bit pointer.  13 tokens are fewer than a run of head_dim 64.  Same numbers as the oracle every time."""
-    g = _geom("wide", 2, 32, 2 * tw, 16, tw, 16, tw, 1, d, "bf16", 71)
+    g = _geom("wide", 3, 32, 2 * tw, 16, tw, 16, tw, 1, d, "bf16", 71)
     dense = canvas_qkv(g)
     wide = _strided(dense, g, 1 << 21)
     p = sg.make_problem(g, shift=shift)

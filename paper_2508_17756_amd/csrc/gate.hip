@@ -12,7 +12,7 @@
 namespace sg {
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kThreads = kPassThreads;
 constexpr int kGateUnroll = 4;   // vectors per input and thread in flight in the gate's partial sums (6, 8, 12 are 2 % slower)
 constexpr int kWavesPerBlock = kThreads / 64;   // every wavefront owns one partial slot per tile
 constexpr int kFinalThreads = 128;
@@ -457,13 +457,14 @@ static int launch_partials(const void* const* a, const void* const* b, const uin
   SG_HIP_TRY(hipGetDevice(&dev));
   SG_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
   const int64_t n_vec = elems / (dtype == SG_BF16 ? 8 : 4);
-  *n_slots = (int)pass_grid(n_vec, 1, n_cu, kGateSlots / kWavesPerBlock).x * kWavesPerBlock;
+  const int blocks = pass_blocks(n_vec, n_tiles, n_cu, kGateSlots / kWavesPerBlock);
+  *n_slots = blocks * kWavesPerBlock;
   for (int t0 = 0; t0 < n_tiles; t0 += kTilesPerLaunch) {
     const int n = (n_tiles - t0 < kTilesPerLaunch) ? n_tiles - t0 : kTilesPerLaunch;
     GatePtrs ptrs;
     for (int i = 0; i < n; ++i) { ptrs.cur[i] = a[t0 + i]; ptrs.cached[i] = b[t0 + i]; }
     for (int i = n; i < kTilesPerLaunch; ++i) { ptrs.cur[i] = nullptr; ptrs.cached[i] = nullptr; }
-    const dim3 grid = pass_grid(n_vec, n, n_cu, kGateSlots / kWavesPerBlock);
+    const dim3 grid = pass_grid(blocks, n_vec, n, n_cu, kGateSlots / kWavesPerBlock);
     const bool cut = pass_cut(n_vec, n_cu, kGateSlots / kWavesPerBlock);
     auto kern = dtype == SG_BF16 ? (cut ? gate_partial_kernel<SG_BF16, true> : gate_partial_kernel<SG_BF16, false>)
                                  : (cut ? gate_partial_kernel<SG_F32, true> : gate_partial_kernel<SG_F32, false>);
@@ -509,7 +510,7 @@ int launch_gain_refresh(void* const* out_cur, const void* const* out_prev, const
   SG_HIP_TRY(hipGetDevice(&dev));
   SG_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
   const int64_t n_vec = elems / (dtype == SG_BF16 ? 8 : 4);
-  const int n_blk = (int)pass_grid(n_vec, 1, n_cu, kGateSlots / kWavesPerBlock, kRefreshVecs).x;
+  const int n_blk = pass_blocks(n_vec, n_tiles, n_cu, kGateSlots / kWavesPerBlock, kRefreshVecs);
   for (int t0 = 0; t0 < n_tiles; t0 += kRefreshTilesPerLaunch) {
     const int n = (n_tiles - t0 < kRefreshTilesPerLaunch) ? n_tiles - t0 : kRefreshTilesPerLaunch;
     GainPtrs ptrs;
@@ -519,7 +520,7 @@ int launch_gain_refresh(void* const* out_cur, const void* const* out_prev, const
       ptrs.latent[i] = i < n ? latent[t0 + i] : nullptr;
       ptrs.delta[i] = i < n ? delta[t0 + i] : nullptr;
     }
-    const dim3 grid = pass_grid(n_vec, n, n_cu, kGateSlots / kWavesPerBlock, kRefreshVecs);
+    const dim3 grid = pass_grid(n_blk, n_vec, n, n_cu, kGateSlots / kWavesPerBlock, kRefreshVecs);
     const bool cut = pass_cut(n_vec, n_cu, kGateSlots / kWavesPerBlock, kRefreshVecs);
     auto kern = dtype == SG_BF16 ? (cut ? gain_refresh_kernel<SG_BF16, true> : gain_refresh_kernel<SG_BF16, false>)
                                  : (cut ? gain_refresh_kernel<SG_F32, true> : gain_refresh_kernel<SG_F32, false>);

@@ -11,7 +11,7 @@
 namespace sg {
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kThreads = kPassThreads;
 constexpr int kFinalThreads = 128;
 constexpr int kTilesPerLaunch = 64;
 constexpr int kMomentsUnroll = 16;   // 16-byte loads in flight per thread: 64 KiB per compute unit (8: 6.6 TB/s, 16: 7.0, 24: 6.9, 32: 6.6)
@@ -165,12 +165,12 @@ int launch_tile_std(const void* const* x, int n_tiles, int64_t elems, int dtype,
   SG_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
   constexpr int kWavesPerBlock = kThreads / 64;   // one partial slot per wavefront
   const int64_t n_vec = elems / (dtype == SG_BF16 ? 8 : 4);
-  const int n_blk = (int)pass_grid(n_vec, 1, n_cu, kGateSlots / kWavesPerBlock).x;
+  const int n_blk = pass_blocks(n_vec, n_tiles, n_cu, kGateSlots / kWavesPerBlock, kPassVecs, kPassVecs);
   for (int t0 = 0; t0 < n_tiles; t0 += kTilesPerLaunch) {
     const int n = (n_tiles - t0 < kTilesPerLaunch) ? n_tiles - t0 : kTilesPerLaunch;
     StdPtrs ptrs;
     for (int i = 0; i < kTilesPerLaunch; ++i) ptrs.x[i] = i < n ? x[t0 + i] : nullptr;
-    const dim3 grid = pass_grid(n_vec, n, n_cu, kGateSlots / kWavesPerBlock);
+    const dim3 grid = pass_grid(n_blk, n_vec, n, n_cu, kGateSlots / kWavesPerBlock);
     const bool cut = pass_cut(n_vec, n_cu, kGateSlots / kWavesPerBlock);
     auto kern = dtype == SG_BF16 ? (cut ? tile_moments_kernel<SG_BF16, true> : tile_moments_kernel<SG_BF16, false>)
                                  : (cut ? tile_moments_kernel<SG_F32, true> : tile_moments_kernel<SG_F32, false>);

@@ -12,7 +12,7 @@
 namespace sg {
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kThreads = kPassThreads;
 constexpr int kSimUnroll = 8;   // vectors per input and thread in flight: 16 loads of 16 bytes (4: 6.9 TB/s, 8: 7.05, 12 and 16: 7.0)
 constexpr int kFinalThreads = 128;
 constexpr int kTilesPerLaunch = 64;
@@ -146,12 +146,12 @@ int launch_similarity(const void* const* x_new, const void* const* x_old, int n_
   SG_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
   constexpr int kMaxBlk = kGateSlots * 2 / kSums;   // the tile's share of the workspace holds this many workgroups' sums
   const int64_t n_vec = elems / (dtype == SG_BF16 ? 8 : 4);
-  const int n_blk = (int)pass_grid(n_vec, 1, n_cu, kMaxBlk).x;
+  const int n_blk = pass_blocks(n_vec, n_tiles, n_cu, kMaxBlk);
   for (int t0 = 0; t0 < n_tiles; t0 += kTilesPerLaunch) {
     const int n = (n_tiles - t0 < kTilesPerLaunch) ? n_tiles - t0 : kTilesPerLaunch;
     SimPtrs ptrs;
     for (int i = 0; i < kTilesPerLaunch; ++i) { ptrs.a[i] = i < n ? x_new[t0 + i] : nullptr; ptrs.b[i] = i < n ? x_old[t0 + i] : nullptr; }
-    const dim3 grid = pass_grid(n_vec, n, n_cu, kMaxBlk);
+    const dim3 grid = pass_grid(n_blk, n_vec, n, n_cu, kMaxBlk);
     const bool cut = pass_cut(n_vec, n_cu, kMaxBlk);
     auto kern = dtype == SG_BF16 ? (cut ? similarity_partial_kernel<SG_BF16, true> : similarity_partial_kernel<SG_BF16, false>)
                                  : (cut ? similarity_partial_kernel<SG_F32, true> : similarity_partial_kernel<SG_F32, false>);

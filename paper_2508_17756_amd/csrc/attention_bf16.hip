@@ -618,10 +618,14 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
         *(SG_LDS u32x4*)(uintptr_t)(dma_dst + (last % kStages) * kTileBytes + kVRegion + u * (4 * kRowBytes) + lane * 16) = u32x4{0, 0, 0, 0};
     }
   };
-  // end of iteration k: the stage issued last but one has landed.  Behind its transfers stand those of the last stage and the
-  // four stores of every stage copied in this iteration and the one before (whole stages: none of them is skipped).
+  // End of iteration k: stage k + 2, issued last but one, has landed.  Behind its transfers stand those of stage k + 3, if there is
+  // one, and the four stores of every stage copied in this iteration and the one before; these are whole stages as long as there
+  // is a stage k + 2, so none of their stores is skipped.  From iteration n_blocks - 2 on every transfer has landed, and a copy's
+  // stores need not be waited for (a step of one tile of 460 tokens, 2 heads x 64: 28.1 -> 27.0 us).
   auto wait_iteration = [&](int k, bool issued) SG_INLINE {
-    wait_stage(issued ? 1 + copies(k) + copies(k - 1) : 0);
+    const int stores = copies(k) + copies(k - 1);
+    if (issued) wait_stage(1 + stores);
+    else if (!REFRESH || k + 2 < n_blocks) wait_stage(stores);
     if (LATE && tail && k == n_blocks - 2) clear_tail();
   };
   bf16x8 p[2 * kMaxSB];   // the first 2 kSB entries

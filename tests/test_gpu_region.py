@@ -150,11 +150,11 @@ def test_similarity_zero_tensors_many_tiles_and_arguments():
 
 def _probes(n, width, seed):
     """Zeros but for integers 8 .. 15 in vectors where a pass may go wrong: both ends of every run of 256 (threads; unrolled steps and
-    chunks end there too), of every workgroup's slab under either rule of cutting and when walked, a few hundred more, the last
-    vector and every element of the tail behind it.  Element 0 stays 0: the deviation's pivot."""
+    chunks end there too), of every workgroup's slab under either rule of cutting, when walked and when three tiles share the device, a few
+    hundred more, the last vector and every element of the tail behind it.  Element 0 stays 0: the deviation's pivot."""
     vecs = n // width
     at = set(range(0, vecs, 256)) | set(range(255, vecs, 256)) | {vecs - 1}
-    for blocks in {-(-vecs // 4096), -(-vecs // 2048), 256}:
+    for blocks in {-(-vecs // 4096), -(-vecs // 2048), 256, 85}:
         slab = -(-vecs // blocks)
         at |= {v for b in range(blocks + 1) for v in (b * slab - 1, b * slab) if 0 <= v < vecs}
     rng = np.random.default_rng(seed)
@@ -166,20 +166,21 @@ def _probes(n, width, seed):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("vecs", [2047, 2048, 2049, 4095, 4096, 4097, 3 * 4096, 255 * 2048, 255 * 2048 + 1, 256 * 2048 + 7,
+@pytest.mark.parametrize("count", [1, 3])
+@pytest.mark.parametrize("vecs", [5, 1000, 2047, 2048, 2049, 4095, 4096, 4097, 3 * 4096, 255 * 2048, 255 * 2048 + 1, 256 * 2048 + 7,
                                   255 * 4096, 255 * 4096 + 1, 256 * 4096 + 7])
-def test_passes_over_tiles_cut_side_by_side_or_walked(dtype, vecs):
+def test_passes_over_tiles_cut_side_by_side_or_walked(dtype, vecs, count):
     """Both grids of the streaming passes around the sizes where they change (4,096 vectors per workgroup, 2,048 in the gain refresh, a
-    device of 256 compute units), over three tiles: every element is counted exactly once.  Each sum is carried by a few thousand
+    device of 256 compute units), over one tile and three, which share the compute units: every element is counted exactly once.  Each sum is carried by a few thousand
     probes (at most 11,000, of 8 to 15, on a background of zeros), so that one lost or repeated changes the results, which are ratios
     and square roots of the sums, by 1e-5 of themselves or more.  All terms are small integers: the sums are exact, the results
     rounded once (2^-24)."""
     width = 8 if dtype == "bf16" else 4
     dt = torch_dtype(dtype)
     n = (vecs * width + 7) // 8 * 8
-    ws = torch.empty(sg.sg_workspace_bytes(3), dtype=torch.uint8, device="cuda").fill_(255)
-    f = lambda: torch.full((3,), float("nan"), device="cuda")
-    has = torch.ones(3, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(sg.sg_workspace_bytes(count), dtype=torch.uint8, device="cuda").fill_(255)
+    f = lambda: torch.full((count,), float("nan"), device="cuda")
+    has = torch.ones(count, dtype=torch.uint8, device="cuda")
 
     def near(got, want, what):
         assert abs(float(got) - want) <= 2e-6 * want, (what, float(got), want)
@@ -187,10 +188,10 @@ def test_passes_over_tiles_cut_side_by_side_or_walked(dtype, vecs):
     # change: probes that differ from a background of ones; level: all ones away from a background of probes
     for kind in ("change", "level"):
         for tail in (0, 3):                                  # gate and similarity also take a ragged end
-            probes = [_probes(n + tail, width, 17 * i + vecs) for i in range(3)]
+            probes = [_probes(n + tail, width, 17 * i + vecs) for i in range(count)]
             olds = [torch.ones_like(p).to(dt) if kind == "change" else p.to(dt) for p in probes]
             tiles = [(p + 1).to(dt) for p in probes]
-            l1, cs, scores, rec = f(), f(), f(), torch.empty(3, dtype=torch.uint8, device="cuda")
+            l1, cs, scores, rec = f(), f(), f(), torch.empty(count, dtype=torch.uint8, device="cuda")
             sg.sg_tile_similarity(tiles, olds, l1, cs, ws)
             sg.sg_cache_gate(tiles, olds, has, 0.5, scores, rec, ws)
             for i, (x, y) in enumerate(zip(tiles, olds)):
@@ -200,17 +201,17 @@ def test_passes_over_tiles_cut_side_by_side_or_walked(dtype, vecs):
                 near(scores[i], want, ("gate", kind, tail, i))
                 if kind == "level":
                     near(cs[i], float((x * y).sum() / (x.norm() * y.norm())), ("cosine", tail, i))
-        probes = [_probes(n, width, 17 * i + vecs) for i in range(3)]
+        probes = [_probes(n, width, 17 * i + vecs) for i in range(count)]
         olds = [torch.ones_like(p).to(dt) if kind == "change" else p.to(dt) for p in probes]
         tiles = [(p + 1).to(dt) for p in probes]
         std = f()
         sg.sg_tile_std([p.to(dt) for p in probes], std, ws)
-        state = sg.GainState(3)
+        state = sg.GainState(count)
         state.has_prev.fill_(1)
         out = [t.clone() for t in tiles]
         delta = [torch.full((n,), 9.0, device="cuda") for _ in tiles]
-        recompute = torch.tensor([1, 0, 1], dtype=torch.uint8, device="cuda")
-        change = torch.full((3,), 0.25, device="cuda")
+        recompute = torch.tensor([1, 0, 1][:count], dtype=torch.uint8, device="cuda")
+        change = torch.full((count,), 0.25, device="cuda")
         sg.sg_gain_refresh(out, olds, olds, delta, recompute, change, state, ws)
         for i, (x, y) in enumerate(zip(tiles, olds)):
             near(std[i], float(probes[i].double().std(unbiased=False)), ("std", i))

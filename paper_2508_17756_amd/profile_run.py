@@ -10,6 +10,8 @@ Sections (choose with --kernels, comma separated):
              traffic the FETCH_SIZE / WRITE_SIZE counters are scaled by
   attention  sg_tile_attention on the 75,600-token tile, 40 heads x 128, bf16
   attention64  the same tile at 48 heads x 64 (not in the default list)
+  window64   a wrapped window of 17,550 tokens, 48 heads x 64, read in place (not in the default list)
+  attention32  an fp32 tile of 2,880 tokens, 32 heads x 128 (not in the default list)
   blend      sg_tile_blend of the 4K canvas (20 tiles of 75,600 tokens -> 21 x 135 x 240)
   gate       sg_cache_gate over 4 tiles of packed Q,K,V (2.32 GB per tile and side)
   update     sg_tile_blend_update of the 4K canvas (blend + scheduler update in place)
@@ -87,6 +89,30 @@ def main():
             sg.sg_tile_attention(p, q, k, v, 0, 0, out)
         torch.cuda.synchronize()
         say("attention64: %d launches, %.6e FLOP per launch (48 heads x 64)" % (args.reps, 4.0 * g.tile_tokens ** 2 * 64 * 48))
+        del q, k, v, out
+
+    if "window64" in todo:
+        from synthetic import TileGeometry
+        g = TileGeometry("window64", 13, 60, 90, 30, 45, 30, 45, 2, 2, 48, 64, "bf16", 0)
+        p = sg.make_problem(g, shift=(5, 8))
+        q, k, v = (rnd(g.grid_shape) for _ in range(3))
+        out = torch.empty(g.tile_shape, dtype=torch.bfloat16, device="cuda")
+        for _ in range(args.reps):
+            sg.sg_tile_attention(p, q, k, v, 1, 1, out)
+        torch.cuda.synchronize()
+        say("window64: %d launches, %.6e FLOP per launch (48 heads x 64)" % (args.reps, 4.0 * g.tile_tokens ** 2 * 64 * 48))
+        del q, k, v, out
+
+    if "attention32" in todo:
+        from synthetic import TileGeometry
+        g = TileGeometry("attention32", 5, 18, 32, 18, 32, 18, 32, 1, 1, 32, 128, "f32", 0)
+        p = sg.make_problem(g)
+        q, k, v = (rnd(g.grid_shape, "f32") for _ in range(3))
+        out = torch.empty(g.tile_shape, dtype=torch.float32, device="cuda")
+        for _ in range(args.reps):
+            sg.sg_tile_attention(p, q, k, v, 0, 0, out)
+        torch.cuda.synchronize()
+        say("attention32: %d launches, %.6e FLOP per launch (32 heads x 128)" % (args.reps, 4.0 * g.tile_tokens ** 2 * 128 * 32))
         del q, k, v, out
 
     if "blend" in todo:

@@ -224,12 +224,13 @@ def test_fp32_attention_takes_an_infinite_last_value(T, th, tw, d, heads):
 @pytest.mark.parametrize("heads", [1, 48])
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("wrapped", [False, True], ids=["fixed", "wrapped"])
-def test_fp32_attention_of_heads_beyond_4_gib(wrapped, d, heads):
-    """Offsets inside a head that leave 32 bits, with either split of the keys."""
+@pytest.mark.parametrize("stride", [1 << 19, 1 << 20], ids=["3gib", "6gib"])
+def test_fp32_attention_of_heads_of_gibibytes(stride, wrapped, d, heads):
+    """Byte offsets inside a head that take all 32 bits, and that leave them, with either split of the keys."""
     n = 400
     gen = torch.Generator().manual_seed(n + d)
     q, k, v = (torch.randn(heads, n, d, generator=gen) for _ in range(3))
-    got = _attend_window("f32", d, heads, 1, 16, 25, q, k, v, wrapped=wrapped, token_stride=1 << 20).double()
+    got = _attend_window("f32", d, heads, 1, 16, 25, q, k, v, wrapped=wrapped, token_stride=stride).double()
     ref = torch.softmax(q.double() @ k.double().transpose(1, 2) / math.sqrt(d), dim=2) @ v.double()
     assert float((got - ref).norm() / ref.norm()) <= 1e-6           # measured 2.3e-7
-    _infinite_last_value("f32", d, heads, 1, 16, 25, wrapped=wrapped, token_stride=1 << 20)
+    _infinite_last_value("f32", d, heads, 1, 16, 25, wrapped=wrapped, token_stride=stride)

@@ -113,6 +113,7 @@ int sg_workspace_bytes(int32_t n_tiles, size_t* out_bytes);
  * outputs stay finite for |V| below 2^111.  Tiles of head_dim 64 that are read in place from a larger canvas (or under a shifted
  * partition), and those of head_dim 128 whose head spans 4 GiB or more and whose window wraps or is no multiple of 8 tokens wide,
  * are scaled in fp32 behind the product instead, against the true running maximum, and take any finite V.
+ * fp32 problems take any finite V as well.  A NaN in Q, K or V reaches every output that depends on it, and no other.
  */
 int sg_tile_attention(const sg_problem* p, const void* q, const void* k, const void* v,
                       int32_t tile_row, int32_t tile_col, void* out_tile, void* stream);

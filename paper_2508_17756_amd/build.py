@@ -11,7 +11,7 @@ LIB = os.path.join(PKG, "libsupergen_tile.so")
 PROBE = os.path.join(PKG, "peak_probe.bin")
 C_CLIENT_SRC = os.path.join(ROOT, "tests", "c_client", "gpu_client.c")
 C_CLIENT = os.path.join(ROOT, "tests", "c_client", "gpu_client.bin")
-SOURCES = ["sg_api.hip", "attention_bf16.hip", "attention_bf16_short.hip", "attention_f32.hip", "blend.hip",
+SOURCES = ["sg_api.hip", "attention_bf16.hip", "attention_bf16_short.hip", "attention_f32.hip", "attention_f32_split.hip", "blend.hip",
            "gate.hip", "gate_static.hip", "region.hip", "similarity.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          # packed fp32 VALU forms are kept out of the generated code on the test machines

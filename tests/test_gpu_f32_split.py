@@ -1,0 +1,124 @@
+"""fp32 attention on the bf16 matrix instruction (three bf16 parts of every number): taken where the rounds of 128-query workgroups over the
+device are short against those of 32-query ones, here with 200 heads of few tokens."""
+import math
+
+import pytest
+import torch
+
+from test_gpu_extremes import _attend_window
+
+pytestmark = pytest.mark.gpu
+
+HEADS = 200    # 256 compute units: one round of 128-query workgroups, three of 32-query ones, up to 128 tokens
+
+
+def _inputs(heads, n, d):
+    gen = torch.Generator().manual_seed(1000 * d + n)
+    return [torch.randn(heads, n, d, generator=gen) for _ in range(3)]
+
+
+def _exact(q, k, v):
+    out = torch.empty(q.shape, dtype=torch.float64)
+    for a in range(q.shape[0]):
+        # the scale as the library gets it, rounded to fp32
+        w = torch.softmax(q[a].double() @ k[a].double().T * float(torch.tensor(1.0 / math.sqrt(q.shape[2]))), dim=1)
+        out[a] = w @ v[a].double()
+    return out
+
+
+def _rel(got, want):
+    """Largest relative 2-norm error of a head."""
+    return float(((got.double() - want).flatten(1).norm(dim=1) / want.flatten(1).norm(dim=1)).max())
+
+
+# Every fp32 sum of products of first parts is rounded d/16 (scores) or n/16 (outputs) times by at most half a unit, 2^-24: as a
+# random walk of uniform errors sqrt((8 + n/16) / 3) 2^-24, under 3e-7 at 700 tokens; products of scores' errors with the scores (up to 5)
+# and the exponential's own 2^-22 double that.
+TOLERANCE = 6e-7
+
+
+@pytest.mark.parametrize("where", ["packed", "fixed", "wrapped"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads,T,th,tw", [
+    (HEADS, 1, 5, 13),      # 65: three stages of 32 keys or two of 64, the last with one key
+    (HEADS, 1, 8, 12),      # 96: whole stages of 32 keys
+    (HEADS, 1, 8, 16),      # 128: whole stages, whole workgroup
+    (120, 1, 3, 43),        # 129: a second workgroup with one query
+    (40, 2, 16, 16),        # 512: 16 or 8 whole stages
+    (40, 3, 9, 19),         # 513: the range is looked at again behind 16 stages, with one stage left
+    (30, 2, 17, 20),        # 680: behind 16 stages in the middle
+    (51, 7, 10, 10),        # 700
+])
+def test_sizes(heads, T, th, tw, d, where):
+    n = T * th * tw
+    q, k, v = _inputs(heads, n, d)
+    got = _attend_window("f32", d, heads, T, th, tw, q, k, v, wrapped=where == "wrapped", packed=where == "packed")
+    assert _rel(got, _exact(q, k, v)) <= TOLERANCE
+
+
+def _put(x, head, tokens, factor):
+    x[head, tokens] = x[head, tokens] * factor
+
+
+# head 7 holds numbers that the parts do not; its neighbours do not
+OUT = {
+    "large_values": lambda q, k, v: _put(v, 7, slice(None), 2.0 ** 100),
+    "one_large_value_in_the_last_stage": lambda q, k, v: _put(v, 7, -1, 2.0 ** 64),
+    "tiny_values": lambda q, k, v: _put(v, 7, slice(None), 2.0 ** -112),
+    "one_tiny_value": lambda q, k, v: _put(v, 7, 40, 2.0 ** -112),
+    "large_keys": lambda q, k, v: (_put(k, 7, slice(None), 2.0 ** 62), _put(q, 7, slice(None), 2.0 ** -62)),
+    "large_queries": lambda q, k, v: (_put(q, 7, slice(None), 2.0 ** 70), _put(k, 7, slice(None), 2.0 ** -70)),
+    "one_large_query": lambda q, k, v: (_put(q, 7, -1, 2.0 ** 70), _put(k, 7, slice(None), 2.0 ** -69)),
+    "zero_values": lambda q, k, v: _put(v, 7, slice(0, 50), 0.0),
+}
+
+
+@pytest.mark.parametrize("name", sorted(OUT))
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads,T,th,tw", [(HEADS, 1, 5, 13), (30, 2, 17, 20)])
+def test_numbers_that_the_parts_do_not_hold(heads, T, th, tw, d, name):
+    n = T * th * tw
+    q, k, v = _inputs(heads, n, d)
+    OUT[name](q, k, v)
+    got = _attend_window("f32", d, heads, T, th, tw, q, k, v)
+    assert _rel(got, _exact(q, k, v)) <= TOLERANCE
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_probabilities_below_the_smallest_normal_number_count(d):
+    """Key 0 has a score 133 below the others' in the log2 domain, and values of 2^100: the products, 2^-33, are all that channel 0 holds."""
+    n = 96
+    q, k, v = _inputs(HEADS, n, d)
+    q[7], k[7] = 0.0, 0.0
+    q[7, :, 0] = 1.0
+    k[7, 0, 0] = -133.0 / math.log2(math.e) * math.sqrt(d)
+    v[7, 1:, 0] = 0.0
+    v[7, 0] = 2.0 ** 100
+    want = _exact(q, k, v)
+    got = _attend_window("f32", d, HEADS, 1, 8, 12, q, k, v)
+    # the probability is a multiple of 2^-149: half a unit at 2^-140 is 2^-10
+    assert float((got[7, :, 0].double() / want[7, :, 0] - 1.0).abs().max()) <= 2.0 ** -9
+    got[7], want[7] = 1.0, 1.0
+    assert _rel(got, want) <= TOLERANCE
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads,T,th,tw", [(HEADS, 1, 5, 13), (30, 2, 17, 20)])
+def test_infinities_and_nan(heads, T, th, tw, d):
+    """An infinite value reaches its channel of every output, also as the last one, for which the keys that fill up the last stage stand
+    in; a NaN in a query reaches that query, in a key every output, in a value its channel."""
+    n = T * th * tw
+    q, k, v = _inputs(heads, n, d)
+    v[3, n - 1, 5] = math.inf
+    q[4, 11, 0] = math.nan
+    k[5, n - 1, 1] = math.nan
+    v[6, 2, 9] = math.nan
+    got = _attend_window("f32", d, heads, T, th, tw, q, k, v)
+    assert bool((got[3, :, 5] == math.inf).all())
+    want = torch.zeros(heads, n, d, dtype=torch.bool)
+    want[4, 11] = True
+    want[5] = True
+    want[6, :, 9] = True
+    assert torch.equal(got.isnan(), want)
+    got[3, :, 5] = 0.0
+    assert bool(torch.isfinite(got[~want]).all())

@@ -147,7 +147,11 @@ enum { kLinear = 0, kWindow = 1, kWalk = 2 };
 // Q first and keep a lazy reference.
 // REFRESH: the launch also refreshes the cache of the tiles it attends (packed tiles: refresh <- the tile's Q, K, V,
 // has_cache <- 1).
-template <int D, int MODE, bool LATE, bool REFRESH>
+// SHORT: tiles of few stages.  Beside its stages a workgroup of 1,000 tokens spent two fifths of its 70,000 cycles on code that is
+// fetched for an iteration or two - 3,600 cycles an iteration before the steady loop, 4,900 on the first behind it, 2,700 inside - and this
+// form has one copy of an iteration for all of them.  Where both are warm it is up to 5 % slower an iteration (scalar branches, scalar registers
+// spilled).
+template <int D, int MODE, bool LATE, bool REFRESH, bool SHORT>
 __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 vw, const float c_log2, const int heads,
                                                                   const int n_qblocks, const int n_tiles, const int cu_per_xcd,
                                                                   const AttnTable tab, const uint8_t* __restrict__ run_flags,
@@ -376,6 +380,17 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
       fetch_plan(blk + 1);   // for the next steady iteration
     }
   };
+  // the same for a stage that may hold keys >= N; its plan has been fetched
+  auto issue_next = [&](int blk, int st) SG_INLINE {
+    const uint32_t dst = dma_dst + st * kTileBytes;
+    if (__builtin_expect(blk * kKeys + kTok * (wave + 1) > N, 0)) look_up(blk, dst);   // (the last stage)
+    else if (MODE != kWindow) move_next(dst);
+    else move_planned(blk, dst);
+    if (MODE == kWindow) {
+      if (st == kStages - 1 && (blk & 63) == 63) plan64(blk + 1);
+      fetch_plan(blk + 1);   // for the next iteration
+    }
+  };
   // Cache refresh: a workgroup copies the keys and values of its own query rows out of the LDS ring while their stages are
   // there (kCopy of its stages, each wavefront what it moved itself, to the place it came from), so that the copy reads
   // nothing from HBM and its stores are spread over the launch; its rows of Q follow at the end.
@@ -401,7 +416,7 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
     }
   };
 
-  // the same for a stage that may hold keys >= N
+  // the same, with its plan, for a slot that is not a constant
   auto issue_any = [&](int blk, int st) SG_INLINE {
     const uint32_t dst = dma_dst + st * kTileBytes;
     if (MODE == kWindow) {
@@ -646,6 +661,19 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
     __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_sched_barrier(0);
   };
+  // Windows of head_dim 64 take QK behind the last stage as well, of stale keys and for nothing: with the branch their scores spill
+  // (one tile of 1,000 tokens, 24 heads: 20.8 us with it, 19.2 without); elsewhere the branch is up to 2 % faster.
+  constexpr bool kQkAlways = D == 64 && LATE;
+  auto mfma_phase_short = [&](int k, auto st_tag) SG_INLINE {
+    constexpr int ST = decltype(st_tag)::value;
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+    pv(ST * kTileBytes, p, ((ST + 1) % kStages) * kTileBytes, true);   // (behind the last stage the K fragments it reads ahead are stale and not used)
+    if (kQkAlways || k + 1 < n_blocks) qk(((ST + 1) % kStages) * kTileBytes, s, true);
+    SG_PIN_SCORES();
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+  };
   auto mfma_phase_any = [&](int k) SG_INLINE {
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_setprio(1);
@@ -686,7 +714,50 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
   SG_PIN_SCORES();
   const int n_steady = (n_blocks >= 2 * kStages) ? kStages + ((n_blocks - 2 * kStages) / kStages) * kStages : 0;
 
-  if (!grp1) {
+  // Short tiles: one copy of an iteration for every ring slot and group serves all of them; what the first and the last need besides is
+  // a scalar branch.  (A kernel of its own: with
+  // the steady loop beside it the compiler spills 130 registers.)
+  auto short_iterations = [&](auto iteration) SG_INLINE {
+    for (int k = 0;; k += kStages) {
+      iteration(k, std::integral_constant<int, 0>{});
+      if (k + 1 >= n_blocks) break;
+      iteration(k + 1, std::integral_constant<int, 1>{});
+      if (k + 2 >= n_blocks) break;
+      iteration(k + 2, std::integral_constant<int, 2>{});
+      if (k + 3 >= n_blocks) break;
+      iteration(k + 3, std::integral_constant<int, 3>{});
+      if (k + 4 >= n_blocks) break;
+    }
+  };
+  if (SHORT && MODE == kWindow) fetch_plan(3);
+  if constexpr (SHORT) {
+    if (!grp1) {
+      softmax_pinned(0, tail && n_blocks == 1, true);
+      wait_stage(n_blocks >= 3 ? 1 : 0);
+      meet();   // B_0
+      short_iterations([&](int k, auto st_tag) SG_INLINE {
+        constexpr int ST = decltype(st_tag)::value;
+        if (k + 3 < n_blocks) issue_next(k + 3, (ST + 3) % kStages);
+        if (copies(k)) copy_stage(k, (k + 1) * kKeys <= N);
+        mfma_phase_short(k, st_tag);
+        if (k + 1 < n_blocks) softmax_pinned(k + 1, tail && k + 1 == n_blocks - 1, false);
+        wait_iteration(k, k + 3 < n_blocks);
+        meet();
+      });
+    } else {
+      wait_stage(n_blocks >= 3 ? 1 : 0);
+      meet();   // B_0
+      short_iterations([&](int k, auto st_tag) SG_INLINE {
+        constexpr int ST = decltype(st_tag)::value;
+        if (k + 3 < n_blocks) issue_next(k + 3, (ST + 3) % kStages);
+        if (copies(k)) copy_stage(k, (k + 1) * kKeys <= N);
+        softmax_pinned(k, tail && k == n_blocks - 1, k == 0);
+        mfma_phase_short(k, st_tag);
+        wait_iteration(k, k + 3 < n_blocks);
+        meet();
+      });
+    }
+  } else if (!grp1) {
     softmax_pinned(0, tail && n_blocks == 1, true);
     wait_stage(n_blocks >= 3 ? 1 : 0);
     meet();   // B_0
@@ -817,13 +888,14 @@ int launch_attention_bf16(const TileView& tv, int heads, int head_dim, float sca
   SG_HIP_TRY(hipGetDevice(&dev));
   SG_HIP_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
   // Windows of head_dim 64 that do not fill the pipeline of the streaming kernel take the register-staged one: up to 448 tokens, and up to
-  // 1,200 where there are workgroups for more than half of the compute units.  (Fewer are dealt as halves here, which the other does
-  // not do.)  Register-staged and streaming, us a step: 9 tiles, 24 heads, of 400 tokens 34.4 and 42.9, of 600 57.7 and 64.4, of 900
-  // 103 and 109, of 1,200 152 and 155, of 1,500 224 and 218; 20 tiles of 1,200 308 and 327; 4 tiles, 8 heads, of 400 tokens 17.5 and
-  // 18.6, of 512 18.7 and 17.7, of 1,024 30.8 and 27.0.
+  // 960 where there are workgroups for more than half of the compute units.  (Fewer are dealt as halves here, which the other does
+  // not do.)  Register-staged and streaming, us a step: 9 tiles, 24 heads, of 300 tokens 29.6 and 33.9, of 500 38.5 and 40.9, of 700 64.1
+  // and 69.6, of 832 91.3 and 89.4, of 960 103.7 and 100.8, of 1,000 108 and 101, of 1,100 146 and 127, of 1,200 155 and 147; 20 tiles, 16
+  // heads, of 770 115 and 120, of 960 133.8 and 133.5, of 1,100 201 and 180; 4 tiles, 12 heads, of 960 31.7 and 32.3, of 1,100 36.4 and
+  // 35.2; 8 heads, of 400 17.5 and 18.6, of 512 18.7 and 17.7.
   if (head_dim == 64 && tv.window) {
     const int64_t workgroups = (int64_t)b.n_tiles * heads * ((tv.N + kBR - 1) / kBR);
-    if (tv.N <= 448 || (tv.N <= 1200 && 2 * workgroups > n_cu)) return launch_attention_bf16_short(tv, heads, scale, b, s);
+    if (tv.N <= 448 || (tv.N <= 960 && 2 * workgroups > n_cu)) return launch_attention_bf16_short(tv, heads, scale, b, s);
   }
   const View16 vw = make_view16(tv);
   // Windows of head_dim 128 whose runs of 8 tokens all lie side by side (width a multiple of 8, none of the launch crosses a canvas
@@ -842,7 +914,7 @@ int launch_attention_bf16(const TileView& tv, int heads, int head_dim, float sca
   const float c_log2 = scale * 1.4426950408889634f;
   // the kernels need more dynamic LDS than the default limit; the attribute is set once per device and kernel
   constexpr int kMaxDevices = 64;
-  static std::atomic<bool> attr_set[kMaxDevices][8];   // zero-initialised; set twice by racing threads is harmless
+  static std::atomic<bool> attr_set[kMaxDevices][16];   // zero-initialised; set twice by racing threads is harmless
   const int cu_per_xcd = n_cu / kXcd > 0 ? n_cu / kXcd : 1;
   // the cache refresh rides on this launch for packed tiles (their inputs are one contiguous run each)
   const bool fuse_refresh = b.refresh_dst && b.has_cache && !window;
@@ -873,16 +945,23 @@ int launch_attention_bf16(const TileView& tv, int heads, int head_dim, float sca
                                              fuse_refresh ? b.has_cache + t0 : nullptr);
       return SG_OK;
     };
+    // Short form, us a step with the other form and with it, 9 tiles, 24 heads.  head_dim 128: 300 tokens 42.6 and 39.7, 700 87.7 and 82.7,
+    // 1,365 256 and 250, 1,500 276 and 273, 2,000 417 and 418, 4,600 1,933 and 1,974; one tile of 700 20.0 and 18.2.  head_dim 64: packed, of
+    // which six run, 300 52.9 and 50.9, 1,500 185 and 177, 3,000 481 and 477, 4,600 941 and 951; windows of 1,500 217 and 202, 3,000 674 and
+    // 671, 4,600 1,419 and 1,440.
+    const bool is_short = tv.N <= (head_dim == 64 ? 3072 : 1536);   // 24 stages
     int st = SG_OK;
+#define SG_BF16(D, MODE, LATE, REFRESH, SLOT) \
+  (is_short ? launch(attention_bf16_kernel<D, MODE, LATE, REFRESH, true>, SLOT) : launch(attention_bf16_kernel<D, MODE, LATE, REFRESH, false>, SLOT + 8))
     if (head_dim == 64)
-      st = window ? launch(attention_bf16_kernel<64, kWindow, true, false>, 0)
-           : fuse_refresh ? launch(attention_bf16_kernel<64, kLinear, false, true>, 1) : launch(attention_bf16_kernel<64, kLinear, false, false>, 2);
+      st = window ? SG_BF16(64, kWindow, true, false, 0) : fuse_refresh ? SG_BF16(64, kLinear, false, true, 1) : SG_BF16(64, kLinear, false, false, 2);
     else if (walk)
-      st = launch(attention_bf16_kernel<128, kWalk, false, false>, 7);
+      st = SG_BF16(128, kWalk, false, false, 7);
     else if (window)
-      st = late ? launch(attention_bf16_kernel<128, kWindow, true, false>, 3) : launch(attention_bf16_kernel<128, kWindow, false, false>, 4);
+      st = late ? SG_BF16(128, kWindow, true, false, 3) : SG_BF16(128, kWindow, false, false, 4);
     else
-      st = fuse_refresh ? launch(attention_bf16_kernel<128, kLinear, false, true>, 5) : launch(attention_bf16_kernel<128, kLinear, false, false>, 6);
+      st = fuse_refresh ? SG_BF16(128, kLinear, false, true, 5) : SG_BF16(128, kLinear, false, false, 6);
+#undef SG_BF16
     if (st != SG_OK) return st;
     SG_HIP_TRY(hipGetLastError());
   }

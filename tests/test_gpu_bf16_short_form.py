@@ -1,5 +1,5 @@
 """bf16 attention of few stages (64 keys, head_dim 64: 128): up to 24 of them every iteration is the same code, the first and the last
-included, and there is one copy of it per slot of the ring of four."""
+included, and there is one copy of it per slot of the ring of four; beyond, a steady loop of groups of four begins at the second."""
 import math
 
 import pytest
@@ -40,6 +40,15 @@ SIZES = [
     (1, 53, 29),    # 1,537: 25 | 13
     (2, 32, 48),    # 3,072: 48 | 24, the last of the short form for head_dim 64
     (1, 7, 439),    # 3,073: 49 | 25
+    # the other form: 1 iteration, groups of four of the steady loop, 4 to 7 iterations
+    (1, 50, 32),    # 1,600: 25, whole
+    (1, 52, 32),    # 1,664: 26, whole
+    (1, 54, 32),    # 1,728: 27, whole
+    (7, 13, 19),    # 1,729: 28, the last with one key
+    (1, 56, 32),    # 1,792: 28, whole
+    (1, 100, 32),   # 3,200: 50 | 25, whole
+    (3, 11, 97),    # 3,201: 51 | 26, the last with one key
+    (1, 112, 32),   # 3,584: 56 | 28, whole
 ]
 
 

@@ -713,10 +713,12 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
   qk(0, s, false);
   SG_PIN_SCORES();
   // The steady loop: from iteration kHead on, in groups of four, while the stage it requests is not the last (which may be partial and is
-  // moved by issue_any).  Iteration 0 sets the reference and stays outside; the other three that used to, in groups that began at a
-  // multiple of four, took 3,600 cycles instead of 2,700: 9 tiles of 3,840 tokens, 40 heads 2,325 -> 2,301 us, of 3,000, 24 heads
-  // 914 -> 903; 4 of 17,550, 48 heads x 64 17.70 -> 17.44 ms.  (A refresh interrupts whole groups of the stages it copies.)
-  constexpr int kHead = REFRESH ? kStages : 1;
+  // moved by issue_any).  Iteration 0 sets the reference and stays outside; the other three that do where groups begin at a
+  // multiple of four take 3,600 cycles instead of 2,700.  From 1, walked windows: 9 tiles of 3,000 tokens, 24 heads 906 -> 896 us, one
+  // 132.4 -> 129.6, of 2,000 430 -> 427; windows of 53,760 tokens, 24 heads x 64 45.6 -> 44.9 ms.  Not planned windows of head_dim 128 (the
+  // loop itself spills: 9 tiles of 80,640 866 -> 901 ms), not packed tiles of head_dim 64 (34.05 -> 34.20 ms), not with a refresh, which
+  // interrupts whole groups of the stages it copies.
+  constexpr int kHead = (MODE == kWalk || (MODE == kWindow && D == 64)) ? 1 : kStages;
   const int n_steady = (n_blocks >= kHead + 2 * kStages) ? kHead + ((n_blocks - kHead - kStages) / kStages) * kStages : 0;
 
   // Short tiles: one copy of an iteration for every ring slot and group serves all of them; what the first and the last need besides is

@@ -481,6 +481,7 @@ __global__ __launch_bounds__(kThreads, 1) void attention_f32_split_kernel(const 
     for_range<0, 6>([&](auto x) SG_INLINE { qk_product(g, x, a); });
   });
   wait_products();
+  meet();   // all wavefronts have read K of stage 0: the first iteration stores K of stage 2 in its place
 
   for (int j = 0; j < n_blocks && !narrow; ++j) {
     const int koff = ((j + 1) & 1) * kStageBytes, voff = (j & 1) * kStageBytes;

@@ -2,11 +2,13 @@
 // tokens; Section 3: tiles exchange no Q/K/V), for calls with enough queries to fill the device with workgroups of 128.
 //
 // Every fp32 number is the sum of three bf16 numbers, 24 bits in three times 8.  Of the nine products of two numbers' parts six count:
-// 1 x 1, 1 x 2, 2 x 1, 2 x 2, 1 x 3, 3 x 1; what is left out is below 2^-24 of the product, mostly 2^-27.  A bf16 product of 16 channels or
+// 1 x 1, 1 x 2, 2 x 1, 2 x 2, 1 x 3, 3 x 1.  Every part is rounded, so the second is at most 2^-8 and the third 2^-17 of a number, and what
+// is left out of a product 2^-24 of it (2 x 3 and 3 x 2; of N(0, 1) numbers 2^-27.4 in the mean square, where rounding the product to
+// fp32 is 2^-25.2).  With a first part that is cut off, one instruction less, it would be 2^-22.  A bf16 product of 16 channels or
 // keys takes 32 cycles, where the fp32 instruction takes 512: six of them 192.  The products of first parts are summed apart from
 // the others, so that the full-size sums are rounded once per 16 channels or keys and the others' roundings are 2^-8 smaller.
-// Error against fp64, fp32 instruction (channels in four chains, keys in four or eight shares) -> here: 2,880 tokens x 128 5.1e-7 ->
-// 3.9e-7, 9,000 8.6e-7 -> 6.5e-7; 4,000 x 64 5.3e-7 -> 4.0e-7; 65 - 1,500 tokens a fifth to a quarter smaller.
+// Error against fp64, fp32 instruction (channels in four chains, keys in four or eight shares) -> here: 2,880 tokens x 128 5.2e-7 ->
+// 3.9e-7, 9,000 8.6e-7 -> 6.5e-7; 4,000 x 64 5.9e-7 -> 4.4e-7; 65 - 1,500 tokens a quarter smaller.
 //
 // A workgroup owns 128 queries of one head, 32 per wavefront, one wavefront per SIMD with the whole register file (Q's parts and two
 // output sums take 224 of its 512 registers).  K and V of a stage (32 keys, head_dim 64: 64) are read as fp32, split in registers and
@@ -21,8 +23,8 @@
 // 2,880 tokens with such values 1,545 us, with one in the last stage 2,218; 1,228 before).
 //
 // Bound: the vector instructions beside the products (matrix pipe busy 48 % of the cycles) and the clock, 1.93 GHz under this mix.  Measured,
-// fp32 instruction -> here, us a step: 4 tiles of 2,880 tokens, 8 heads x 128 1,228 -> 784 (176 TFLOP/s; a large fp32 matrix product
-// 154), 16 heads x 64 1,281 -> 822; 9,000 tokens, 12 heads x 128 4,264 -> 3,049; 4 tiles of 700, 8 heads x 64 57 -> 45.  Taken back:
+// fp32 instruction -> here, us a step: 4 tiles of 2,880 tokens, 8 heads x 128 1,228 -> 762 (180 TFLOP/s; a large fp32 matrix product
+// 154), 16 heads x 64 1,292 -> 817; 9,000 tokens, 12 heads x 128 4,266 -> 2,986; 4 tiles of 700, 8 heads x 64 58 -> 48.  Taken back:
 // 8 wavefronts of 16 queries with 16x16x32 products, two per SIMD (821: twice the fragment reads, and a wavefront whose neighbour is at
 // the barrier waits for every dependent product), V in rows with transposing reads (862).
 #include <atomic>
@@ -111,34 +113,29 @@ __global__ __launch_bounds__(kThreads, 1) void attention_f32_split_kernel(const 
   const int q0 = qblk * kBR + wave * 32;
   const char* const q_row = qh + (size_t)token_off8(q0 + lq < N ? q0 + lq : N - 1) * 32;
 
-  // ---- three bf16 parts of four fp32 numbers.  The first part is cut off, the others are rounded, so that the parts add up to the
-  // number, the first is finite wherever the number is and the second has no bias.  In five steps: a step's instructions do not depend
-  // on each other (a dependent one waits 9 cycles), and no more than six fit between two matrix products.
+  // ---- three bf16 parts of four fp32 numbers, each the nearest to what is left, so that they add up to the number; the second is at most
+  // 2^-8 of the number's power of two, the third 2^-17.  In five steps, of which the first and the third are a conversion and what
+  // takes its result (a dependent instruction waits 9 cycles); no more than six instructions fit between two matrix products.
   struct Split {
     float x[4];            // the numbers, what is left of them
     float y[4];
     uint32_t h[2], m[2], l[2];
     __device__ __forceinline__ void step(int i) {
-      if (i == 0) {
+      if (i == 0 || i == 2) {
+        uint32_t (&part)[2] = (i == 0) ? h : m;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) y[e] = __uint_as_float(__float_as_uint(x[e]) & 0xffff0000u);
+        for (int e = 0; e < 2; ++e) part[e] = cvt2(x[2 * e], x[2 * e + 1]);
+        asm volatile("" : "+v"(part[0]), "+v"(part[1]));   // both halves from this one
 #pragma unroll
-        for (int e = 0; e < 2; ++e) h[e] = __builtin_amdgcn_perm(__float_as_uint(x[2 * e + 1]), __float_as_uint(x[2 * e]), 0x07060302u);
-        asm volatile("" : "+v"(y[0]), "+v"(y[1]), "+v"(y[2]), "+v"(y[3]), "+v"(h[0]), "+v"(h[1]));
+        for (int e = 0; e < 2; ++e) {
+          y[2 * e] = __uint_as_float(part[e] << 16);
+          y[2 * e + 1] = __uint_as_float(part[e] & 0xffff0000u);
+        }
+        asm volatile("" : "+v"(y[0]), "+v"(y[1]), "+v"(y[2]), "+v"(y[3]));
       } else if (i == 1 || i == 3) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) x[e] -= y[e];
         asm volatile("" : "+v"(x[0]), "+v"(x[1]), "+v"(x[2]), "+v"(x[3]));
-      } else if (i == 2) {
-#pragma unroll
-        for (int e = 0; e < 2; ++e) m[e] = cvt2(x[2 * e], x[2 * e + 1]);
-        asm volatile("" : "+v"(m[0]), "+v"(m[1]));   // both halves from this one
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          y[2 * e] = __uint_as_float(m[e] << 16);
-          y[2 * e + 1] = __uint_as_float(m[e] & 0xffff0000u);
-        }
-        asm volatile("" : "+v"(y[0]), "+v"(y[1]), "+v"(y[2]), "+v"(y[3]));
       } else {
 #pragma unroll
         for (int e = 0; e < 2; ++e) l[e] = cvt2(x[2 * e], x[2 * e + 1]);

@@ -32,8 +32,8 @@ def _rel(got, want):
 
 
 # Every fp32 sum of products of first parts is rounded d/16 (scores) or n/16 (outputs) times by at most half a unit, 2^-24: as a
-# random walk of uniform errors sqrt((8 + n/16) / 3) 2^-24, under 3e-7 at 700 tokens; products of scores' errors with the scores (up to 5)
-# and the exponential's own 2^-22 double that.
+# random walk of uniform errors sqrt((8 + n/16) / 3) 2^-24, under 3e-7 at 700 tokens; what the parts leave out of every product (2^-24 at most,
+# 2^-27.4 in the mean square), products of scores' errors with the scores (up to 5) and the exponential's own 2^-22 double that.
 TOLERANCE = 6e-7
 
 
@@ -122,3 +122,59 @@ def test_infinities_and_nan(heads, T, th, tw, d):
     assert torch.equal(got.isnan(), want)
     got[3, :, 5] = 0.0
     assert bool(torch.isfinite(got[~want]).all())
+
+
+def _near_one(shape, gen):
+    """Numbers of [1, 1 + 2^-7), all 24 bits in use: what a first part that is cut off leaves of them is largest there."""
+    return 1.0 + torch.rand(shape, generator=gen, dtype=torch.float64).mul(2.0 ** -7).float()
+
+
+def single_score_products(d, n):
+    """Q and K have one channel.  Key 0 has score 0, key j one of -32 to -32.6 in the log2 domain, channel j of the output its probability.
+    Returns q, k, v and the scores [head][query][key] of the fp32 factors that are multiplied."""
+    gen = torch.Generator().manual_seed(d + n)
+    factor = float(torch.tensor(1.0 / math.sqrt(d))) * 1.4426950408889634
+    q, k, v = (torch.zeros(HEADS, n, d) for _ in range(3))
+    q[:, :, 0] = (_near_one((HEADS, n), gen).double() / factor).float()
+    k[:, 1:, 0] = -32.0 * _near_one((HEADS, n - 1), gen)
+    v[:, :d] = torch.eye(d)
+    scaled = (q[:, :, 0].double() * factor).float()
+    return q, k, v, scaled[:, :, None].double() * k[:, None, 1:d, 0].double()
+
+
+def check_single_score_products(out, scores):
+    """Of the product two thirds of a unit of 2^-24 are rounded off in the sum of its parts (|score| above 32), one at most is left out;
+    2^-23 of the exponential and twice 2^-24 of the normalisation are 2^-26 of a score of 32."""
+    got = torch.log2(out[:, :, 1:].double() / out[:, :, :1].double())
+    assert float((got / scores - 1.0).abs().max()) <= 2.3 * 2.0 ** -24
+
+
+def single_value_products(d, n):
+    """Key j has a probability just above one half of that of key 0, and two channels, 2 j with value 1 and 2 j + 1 with a generic one."""
+    gen = torch.Generator().manual_seed(d + n)
+    q, k, v = (torch.zeros(HEADS, n, d) for _ in range(3))
+    q[:, :, 0] = math.sqrt(d) / 1.4426950408889634
+    q[:, :, 0] *= 1.0 + torch.rand((HEADS, n), generator=gen) * 2.0 ** -10
+    k[:, 1:, 0] = -0.998 + 0.008 * torch.rand((HEADS, n - 1), generator=gen)
+    generic = _near_one((HEADS, d // 2), gen)
+    for j in range(1, d // 2):
+        v[:, j, 2 * j], v[:, j, 2 * j + 1] = 1.0, generic[:, j]
+    return q, k, v, generic
+
+
+def check_single_value_products(out, generic):
+    """One unit of 2^-24 at most is left out of the product of the generic value, one rounded off in the sum of its parts, one in either
+    channel's normalisation; the probability itself is the same in both channels."""
+    got = out[:, :, 3::2].double() / out[:, :, 2::2].double()
+    assert float((got / generic[:, None, 1:].double() - 1.0).abs().max()) <= 4.05 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_a_product_alone(d):
+    """No sum of many products hides what the parts leave out of one: below 2^-24 of it, where the first part is rounded (2^-22 where it is
+    cut off)."""
+    T, th, tw = 1, 8, 16
+    q, k, v, scores = single_score_products(d, th * tw)
+    check_single_score_products(_attend_window("f32", d, HEADS, T, th, tw, q, k, v), scores)
+    q, k, v, generic = single_value_products(d, th * tw)
+    check_single_value_products(_attend_window("f32", d, HEADS, T, th, tw, q, k, v), generic)

@@ -23,7 +23,7 @@
 // 2,880 tokens with such values 1,545 us, with one in the last stage 2,218; 1,228 before).
 //
 // Bound: the vector instructions beside the products (matrix pipe busy 48 % of the cycles) and the clock, 1.93 GHz under this mix.  Measured,
-// fp32 instruction -> here, us a step: 4 tiles of 2,880 tokens, 8 heads x 128 1,228 -> 762 (180 TFLOP/s; a large fp32 matrix product
+// fp32 instruction -> here, us a step: 4 tiles of 2,880 tokens, 8 heads x 128 1,228 -> 769 (179 TFLOP/s; a large fp32 matrix product
 // 154), 16 heads x 64 1,292 -> 817; 9,000 tokens, 12 heads x 128 4,266 -> 2,986; 4 tiles of 700, 8 heads x 64 58 -> 48.  Taken back:
 // 8 wavefronts of 16 queries with 16x16x32 products, two per SIMD (821: twice the fragment reads, and a wavefront whose neighbour is at
 // the barrier waits for every dependent product), V in rows with transposing reads (862).
@@ -215,10 +215,11 @@ __global__ __launch_bounds__(kThreads, 1) void attention_f32_split_kernel(const 
   Split sp;
   u32x4 vpart[3];
   // steps of moving a stage of K: range, 4 x (four elements, store), requests; of V: range, 2 channels x (2 x four elements, store), requests
-  constexpr int kKQuad = kSplitSteps + 1, kKSteps = 2 + 4 * kKQuad + 4, kVChannel = 2 * kSplitSteps + 1, kVSteps = 4 + 2 * kVChannel + 8;
+  constexpr int kKQuad = kSplitSteps + 1, kKSteps = 2 + 4 * kKQuad + 4, kVChannel = 2 * kSplitSteps + 1, kVRange = 8, kVSteps = kVRange + 2 * kVChannel + 8;
   auto range_step = [&](float a, float b, float& most) SG_INLINE { most = fmaxf(fmaxf(most, fabsf(a)), fabsf(b)); };
   float most2[2] = {0.f, 0.f};   // in two chains
   uint32_t least2[2] = {0xffffffffu, 0xffffffffu};
+  uint32_t zeros2[2] = {0, 0};   // all bits set: a value of 0 has been seen
   auto k_step = [&](auto m_tag, int j) SG_INLINE {
     constexpr int m = decltype(m_tag)::value;
     if constexpr (m < 2) {
@@ -245,19 +246,17 @@ __global__ __launch_bounds__(kThreads, 1) void attention_f32_split_kernel(const 
   };
   auto v_step = [&](auto m_tag, int j) SG_INLINE {
     constexpr int m = decltype(m_tag)::value;
-    if constexpr (m < 4) {
-#pragma unroll
-      for (int e = 4 * (m & 1); e < 4 * (m & 1) + 4; e += 2) {
-        const float a = vx[e][m >> 1], b = vx[e + 1][m >> 1];
-        range_step(a, b, v_most);
-        const uint32_t ta = (__float_as_uint(a) << 1) - 1u, tb = (__float_as_uint(b) << 1) - 1u;   // a zero becomes the largest
-        uint32_t& least = (e & 2) ? least2[1] : least2[0];
-        const uint32_t lo = ta < tb ? ta : tb;
-        least = lo < least ? lo : least;
-      }
-      asm volatile("" : "+v"(v_most), "+v"(least2[0]), "+v"(least2[1]));
-    } else if constexpr (m < 4 + 2 * kVChannel) {
-      constexpr int c = (m - 4) / kVChannel, at = (m - 4) % kVChannel, q = at / kSplitSteps, i = at % kSplitSteps;
+    if constexpr (m < kVRange) {
+      constexpr int e = 2 * (m & 3);
+      const float a = vx[e][m >> 2], b = vx[e + 1][m >> 2];
+      range_step(a, b, v_most);
+      const uint32_t ta = (__float_as_uint(a) << 1) - 1u, tb = (__float_as_uint(b) << 1) - 1u;   // a zero becomes the largest
+      const uint32_t lo = ta < tb ? ta : tb, hi = ta < tb ? tb : ta;
+      least2[m & 1] = lo < least2[m & 1] ? lo : least2[m & 1];
+      zeros2[m & 1] = hi > zeros2[m & 1] ? hi : zeros2[m & 1];
+      asm volatile("" : "+v"(v_most), "+v"(least2[m & 1]), "+v"(zeros2[m & 1]));
+    } else if constexpr (m < kVRange + 2 * kVChannel) {
+      constexpr int c = (m - kVRange) / kVChannel, at = (m - kVRange) % kVChannel, q = at / kSplitSteps, i = at % kSplitSteps;
       if constexpr (at < 2 * kSplitSteps) {
         if constexpr (i == 0) {
 #pragma unroll
@@ -274,13 +273,13 @@ __global__ __launch_bounds__(kThreads, 1) void attention_f32_split_kernel(const 
         for (int x = 0; x < 3; ++x) *(SG_LDS u32x4*)(uintptr_t)(dst + x * kPlane) = vpart[x];
       }
     } else {
-      load_v(m - 4 - 2 * kVChannel);
+      load_v(m - kVRange - 2 * kVChannel);
     }
   };
-  auto zero_tail_values = [&](int stage) SG_INLINE {   // values of keys >= N: probability 0 times an infinite last value
+  auto fill_tail_values = [&](int stage) SG_INLINE {   // values of keys >= N, whose probability is 0: neither an infinite last one nor 0
 #pragma unroll
     for (int e = 0; e < 8; ++e)
-      if (stage * kKeys + kPar * v_slot(e) + v_par >= N) vx[e] = f32x2{0.f, 0.f};
+      if (stage * kKeys + kPar * v_slot(e) + v_par >= N) vx[e] = f32x2{1.f, 1.f};
   };
   // K of stage j + 2 and V of stage j + 1 are in registers: their parts go to LDS, K of stage j + 3 and V of stage j + 2 are requested
   constexpr int kStageSteps = kKSteps + kVSteps;
@@ -291,19 +290,21 @@ __global__ __launch_bounds__(kThreads, 1) void attention_f32_split_kernel(const 
   };
   auto stage_begin = [&](int j) SG_INLINE {
     next_offsets(j + 3);
-    if (tail && j + 1 == n_blocks - 1) zero_tail_values(j + 1);
+    if (tail && j + 1 == n_blocks - 1) fill_tail_values(j + 1);
   };
   // What a wavefront has seen goes into one of two sets of flags, in turn: a wavefront that still reads one is not overtaken, as a barrier
   // lies between two calls.  The three parts of a factor or value hold all its 24 bits, and no sum overflows, if it lies between
   // 2^-100 and 2^60; below that factors are of no weight, values are if they are 0.  Probabilities below 2^-100 lose bits and below
-  // 2^-126 are 0, which is of no weight either unless values differ by more than 2^74.
+  // 2^-126 are 0.  That is of no weight beside the key that the reference comes from, with its probability of 1 or more, if all values lie
+  // between 2^-50 and 2^24; if that key's value is 0, such probabilities may be all that a channel holds.
   float gap = 0.f;   // the lowest log2 of a probability
   int told = 0;
   auto tell_range = [&]() SG_INLINE {
     const float factor = fmaxf(factor_most, fmaxf(most2[0], most2[1]));
     const uint32_t least = least2[0] < least2[1] ? least2[0] : least2[1];
+    const bool zero = (zeros2[0] > zeros2[1] ? zeros2[0] : zeros2[1]) == 0xffffffffu;
     const uint32_t seen = (__any(!(factor < kMaxFactor) || !(v_most < kMaxFactor) || least < kMinValue2) ? 1u : 0u) |
-                          (__any(gap < kLowest) ? 2u : 0u) | (__any(!(v_most < kWideMax) || least < kWideMin2) ? 4u : 0u);
+                          (__any(gap < kLowest) ? 2u : 0u) | (__any(!(v_most < kWideMax) || least < kWideMin2 || zero) ? 4u : 0u);
     if (lane == 0) *(SG_LDS uint32_t*)(uintptr_t)(lds0 + kFlags + (told & 1) * (kWaves * 4) + wave * 4) = seen;
   };
   auto meet = [&]() SG_INLINE {
@@ -463,7 +464,7 @@ __global__ __launch_bounds__(kThreads, 1) void attention_f32_split_kernel(const 
   for_range<-2, 0>([&](auto j_tag) SG_INLINE {   // K of stage j + 2, V of stage j + 1
     constexpr int j = decltype(j_tag)::value;
     next_offsets(j + 3);
-    if (j == -1 && tail && n_blocks == 1) zero_tail_values(0);
+    if (j == -1 && tail && n_blocks == 1) fill_tail_values(0);
     for_range<0, kStageSteps>([&](auto m) SG_INLINE {   // no V in the first: only its requests
       if constexpr (j == -1 || m < kKSteps || m >= kStageSteps - 8) stage_step(m, j);
     });

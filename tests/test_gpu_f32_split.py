@@ -102,6 +102,27 @@ def test_probabilities_below_the_smallest_normal_number_count(d):
     assert _rel(got, want) <= TOLERANCE
 
 
+@pytest.mark.parametrize("log2p", [-112, -125, -133, -140])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads,T,th,tw,key", [(HEADS, 1, 5, 13, 0), (HEADS, 1, 5, 13, 64), (30, 2, 17, 20, 0), (30, 2, 17, 20, 679)])
+def test_small_probabilities_are_all_that_a_channel_holds(heads, T, th, tw, key, d, log2p):
+    """Channel 0 is 0 but for one key, whose probability is 2^log2p of the others' and whose value is an ordinary number.  The probability is a
+    multiple of 2^-149; the roundings of the scaled query, the score, the exponent, log2(e) and the exponential's argument are 2^-24
+    of |log2p| each."""
+    n = T * th * tw
+    q, k, v = _inputs(heads, n, d)
+    q[7], k[7] = 0.0, 0.0
+    q[7, :, 0] = 1.0
+    k[7, key, 0] = log2p / math.log2(math.e) * math.sqrt(d)
+    v[7, :, 0] = 0.0
+    v[7, key, 0] = 2.0 ** 20
+    want = _exact(q, k, v)
+    got = _attend_window("f32", d, heads, T, th, tw, q, k, v)
+    assert float((got[7, :, 0].double() / want[7, :, 0] - 1.0).abs().max()) <= 2.0 ** (-150 - log2p) - log2p * 5 * math.log(2.0) * 2.0 ** -24
+    got[7, :, 0], want[7, :, 0] = 1.0, 1.0
+    assert _rel(got, want) <= TOLERANCE
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("heads,T,th,tw", [(HEADS, 1, 5, 13), (30, 2, 17, 20)])
 def test_infinities_and_nan(heads, T, th, tw, d):

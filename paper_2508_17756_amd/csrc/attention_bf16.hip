@@ -246,14 +246,18 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
     chunk = (uint32_t)(D == 128 ? c : c & 7);
     return D == 128 ? slot_w : 2 * slot_w + (c >> 3);
   };
+  auto lane_offset = [&](int l, int u, bool is_v) SG_INLINE -> uint32_t {
+    uint32_t chunk;
+    const int t = slot_token(l, u, is_v, chunk);
+    return ((uint32_t)t * vw.st16 + chunk) << 4;
+  };
+  // The short form of packed tiles of head_dim 64 works these offsets out for every stage: kept over the iterations they are spilled, and
+  // their reload waits for all transfers in flight.  us a step, spilled, worked out (other form): 20 tiles, 48 heads, of 1,000 tokens 578, 503
+  // (524), of 2,000 1,789, 1,440 (1,457); one tile, 8 heads, of 700 15.5, 14.6 (15.8).
+  constexpr bool kFormed = SHORT && D == 64 && MODE == kLinear && !REFRESH;
   uint32_t klane[2], vlane[2];
 #pragma unroll
-  for (int u = 0; u < 2; ++u) {
-    uint32_t kc, vc;
-    const int kt = slot_token(lane, u, false, kc), vt = slot_token(lane, u, true, vc);
-    klane[u] = ((uint32_t)kt * vw.st16 + kc) << 4;
-    vlane[u] = ((uint32_t)vt * vw.st16 + vc) << 4;
-  }
+  for (int u = 0; u < 2; ++u) { klane[u] = lane_offset(lane, u, false); vlane[u] = lane_offset(lane, u, true); }
   const uint32_t dma_dst = lds0 + wave * (8 * kRowBytes);
   uint32_t plan_first = 0, plan_jump = 0, plan_info = 0;   // lane l: this wavefront's run of stage 64 m + l
   const int edge0 = (wx0 + vw.tw > vw.W) ? vw.W - wx0 : 0x3fffffff;   // tokens of a tile row before the canvas edge (none crossed: many)
@@ -303,10 +307,13 @@ __global__ __launch_bounds__(kThreads) void attention_bf16_kernel(const View16 v
     }
   };
   auto move_run = [&](const char* kp, const char* vp, uint32_t dst) SG_INLINE {
+    uint32_t all = ~0u;
+    if (kFormed) asm volatile("" : "+s"(all));
+    const int l = (int)__builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0));   // lane, which is spilled as well
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      dma16(kp, klane[u], dst + u * (4 * kRowBytes));
-      dma16(vp, vlane[u], dst + kVRegion + u * (4 * kRowBytes));
+      dma16(kp, kFormed ? lane_offset(l, u, false) : klane[u], dst + u * (4 * kRowBytes));
+      dma16(vp, kFormed ? lane_offset(l, u, true) : vlane[u], dst + kVRegion + u * (4 * kRowBytes));
     }
   };
   // packed tiles and walked windows: pointers to the run of the stage to issue; a walk also knows its tile row and column
@@ -953,10 +960,13 @@ int launch_attention_bf16(const TileView& tv, int heads, int head_dim, float sca
       return SG_OK;
     };
     // Short form, us a step with the other form and with it, 9 tiles, 24 heads.  head_dim 128: 300 tokens 42.6 and 39.7, 700 87.7 and 82.7,
-    // 1,365 256 and 250, 1,500 276 and 273, 2,000 417 and 418, 4,600 1,933 and 1,974; one tile of 700 20.0 and 18.2.  head_dim 64: packed, of
+    // 1,365 256 and 250, 1,500 276 and 273, 2,000 417 and 418, 4,600 1,933 and 1,974; one tile of 700 20.0 and 18.2.  head_dim 64: refreshed, of
     // which six run, 300 52.9 and 50.9, 1,500 185 and 177, 3,000 481 and 477, 4,600 941 and 951; windows of 1,500 217 and 202, 3,000 674 and
-    // 671, 4,600 1,419 and 1,440.
-    const bool is_short = tv.N <= (head_dim == 64 ? 3072 : 1536);   // 24 stages
+    // 671, 4,600 1,419 and 1,440; packed without a refresh, 48 heads, 9 tiles of 400 101 and 97, 1,000 243 and 235, 2,000 657 and 649, 3,000
+    // 1,270 and 1,275, one of 3,000 135 and 138 (8 heads 36.4 and 38.0).  Of many rounds, 20 tiles, 48 heads: head_dim 128, 1,000 626 and 606,
+    // 1,536 1,190 and 1,180; head_dim 64, refreshed, 1,500 1,016 and 985, 3,000 2,895 and 2,878, windows of 1,500 887 and 834, 3,000 2,936 and 2,921.
+    const bool plain64 = head_dim == 64 && !window && !fuse_refresh;
+    const bool is_short = tv.N <= (plain64 ? 2048 : head_dim == 64 ? 3072 : 1536);   // 24 stages, 16
     int st = SG_OK;
 #define SG_BF16(D, MODE, LATE, REFRESH, SLOT) \
   (is_short ? launch(attention_bf16_kernel<D, MODE, LATE, REFRESH, true>, SLOT) : launch(attention_bf16_kernel<D, MODE, LATE, REFRESH, false>, SLOT + 8))

@@ -38,6 +38,8 @@ SIZES = [
     (2, 23, 32),    # 1,472: 23 | 12
     (1, 48, 32),    # 1,536: 24 | 12, the last of the short form for head_dim 128
     (1, 53, 29),    # 1,537: 25 | 13
+    (1, 32, 64),    # 2,048: 32 | 16, the last of the short form for packed tiles of head_dim 64 without a refresh
+    (1, 3, 683),    # 2,049: 33 | 17, the last with one key
     (2, 32, 48),    # 3,072: 48 | 24, the last of the short form for head_dim 64
     (1, 7, 439),    # 3,073: 49 | 25
     # the other form: 1 iteration, groups of four of the steady loop, 4 to 7 iterations

@@ -526,7 +526,7 @@ __global__ __launch_bounds__(kThreads, 1) void attention_f32_split_kernel(const 
     if (tell) narrow = out_of_range();
   }
   if (narrow) {   // numbers beyond the parts' range: all over on the fp32 instruction
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < kWaves && qblk * kBR + 32 * i < N; ++i) {   // the same in all wavefronts
       attend_f32<D, 1, 4, MODE, false>(vw, scale, tab, head_bytes, tile, head, qblk * kBR + 32 * i, wy0, wx0, lds);
       __syncthreads();
     }

@@ -84,6 +84,37 @@ def test_numbers_that_the_parts_do_not_hold(heads, T, th, tw, d, name):
     assert _rel(got, _exact(q, k, v)) <= TOLERANCE
 
 
+@pytest.mark.parametrize("name", ["large_keys", "large_values", "one_large_value_in_the_last_stage"])
+@pytest.mark.parametrize("where", ["packed", "fixed", "wrapped"])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads,T,th,tw", [(120, 1, 3, 43), (51, 7, 10, 10)])
+def test_numbers_that_the_parts_do_not_hold_in_packed_and_wrapped_tiles(heads, T, th, tw, d, where, name):
+    """129 tokens: one query in the last workgroup, of whose four blocks of 32 only the first is done over; 700: 60 in three blocks."""
+    q, k, v = _inputs(heads, T * th * tw, d)
+    OUT[name](q, k, v)
+    got = _attend_window("f32", d, heads, T, th, tw, q, k, v, wrapped=where == "wrapped", packed=where == "packed")
+    assert _rel(got, _exact(q, k, v)) <= TOLERANCE
+
+
+# The ends of the range that the parts hold: 2^-100 <= |v| < 2^60 for values that are not 0, scaled queries and keys below 2^60
+IN = {
+    "smallest_values": lambda q, k, v: v[7].copy_(torch.sign(v[7]) * (1.0 + v[7].abs().fmod(1.0)) * 2.0 ** -100),
+    "largest_values": lambda q, k, v: v[7].copy_(torch.sign(v[7]) * (1.0 + v[7].abs().fmod(1.0)) * 2.0 ** 58),
+    "large_keys": lambda q, k, v: (_put(k, 7, slice(None), 2.0 ** 57), _put(q, 7, slice(None), 2.0 ** -57)),
+    "large_queries": lambda q, k, v: (_put(q, 7, slice(None), 2.0 ** 59), _put(k, 7, slice(None), 2.0 ** -59)),
+}
+
+
+@pytest.mark.parametrize("name", sorted(IN))
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads,T,th,tw", [(HEADS, 1, 5, 13), (30, 2, 17, 20)])
+def test_the_ends_of_the_range_that_the_parts_hold(heads, T, th, tw, d, name):
+    q, k, v = _inputs(heads, T * th * tw, d)
+    IN[name](q, k, v)
+    got = _attend_window("f32", d, heads, T, th, tw, q, k, v)
+    assert _rel(got, _exact(q, k, v)) <= TOLERANCE
+
+
 @pytest.mark.parametrize("d", [64, 128])
 def test_probabilities_below_the_smallest_normal_number_count(d):
     """Key 0 has a score 133 below the others' in the log2 domain, and values of 2^100: the products, 2^-33, are all that channel 0 holds."""

@@ -83,3 +83,19 @@ def test_the_cache_refresh_copies_the_input(T, th, tw, d):
     assert torch.equal(cache_x[0], x[0]) and torch.equal(cache_x[1], x[1])
     assert not out[1].any()
     assert_close(out[0].cpu().double().reshape(HEADS, n, d).numpy(), _exact(*x[0].cpu().reshape(3, HEADS, n, d)).numpy(), "bf16")
+
+
+@pytest.mark.parametrize("where", ["fixed", "wrapped"])
+@pytest.mark.parametrize("d,T,th,tw,stride", [
+    (128, 2, 40, 21, 1 << 19),   # 1,680 tokens: 27 stages, runs of 8 tokens broken
+    (128, 2, 35, 24, 1 << 19),   # 1,680, unbroken unless the window wraps
+    (64, 4, 37, 21, 1 << 18),    # 3,108: 25 stages, runs of 16 broken
+    (64, 5, 50, 13, 1 << 18),    # 3,250: 26, narrower than a run
+    (64, 4, 25, 32, 1 << 18),    # 3,200: 25 whole, unbroken unless the window wraps
+])
+def test_windows_of_heads_beyond_4_gib_in_the_other_form(d, T, th, tw, stride, where):
+    """More than 24 stages of a head that spans 4 GiB or more: broken runs are looked up with 64-bit addresses."""
+    n = T * th * tw
+    q, k, v = (x[:1] for x in _inputs(n, d))
+    got = _attend_window("bf16", d, 1, T, th, tw, q, k, v, wrapped=where == "wrapped", token_stride=stride)
+    assert_close(got.double().numpy(), _exact(q, k, v).numpy(), "bf16", "%d tokens x %d" % (n, d))

@@ -161,7 +161,8 @@ def test_fp32_attention_is_as_close_to_fp64_as_plain_fp32(th, tw, d):
     assert float((got - ref).norm()) <= 1.05 * float((plain - ref).norm())
 
 
-# 1 head: eight shares of the keys; 48 heads: enough workgroups for four.  400 tokens are 13 blocks of 32 keys, dealt to the shares in turn.
+# 1 head: eight shares of the keys, 400 tokens are 13 blocks of 32 keys, dealt to the shares in turn; 48 heads: the kernel on the bf16 instruction, but
+# four shares for heads beyond 4 GiB and eight up to 64 tokens.
 @pytest.mark.parametrize("heads", [1, 48])
 @pytest.mark.parametrize("d", [64, 128])
 def test_fp32_attention_takes_values_up_to_the_largest_number(d, heads):
@@ -226,7 +227,8 @@ def test_fp32_attention_takes_an_infinite_last_value(T, th, tw, d, heads):
 @pytest.mark.parametrize("wrapped", [False, True], ids=["fixed", "wrapped"])
 @pytest.mark.parametrize("stride", [1 << 19, 1 << 20], ids=["3gib", "6gib"])
 def test_fp32_attention_of_heads_of_gibibytes(stride, wrapped, d, heads):
-    """Byte offsets inside a head that take all 32 bits, and that leave them, with either split of the keys."""
+    """Byte offsets inside a head that take all 32 bits (48 heads: in the kernel on the bf16 instruction), and that leave them, with either
+    split of the keys."""
     n = 400
     gen = torch.Generator().manual_seed(n + d)
     q, k, v = (torch.randn(heads, n, d, generator=gen) for _ in range(3))

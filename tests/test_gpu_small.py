@@ -54,9 +54,9 @@ def test_attention_f32_key_split(th, tw):
 @pytest.mark.parametrize("view", [False, True], ids=["packed", "wrapped"])
 def test_attention_f32_growing_scores(d, heads, th, tw, view):
     """Scores that grow along the key axis, so that the softmax reference has to move past its slack in every share of the
-    keys; 9 heads of about 1,000 tokens take 64 queries per workgroup (head_dim 64), the others 32; 255, 256, 272, 989 and
-    1,000 tokens end in partial and whole 32-key blocks; 16 and 32 heads of 1,023 and 1,030 tokens make enough workgroups for
-    four shares of the keys instead of eight, with 64 and with 32 queries each.  The logits reach 12: their rounding, a few times 12 * 2^-24,
+    keys; 9 heads of about 1,000 tokens take 64 queries per workgroup (head_dim 64), those of 255, 256 and 272 32; 255, 256, 272, 989 and
+    1,000 tokens end in partial and whole 32-key blocks; 16 and 32 heads of 1,023 and 1,030 tokens go to the kernel on the bf16
+    instruction.  (Four shares of the keys: test_gpu_attention_routes.py.)  The logits reach 12: their rounding, a few times 12 * 2^-24,
     is the relative error of the probabilities (the bound below leaves a factor of three)."""
     g = _geom("f32g", 1, 2 * th, 2 * tw, th, tw, th, tw, heads, d, "f32", 900 + th) if view else _geom(
         "f32g", 1, th, tw, th, tw, th, tw, heads, d, "f32", 900 + th)
@@ -125,10 +125,11 @@ def test_attention_bf16_head_dim_64(case):
         assert_close(to_f64(got), oracle_tile_attention_full(g, q, k, v, tr, tc), "bf16", f"{name} {tr},{tc}")
 
 
-@pytest.mark.parametrize("heads,th,tw", [(2, 16, 28), (2, 20, 23), (64, 14, 33), (65, 14, 33), (25, 24, 50), (26, 24, 50), (26, 25, 49)])
+@pytest.mark.parametrize("heads,th,tw", [(2, 16, 28), (2, 20, 23), (64, 14, 33), (65, 14, 33), (25, 24, 50), (26, 24, 50), (26, 25, 49),
+                                         (32, 24, 40), (33, 24, 40), (33, 31, 31)])
 def test_attention_bf16_head_dim_64_windows_around_the_kernels_sizes(heads, th, tw):
     """Windows of head_dim 64 on either side of the rule that picks the kernel: 448 and 460 tokens with few workgroups; 462 tokens with 128
-    and 130 of them on 256 compute units, 1,200 with 125 and 130, 1,225 with 130."""
+    and 130 of them on 256 compute units, 960 with 128 and 132, 961 with 132; behind it 1,200 with 125 and 130, 1,225 with 130."""
     g = _geom("rule", 1, 2 * th, 2 * tw, th, tw, th, tw, heads, 64, "bf16", 29 + heads)
     q, k, v = canvas_qkv(g)
     out = gpu_tile_attention(g, q, k, v, 1, 0)
@@ -139,8 +140,8 @@ def test_attention_bf16_head_dim_64_windows_around_the_kernels_sizes(heads, th, 
 
 @pytest.mark.parametrize("shape", [(3, 20, 25), (2, 33, 37), (4, 16, 32)], ids=["n1500", "n2442", "n2048"])
 def test_attention_bf16_head_dim_64_long_packed(shape):
-    """Packed head_dim-64 tiles long enough for the steady loop of the streaming kernel (128-key stages,
-    two keys per LDS slot): 11.7, 19.1 and exactly 16 stages."""
+    """Packed head_dim-64 tiles of many stages of the streaming kernel (128 keys, two keys per LDS slot): 11.7 and exactly 16 in
+    its form for few stages, 19.1 in the one with a steady loop."""
     T, H, W = shape
     g = _geom("d64long", T, H, W, H, W, H, W, 2, 64, "bf16", 27)
     q, k, v = canvas_qkv(g)

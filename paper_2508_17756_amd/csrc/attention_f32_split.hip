@@ -19,12 +19,14 @@
 // lane of PV contracts them.
 //
 // Numbers whose parts bf16's range does not hold (tell_range says which) are looked for on the way; a workgroup whose tile has one does its
-// queries once more on the fp32 instruction, with the result and the range of the kernel for few queries, at 0.8 of its speed (the step of
-// 2,880 tokens with such values 1,545 us, with one in the last stage 2,218; 1,228 before).
+// queries once more on the fp32 instruction, with the result and the range of the kernel for few queries, at 0.8 of its speed.  With such
+// values against the fp32 instruction alone: the step of 2,880 tokens 1,547 us and 1,220, with one in the last stage 2,219; 120 heads of 129 tokens x
+// 64 42 and 23.  (A second launch for them would need flags in memory, which the call does not have.)
 //
-// Bound: the vector instructions beside the products (matrix pipe busy 48 % of the cycles) and the clock, 1.93 GHz under this mix.  Measured,
-// fp32 instruction -> here, us a step: 4 tiles of 2,880 tokens, 8 heads x 128 1,228 -> 769 (179 TFLOP/s; a large fp32 matrix product
-// 154), 16 heads x 64 1,292 -> 817; 9,000 tokens, 12 heads x 128 4,266 -> 2,986; 4 tiles of 700, 8 heads x 64 58 -> 48.  Taken back:
+// Bound: the vector instructions beside the products (matrix pipe busy 48 % of the cycles) and the clock, 2.06 GHz under this mix.  Measured,
+// fp32 instruction -> here, us a step, on one box (others are up to 5 % faster): 4 tiles of 2,880 tokens, 8 heads x 128 1,225 -> 812 (167 TFLOP/s;
+// a large fp32 matrix product 154), 16 heads x 64 1,286 -> 842; 9,000 tokens, 12 heads x 128 4,276 -> 3,119; 4 tiles of 700, 8 heads x 64 62 -> 50;
+// 200 heads of 65 tokens x 128 23.3 -> 19.5.  Of the first, 0.8 % are the test of the values for 0.  Taken back:
 // 8 wavefronts of 16 queries with 16x16x32 products, two per SIMD (821: twice the fragment reads, and a wavefront whose neighbour is at
 // the barrier waits for every dependent product), V in rows with transposing reads (862).
 #include <atomic>
@@ -175,7 +177,7 @@ __global__ __launch_bounds__(kThreads, 1) void attention_f32_split_kernel(const 
   // ---- staging.  K: thread t moves 4 channels (of key t / 16 % 2 of the slot, head_dim 64) of slots t / 32 + 8 u of every stage;
   // 16-byte chunk c of slot r sits at chunk c ^ (r % 16).  V: thread t moves 8 slots of channels 2 (t % 64) and + 1, those slots that one
   // lane of PV contracts, so that V lies transposed: row = key of the slot * 64 + channel, 4 chunks of 8 slots, chunk g at
-  // g ^ (row / 4 % 4) of row row ^ (row / 16 % 2).  Fragment reads and stores fall on all banks.
+  // g ^ (row / 4 % 4) of row row ^ (row / 16 % 2).  Fragment reads and stores are laid out over all banks (14 % of the LDS cycles are conflicts even so).
   const int k_slot = tid >> 5, k_par = (D == 128) ? 0 : ((tid >> 4) & 1);
   const uint32_t k_ch4 = (tid & (D / 4 - 1)) * 16;
   uint32_t kdst[2];   // u even, odd (+ 16 slots for u >= 2)
@@ -363,7 +365,7 @@ __global__ __launch_bounds__(kThreads, 1) void attention_f32_split_kernel(const 
     asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(va), "v"(pb));
   };
 
-  float t[2 * kNP];             // scores of the stage, then (unused)
+  float t[2 * kNP];             // scores of the stage
   auto mask_tail = [&](int stage) SG_INLINE {
 #pragma unroll
     for (int i = 0; i < 2 * kNP; ++i) {

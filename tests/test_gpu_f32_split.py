@@ -230,3 +230,20 @@ def test_a_product_alone(d):
     check_single_score_products(_attend_window("f32", d, HEADS, T, th, tw, q, k, v), scores)
     q, k, v, generic = single_value_products(d, th * tw)
     check_single_value_products(_attend_window("f32", d, HEADS, T, th, tw, q, k, v), generic)
+
+
+# The number of [1, 2) of whose square the parts leave out most, 2^-24.01 (2^-22.02 of the second's, if the first part were cut off)
+REPEATED = [1.0038986206054688, 1.0077972412109375]
+
+
+@pytest.mark.parametrize("number", REPEATED)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("heads,T,th,tw", [(HEADS, 1, 5, 13), (51, 7, 10, 10)])
+def test_numbers_of_one_mantissa(heads, T, th, tw, d, number):
+    """What is left out of every product is the same share of it and does not average out."""
+    n = T * th * tw
+    gen = torch.Generator().manual_seed(n + d)
+    q, k, v = (number * torch.exp2(torch.randint(-2, 2, (heads, n, d), generator=gen).float()) *
+               (2.0 * torch.randint(0, 2, (heads, n, d), generator=gen) - 1.0) for _ in range(3))
+    got = _attend_window("f32", d, heads, T, th, tw, q, k, v)
+    assert _rel(got, _exact(q, k, v)) <= TOLERANCE

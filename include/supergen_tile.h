@@ -117,7 +117,7 @@ int sg_workspace_bytes(int32_t n_tiles, size_t* out_bytes);
  * are scaled in fp32 behind the product instead, against the true running maximum, and take any finite V.
  * fp32 problems take any finite V as well.  A NaN in Q, K or V reaches every output that depends on it, and no other.
  * fp32 problems multiply on the fp32 matrix instruction or, where tiles x heads x tokens fill the compute units with workgroups
- * of 128 queries, on the bf16 one, which is up to 1.6 times as fast: every number is the sum of three bf16 numbers, 24 bits in three
+ * of 128 queries (many tiles or heads of up to 256 tokens: where that is the faster), on the bf16 one, which is up to 1.6 times as fast: every number is the sum of three bf16 numbers, 24 bits in three
  * times 8, and six of the nine products of two numbers' parts are summed in fp32; at most 2^-24 of a product is left out.  The
  * error against fp64 is a fifth to a quarter smaller (2,880 tokens x 128: 3.9e-7, 5.2e-7 on the fp32 instruction), but which of the two a tile gets, and
  * with it the last bits of its output, depends on the number of tiles, heads and tokens of the call and on the device.  128 queries

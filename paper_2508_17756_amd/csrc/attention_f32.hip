@@ -55,6 +55,22 @@ __global__ __launch_bounds__(64 * KS, 2) void attention_f32_kernel(
   attend_f32<D, QB, KS, MODE, WIDE>(vw, scale, tab, head_bytes, tile, head, qblk * (QB * 32), wy0, wx0, lds);
 }
 
+// Several rounds of tiles of up to 256 tokens: start and end of a round, which nothing runs beside in the split kernel, are as long as three to
+// five stages, so that the rounds alone do not tell.  Times in us, fitted to both kernels' at 65 - 1,100 tokens (within 3 to 7 % in the mean
+// square, 18 at most): of the split kernel a round and its stages of 32 keys (head_dim 64: 64); here, of two workgroups per compute unit, a round
+// of blocks of 32 keys dealt to four shares, and of what stays on average beside it a workgroup and its blocks.  us here and on the split kernel,
+// head_dim 64: 342 heads of 65 tokens 18.9 and 26.2, 769 38.2 and 52.7, 512 of 129 58.0 and 64.5, 192 of 192 34.7 and 32.1, 640 of 97 52.1 and 42.4;
+// head_dim 128: 769 of 65 62.2 and 74.8, 769 of 97 97.4 and 87.8.  Where this chooses wrongly it costs up to 8 % (wrapped windows of 65 tokens x
+// 128 11).  One round and longer tiles go by the rounds alone, which costs them 7 % at most.
+bool split_is_faster(int tokens, int head_dim, int64_t heads, int64_t rounds, bool two_blocks, int n_cu) {
+  const int blocks = (tokens + 31) / 32, dealt = (blocks + 3) / 4;
+  const int64_t workgroups = heads * (two_blocks ? (tokens + 63) / 64 : blocks);
+  const double full = (double)((workgroups + 2 * n_cu - 1) / (2 * n_cu)), part = (double)workgroups / (2 * n_cu);
+  if (head_dim == 128) return rounds * (11.8 + 2.56 * blocks) < full * 4.1 * dealt + part * (5.9 + blocks) + 6.0;
+  const double split = rounds * (8.0 + 2.65 * ((blocks + 1) / 2)) + 1.0;
+  return split < (two_blocks ? full * 7.3 * dealt + part * (6.1 + 3.1 * dealt) + 7.0 : full * 2.6 * dealt + part * (3.2 + 0.43 * blocks) + 4.0);
+}
+
 }  // namespace
 
 int launch_attention_f32(const TileView& tv, int heads, int head_dim, float scale, const AttnBatch& b, hipStream_t s) {
@@ -107,8 +123,8 @@ int launch_attention_f32(const TileView& tv, int heads, int head_dim, float scal
     // for 32 (see there): taken where the rounds over the device say so, however many of the tiles the gate lets run.
     bool split = !far;
     for (int a = b.run_flags ? 1 : n; a <= n && split; ++a) {
-      const int64_t big = (int64_t)a * heads * ((tv.N + 127) / 128), small = (int64_t)a * heads * ((tv.N + 31) / 32);
-      split = 12 * ((big + n_cu - 1) / n_cu) < 5 * ((small + n_cu - 1) / n_cu);
+      const int64_t big = ((int64_t)a * heads * ((tv.N + 127) / 128) + n_cu - 1) / n_cu, small = ((int64_t)a * heads * ((tv.N + 31) / 32) + n_cu - 1) / n_cu;
+      split = 12 * big < 5 * small && (big == 1 || tv.N > 256 || split_is_faster(tv.N, head_dim, (int64_t)a * heads, big, two_blocks, n_cu));
     }
     int st;
 #define SG_F32_MODES(D, QB, KS, WIDE, SLOT)                                                        \

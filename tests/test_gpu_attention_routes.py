@@ -117,8 +117,8 @@ F32_ROUTES = [
     ("split_window_128", lambda: Window(120, 1, 3, 43, 128, "f32"), [(SPLIT, "128,1")]),
     ("split_wide_strides", lambda: Window(48, 1, 16, 25, 128, "f32", token_stride=1 << 19), [(SPLIT, "128,1")]),
     ("beyond_4_gib", lambda: Window(48, 1, 16, 25, 128, "f32", token_stride=1 << 20), [(F32, "128,1,4,1,true")]),
-    ("split_gated_64", lambda: _gated(4, 200, 1, 8, 12, 64, "f32"), [(SPLIT, "64,0")]),
-    ("split_gated_128", lambda: _gated(4, 200, 1, 5, 13, 128, "f32"), [(SPLIT, "128,0")]),
+    ("split_gated_64", lambda: _gated(4, 250, 1, 9, 11, 64, "f32"), [(SPLIT, "64,0")]),
+    ("split_gated_128", lambda: _gated(4, 250, 1, 9, 11, 128, "f32"), [(SPLIT, "128,0")]),
     ("gated_64_queries", lambda: _gated(9, 12, 1, 16, 25, 64, "f32"), [(F32, "64,2,4,0,false")]),
     ("gated_32_queries_64", lambda: _gated(8, 5, 1, 16, 25, 64, "f32"), [(F32, "64,1,4,0,false")]),
     ("gated_32_queries_128", lambda: _gated(9, 12, 1, 16, 25, 128, "f32"), [(F32, "128,1,4,0,false")]),
@@ -159,6 +159,15 @@ def test_windows_of_head_dim_64_with_few_keys(heads, tokens, kernel):
     assert [n for n, _ in _attention_kernels(Window(heads, 1, 16, tokens // 16, 64, "bf16"))] == [kernel]
 
 
+@pytest.mark.parametrize("d,heads,th,tw,kernel", [
+    (64, 200, 5, 13, SPLIT), (64, 342, 5, 13, F32), (64, 769, 5, 13, F32), (64, 512, 3, 43, F32), (64, 512, 8, 12, F32), (64, 257, 8, 25, F32),
+    (64, 257, 1, 97, F32), (64, 640, 1, 97, SPLIT), (64, 385, 7, 23, SPLIT), (64, 192, 16, 16, SPLIT), (64, 129, 16, 16, F32),
+    (128, 200, 5, 13, SPLIT), (128, 769, 5, 13, F32), (128, 257, 8, 16, F32), (128, 769, 1, 97, SPLIT), (128, 359, 3, 43, SPLIT)])
+def test_fp32_calls_of_several_rounds_of_short_tiles(d, heads, th, tw, kernel):
+    """One round of 128-query workgroups goes to the split kernel; several of up to 256 tokens only where they hide its start and end."""
+    assert [n for n, _ in _attention_kernels(Window(heads, 1, th, tw, d, "f32", packed=True))] == [kernel]
+
+
 def _exact(x, scale):
     q, k, v = (t.double() for t in x)
     out = torch.empty(q.shape, dtype=torch.float64)
@@ -178,10 +187,10 @@ def _fp32_scale(d):
 # ---- the split kernel over several tiles and under run flags
 @pytest.mark.parametrize("reused", [[], [1], [0, 3]], ids=["all", "one_reused", "two_reused"])
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("th,tw", [(5, 13), (8, 16)])
+@pytest.mark.parametrize("th,tw", [(9, 11), (8, 16)])
 def test_split_kernel_attends_the_active_tiles(th, tw, d, reused):
     """Tile 2 holds values that the parts do not (one head of it), beside tiles of ordinary numbers; reused tiles are skipped."""
-    heads = 200
+    heads = 250
     gen = torch.Generator().manual_seed(d + th)
     x = [torch.randn(3, heads, th * tw, d, generator=gen) for _ in range(4)]
     x[2][2, 7] *= 2.0 ** 100
@@ -196,9 +205,9 @@ def test_split_kernel_attends_the_active_tiles(th, tw, d, reused):
 @pytest.mark.parametrize("shift", [(0, 0), (5, 9)], ids=["fixed", "wrapped"])
 @pytest.mark.parametrize("d", [64, 128])
 def test_split_kernel_attends_overlapping_tiles_of_a_canvas(d, shift):
-    """2 x 3 tiles of 1 x 13 x 10 tokens that share rows and columns, 42 heads: one launch, two workgroups a head, the second with two
+    """2 x 3 tiles of 1 x 13 x 10 tokens that share rows and columns, 21 heads: one launch, two workgroups a head, the second with two
     queries; a value that the parts do not hold lies in some of the windows only."""
-    heads = 42
+    heads = 21
     g = TileGeometry("over", 1, 20, 24, 13, 10, 7, 7, 2, 3, heads, d, "f32", 0)
     qkv = [randn_tensor(g.grid_shape, "f32", 40 + i) for i in range(3)]
     qkv[2][5, 0, 9, 16, 3] = 2.0 ** 90

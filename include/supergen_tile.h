@@ -116,14 +116,15 @@ int sg_workspace_bytes(int32_t n_tiles, size_t* out_bytes);
  * partition), and those of head_dim 128 whose head spans 4 GiB or more and whose window wraps or is no multiple of 8 tokens wide,
  * are scaled in fp32 behind the product instead, against the true running maximum, and take any finite V.
  * fp32 problems take any finite V as well.  A NaN in Q, K or V reaches every output that depends on it, and no other.
- * fp32 problems multiply on the fp32 matrix instruction or, where tiles x heads x tokens fill the compute units with workgroups
- * of 128 queries (many tiles or heads of up to 256 tokens: where that is the faster), on the bf16 one, which is up to 1.6 times as fast: every number is the sum of three bf16 numbers, 24 bits in three
- * times 8, and six of the nine products of two numbers' parts are summed in fp32; at most 2^-24 of a product is left out.  The
- * error against fp64 is a fifth to a quarter smaller (2,880 tokens x 128: 3.9e-7, 5.2e-7 on the fp32 instruction), but which of the two a tile gets, and
- * with it the last bits of its output, depends on the number of tiles, heads and tokens of the call and on the device.  128 queries
- * whose head holds numbers that the parts do not are done over on the fp32 instruction, in the same launch: |V| below 2^-100 and not 0,
- * |V|, |K| or |Q * scale * log2(e)| of 2^60 and more, or a score 69 below the largest before it together with a V that is 0, below 2^-50 or from
- * 2^24 on.  Such calls take 1.3 times, at worst 1.8 times, what the fp32 instruction alone would.
+ * fp32 problems multiply on the fp32 matrix instruction or, where tiles x heads x tokens fill the compute units with workgroups of 128
+ * queries (many tiles or heads of up to 256 tokens: where that is the faster), on the bf16 one, which is up to twice as fast: every
+ * number is the sum of three bf16 numbers, 24 bits in three times 8, and six of the nine products of two numbers' parts are summed in
+ * fp32; at most 2^-24 of a product is left out.  The error against fp64 is a fifth to a quarter smaller (2,880 tokens x 128: 3.9e-7,
+ * 5.2e-7 on the fp32 instruction), but which of the two a tile gets, and with it the last bits of its output, depends on the number of
+ * tiles, heads and tokens of the call and on the device.  128 queries whose head holds numbers that the parts do not are done over on
+ * the fp32 instruction, in the same launch: |V| below 2^-100 and not 0, |V|, |K| or |Q * scale * log2(e)| of 2^60 and more, or a score
+ * 69 below the largest before it together with a V that is 0, below 2^-50 or from 2^24 on.  Such calls take 1.3 times, at worst 1.8
+ * times, what the fp32 instruction alone would.
  */
 int sg_tile_attention(const sg_problem* p, const void* q, const void* k, const void* v,
                       int32_t tile_row, int32_t tile_col, void* out_tile, void* stream);

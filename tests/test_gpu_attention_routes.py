@@ -165,7 +165,9 @@ def test_windows_of_head_dim_64_with_few_keys(heads, tokens, kernel):
     (128, 200, 5, 13, SPLIT), (128, 769, 5, 13, F32), (128, 257, 8, 16, F32), (128, 769, 1, 97, SPLIT), (128, 359, 3, 43, SPLIT)])
 def test_fp32_calls_of_several_rounds_of_short_tiles(d, heads, th, tw, kernel):
     """One round of 128-query workgroups goes to the split kernel; several of up to 256 tokens only where they hide its start and end."""
-    assert [n for n, _ in _attention_kernels(Window(heads, 1, th, tw, d, "f32", packed=True))] == [kernel]
+    w = Window(heads, 1, th, tw, d, "f32", packed=True)
+    assert [n for n, _ in _attention_kernels(w)] == [kernel]
+    assert _rel(w.out.cpu().reshape(heads, -1, d), _exact([t.cpu().reshape(heads, -1, d) for t in w.qkv], _fp32_scale(d))) <= TOLERANCE
 
 
 def _exact(x, scale):
